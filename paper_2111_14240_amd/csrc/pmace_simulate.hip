@@ -18,6 +18,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "pmace.h"
 #include "pmace_dft.hpp"
@@ -34,17 +35,26 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
   const uint32_t w0 = 0x9E3779B9u, w1 = 0xBB67AE85u;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(m0, c.x), lo0 = m0 * c.x;
-    const uint32_t hi1 = __umulhi(m1, c.z), lo1 = m1 * c.z;
-    c = make_uint4(hi1 ^ c.y ^ k.x, lo1, hi0 ^ c.w ^ k.y, lo0);
+    const uint64_t p0 = (uint64_t)m0 * c.x, p1 = (uint64_t)m1 * c.z;  // one v_mad_u64_u32 each
+    c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k.x, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ c.w ^ k.y,
+                   (uint32_t)p0);
     k.x += w0;
     k.y += w1;
   }
   return c;
 }
 
-// Uniform doubles in (0, 1) for element `idx`: block n of the stream is
-// Philox(counter = (idx lo, idx hi, n, 0x50495853), key = seed).
+// Block n of element `idx`'s stream of uniforms: Philox(counter = (idx lo,
+// idx hi, n, 0x50495853), key = seed).
+__device__ __forceinline__ uint4 uniform_block(uint32_t i0, uint32_t i1, uint32_t n, uint2 key) {
+  return philox4x32_10(make_uint4(i0, i1, n, 0x50495853u), key);
+}
+// 53 random bits, centred in their interval: never 0
+__device__ __forceinline__ double unit_double(uint32_t a, uint32_t b) {
+  return ((double)(a >> 5) * 67108864.0 + (double)(b >> 6) + 0.5) * (1.0 / 9007199254740992.0);
+}
+
+// Uniform doubles in (0, 1) for element `idx`, two from each block.
 struct Uniforms {
   uint2 key;
   uint32_t i0, i1, n;
@@ -55,15 +65,48 @@ struct Uniforms {
         i0((uint32_t)idx), i1((uint32_t)(idx >> 32)), n(0), have(0) {}
   __device__ double next() {
     if (have == 0) {
-      buf = philox4x32_10(make_uint4(i0, i1, n++, 0x50495853u), key);
+      buf = uniform_block(i0, i1, n++, key);
       have = 2;
     }
     const uint32_t a = have == 2 ? buf.x : buf.z, b = have == 2 ? buf.y : buf.w;
     --have;
-    // 53 random bits, centred in their interval: never 0 or 1
-    return ((double)(a >> 5) * 67108864.0 + (double)(b >> 6) + 0.5) * (1.0 / 9007199254740992.0);
+    return unit_double(a, b);
   }
 };
+
+// Transformed rejection (mean >= 10): one try from two uniforms.  `fast`: the
+// squeeze accepted k; else the try has still to pass the exact test.
+struct Ptrs {
+  double slam, a, b, vr;
+  __device__ __forceinline__ explicit Ptrs(double lam)
+      : slam(sqrt(lam)), a(-0.059 + 0.02483 * (0.931 + 2.53 * slam)), b(0.931 + 2.53 * slam),
+        vr(0.9277 - 3.6224 / (b - 2.0)) {}
+  __device__ __forceinline__ bool fast(double lam, double U, double V, double& us, double& k) const {
+    us = 0.5 - fabs(U);
+    k = floor((2.0 * a / us + b) * U + lam + 0.43);
+    return us >= 0.07 && V <= vr;
+  }
+};
+
+// The exact acceptance test of a try that the squeeze left open.
+__device__ __forceinline__ bool ptrs_exact(const Ptrs& t, double lam, double loglam, double invalpha,
+                                           double V, double us, double k) {
+  return log(V) + log(invalpha) - log(t.a / (us * us) + t.b) <= -lam + k * loglam - lgamma(k + 1.0);
+}
+
+// The same decision for less: one logarithm for the left side's three, and
+// Stirling's series to 1/n^5 for lgamma(n), n = k + 1 >= 8 (its error is under
+// 1/(1680 n^7) < 3e-10).  Where the two sides are nearer than that and than
+// 45 roundings of the largest term, the exact test decides.
+__device__ __forceinline__ bool ptrs_accept(const Ptrs& t, double lam, double loglam, double invalpha,
+                                            double V, double us, double k) {
+  const double n = k + 1.0, r = 1.0 / n, r2 = r * r, m = k * loglam;
+  const double lg = (n - 0.5) * log(n) - n + 0.91893853320467274 +
+                    r * (1.0 / 12.0 - r2 * (1.0 / 360.0 - r2 * (1.0 / 1260.0)));
+  const double d = log(V * invalpha / (t.a / (us * us) + t.b)) - ((m - lam) - lg);
+  if (n >= 8.0 && fabs(d) > 1e-9 + 1e-14 * (fabs(m) + lam)) return d < 0.0;
+  return ptrs_exact(t, lam, loglam, invalpha, V, us, k);
+}
 
 __device__ double poisson_draw(double lam, Uniforms& u) {
   if (!(lam > 0.0)) return 0.0;
@@ -77,20 +120,16 @@ __device__ double poisson_draw(double lam, Uniforms& u) {
     } while (p > L && k < 1000);
     return (double)(k - 1);
   }
-  const double slam = sqrt(lam), loglam = log(lam);
-  const double b = 0.931 + 2.53 * slam;
-  const double a = -0.059 + 0.02483 * b;
-  const double invalpha = 1.1239 + 1.1328 / (b - 3.4);
-  const double vr = 0.9277 - 3.6224 / (b - 2.0);
+  const Ptrs t(lam);
+  const double loglam = log(lam);
+  const double invalpha = 1.1239 + 1.1328 / (t.b - 3.4);
   for (int it = 0; it < 1000; ++it) {  // each try accepts with probability > 0.8
     const double U = u.next() - 0.5;
     const double V = u.next();
-    const double us = 0.5 - fabs(U);
-    const double k = floor((2.0 * a / us + b) * U + lam + 0.43);
-    if (us >= 0.07 && V <= vr) return k;
+    double us, k;
+    if (t.fast(lam, U, V, us, k)) return k;
     if (k < 0.0 || (us < 0.013 && V > us)) continue;
-    if (log(V) + log(invalpha) - log(a / (us * us) + b) <= -lam + k * loglam - lgamma(k + 1.0))
-      return k;
+    if (ptrs_exact(t, lam, loglam, invalpha, V, us, k)) return k;
   }
   return floor(lam + 0.5);
 }
@@ -243,14 +282,173 @@ hipError_t launch_sim_intensities(int J, const float2* d, const int2* pos, const
   return hipGetLastError();
 }
 
-__global__ void poisson_k(float* __restrict__ z, const unsigned* __restrict__ maxbits, double peak,
-                          uint64_t seed, long long total) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
+// Poisson counts in place, PER elements per thread of a workgroup.
+//
+// A diffraction pattern is dark nearly everywhere: at a peak of 1e6 photons
+// 94% of a 256^2 pattern's pixels have a mean under 0.1, 2% one of 1..10 and
+// 2.5% one of 10 and more, in clusters.  One element per thread has every wave
+// run the FP64 exponential, and the waves of a bright region run the product
+// loop, the squeeze and the exact rejection test (logarithms and a lgamma) one
+// after the other, each for a few of its lanes.  Here most elements end on
+// one integer word: the first uniform lies below (a + 1)/2^32, a its top
+// word, and the count is 0 when it is <= exp(-lam), so surely when
+// (a + 1)/2^32 <= 1 - lam (tested with slack for the float rounding of both
+// sides).  The others are listed in LDS by what they need and drawn by full
+// waves: the squeeze of the means of 10 and more, the tries that it leaves
+// open, and the product-of-uniforms draws, each lane taking the next element
+// as it finishes one.  Every element keeps its own stream and decisions, so
+// the counts are poisson_draw's, bit for bit.  Bound by the generator's
+// integer multiplies (about 17 64-bit products per element: 200 us for 900
+// patterns of 256^2) and the latency of the bright workgroups' draws.  The
+// simulate call on those: 1189 us with one element per thread, 645 now.
+constexpr int kPoisT = 256;
+// 8 waves per SIMD (64 VGPRs): the rare draws spill, the common path does not.
+// Measured, simulate call of 900 patterns of 256^2 at peak 1e6: 1122 us without
+// the bound (193 VGPRs, 2 waves), 918 at 6 waves, 934 at 8; with the rotation
+// of the groups of workgroups below 672 and 655.
+constexpr int kPoisWaves = 8;
+
+// Appends this lane's element to an LDS list (one LDS atomic per wave).
+__device__ __forceinline__ void wave_push(bool want, uint16_t v, uint16_t* list, int* count, int step) {
+  const unsigned long long m = __ballot(want);
+  if (m == 0) return;
+  const int lane = threadIdx.x & 63;
+  int at = 0;
+  if (lane == __ffsll((long long)m) - 1) at = atomicAdd(count, __popcll(m));
+  at = __builtin_amdgcn_readlane(at, __ffsll((long long)m) - 1);
+  if (want) list[step * (at + __popcll(m & ((1ull << lane) - 1)))] = v;
+}
+
+template <int PER>
+__global__ void __launch_bounds__(kPoisT, kPoisWaves) poisson_k(float* __restrict__ z,
+                                                                const unsigned* __restrict__ maxbits,
+                                                                double peak, uint64_t seed,
+                                                                long long total) {
+  constexpr int kPoisN = kPoisT * PER, kPoisIn = PER < 4 ? PER : 4;
+  static_assert((1ll << 32) % kPoisN == 0, "a workgroup's elements share the high index word");
+  // lists of elements (offsets in the block): small means from the front of
+  // `list`, larger ones from its end; `open` the larger ones the squeeze left
+  __shared__ uint16_t list[kPoisN], open[kPoisN];
+  __shared__ int n_small, n_large, n_open, next;
+  const int tid = threadIdx.x;
+  // Bright rows come at the same places of every pattern, and the dispatcher
+  // sends workgroup b to XCD b mod 8: each group of 8 is rotated by a hash of
+  // its number, or two XCDs would get most of the bright ones.
+  unsigned blk8 = blockIdx.x;
+  if ((blk8 | 7u) < gridDim.x) blk8 = (blk8 & ~7u) | ((blk8 + (((blk8 >> 3) * 0x9E3779B1u) >> 29)) & 7u);
+  const long long base = (long long)blk8 * kPoisN;
+  const int n = total - base < kPoisN ? (int)(total - base) : kPoisN;
   const double mx = (double)__uint_as_float(*maxbits);
   const double scale = mx > 0.0 ? peak / mx : 0.0;
-  Uniforms u(seed, (uint64_t)i);
-  z[i] = (float)poisson_draw((double)z[i] * scale, u);
+  const uint2 key = make_uint2((uint32_t)seed, (uint32_t)(seed >> 32));
+  const uint32_t b0 = (uint32_t)base, b1 = (uint32_t)((unsigned long long)base >> 32);
+  float* zb = z + base;
+  if (tid == 0) n_small = n_large = n_open = next = 0;
+  __syncthreads();
+  // kPoisIn elements of a thread in flight at a time
+#pragma unroll 1
+  for (int k0 = 0; k0 < PER; k0 += kPoisIn) {
+    float zv[kPoisIn];
+#pragma unroll
+    for (int k = 0; k < kPoisIn; ++k) {
+      const int i = tid + (k0 + k) * kPoisT;
+      zv[k] = i < n ? zb[i] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < kPoisIn; ++k) {
+      const int i = tid + (k0 + k) * kPoisT;
+      const double lam = (double)zv[k] * scale;
+      const bool pos = lam > 0.0;            // false for NaN: those draw 0, as do the zeros
+      const uint32_t a = uniform_block(b0 + (uint32_t)i, b1, 0u, key).x;
+      const bool zero =
+          !pos || (float)(~a) * 0.999999f >= fmaf((float)lam, 4294967296.f * 1.000001f, 1.f);
+      if (zero && i < n) zb[i] = 0.f;
+      wave_push(!zero && lam < 10.0, (uint16_t)i, list, &n_small, 1);
+      wave_push(!zero && !(lam < 10.0), (uint16_t)i, list + kPoisN - 1, &n_large, -1);
+    }
+  }
+  __syncthreads();
+  // means of 10 and more: the first try's squeeze
+  const int nl = n_large, ns = n_small;
+  for (int e = tid; e < ((nl + 63) & ~63); e += kPoisT) {
+    int i = 0;
+    bool left = false;
+    if (e < nl) {
+      i = list[kPoisN - 1 - e];
+      const double lam = (double)zb[i] * scale;
+      const uint4 w = uniform_block(b0 + (uint32_t)i, b1, 0u, key);
+      const Ptrs t(lam);
+      double us, k;
+      left = !t.fast(lam, unit_double(w.x, w.y) - 0.5, unit_double(w.z, w.w), us, k);
+      if (!left) zb[i] = (float)k;
+    }
+    wave_push(left, (uint16_t)i, open, &n_open, 1);
+  }
+  __syncthreads();
+  // ... and what it left open: from the same try on
+  for (int e = tid; e < n_open; e += kPoisT) {
+    const int i = open[e];
+    const double lam = (double)zb[i] * scale;
+    const Ptrs t(lam);
+    const double loglam = log(lam);
+    const double invalpha = 1.1239 + 1.1328 / (t.b - 3.4);
+    double k = 0.0;
+    int it = 0;
+    for (; it < 1000; ++it) {
+      const uint4 w = uniform_block(b0 + (uint32_t)i, b1, (uint32_t)it, key);
+      const double V = unit_double(w.z, w.w);
+      double us;
+      if (t.fast(lam, unit_double(w.x, w.y) - 0.5, V, us, k)) break;
+      if (k < 0.0 || (us < 0.013 && V > us)) continue;
+      if (ptrs_accept(t, lam, loglam, invalpha, V, us, k)) break;
+    }
+    zb[i] = (float)(it < 1000 ? k : floor(lam + 0.5));
+  }
+  // means below 10: the product of uniforms passes exp(-lam), two factors per
+  // block of the stream
+  int i = -1, k = 0;
+  uint32_t blk = 0;
+  double p = 1.0, L = 0.0;
+  for (;;) {
+    if (i < 0) {
+      const int e = atomicAdd(&next, 1);
+      if (e >= ns) break;
+      i = list[e];
+      L = exp(-((double)zb[i] * scale));
+      p = 1.0;
+      k = 0;
+      blk = 0;
+    }
+    const uint4 w = uniform_block(b0 + (uint32_t)i, b1, blk++, key);
+    p *= unit_double(w.x, w.y);
+    bool done = !(p > L) || ++k >= 1000;
+    if (!done) {
+      p *= unit_double(w.z, w.w);
+      done = !(p > L) || ++k >= 1000;
+    }
+    if (done) {
+      zb[i] = (float)(k < 1000 ? k : 999);
+      i = -1;
+    }
+  }
+}
+
+// Elements per thread: with 16, lists are long enough for full waves, once
+// there are 8 such workgroups per CU; smaller totals are spread over more
+// workgroups, as their time is one workgroup's latency.  Measured, simulate
+// calls with 1 / 4 / 16 elements per thread: 36 patterns of 32^2 68 / 70 / 80
+// us, 200 of 48^2 76.6 / 76.3 / 82, 300 of 160^2 181 / 156 / 158, 300 of
+// 256^2 328 / 268 / 245.
+void launch_poisson(float* z, const unsigned* maxbits, double peak, uint64_t seed, long long total,
+                    hipStream_t st) {
+  const auto go = [&](auto per) {
+    constexpr int PER = decltype(per)::value, N = kPoisT * PER;
+    hipLaunchKernelGGL(poisson_k<PER>, dim3((unsigned)((total + N - 1) / N)), dim3(kPoisT), 0, st, z, maxbits,
+                       peak, seed, total);
+  };
+  if (total >= 2048ll * 4096) go(std::integral_constant<int, 16>());
+  else if (total >= 128ll * 1024) go(std::integral_constant<int, 4>());
+  else go(std::integral_constant<int, 1>());
 }
 
 __global__ void philox_k(uint32_t* io, int n) {
@@ -324,8 +522,7 @@ pmace_status run_simulation(int32_t n2, int32_t np, int32_t num_pos, const void*
   }
   if (e != hipSuccess) return PMACE_EDEVICE;
   if (peak_photons > 0.0)
-    hipLaunchKernelGGL(pmace::poisson_k, dim3(nblocks(total, 256)), dim3(256), 0, st, z_d, maxbits,
-                       peak_photons, seed, total);
+    pmace::launch_poisson(z_d, maxbits, peak_photons, seed, total, st);
   if (hipGetLastError() != hipSuccess) return PMACE_EDEVICE;
   if (scale_out) {
     unsigned mb = 0;
