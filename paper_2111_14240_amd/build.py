@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpmace.so")
 DEMO = os.path.join(HERE, "pmace_demo")
 TUNED = os.path.join(HERE, "tuned.json")
-SOURCES = ["pmace_api.hip", "pmace_kernels.hip", "pmace_simulate.hip"]
+SOURCES = ["pmace_api.hip", "pmace_setup.hip", "pmace_kernels.hip", "pmace_simulate.hip"]
 
 # Packed FP32 VALU forms are kept out of the generated code on purpose, and
 # floating-point contraction is off: every fused multiply-add is written out in

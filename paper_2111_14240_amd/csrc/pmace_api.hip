@@ -1,14 +1,12 @@
 // C ABI of libpmace.so (declared in include/pmace.h).
 //
-// Host responsibilities: argument validation, the workspace layout, the FP64
-// tables computed once per reconstruction (|d|^kappa, d^{-1}, Lambda^{-1} of
-// eq. (11)), the consensus tile tables, and replaying iterations as HIP
-// graphs (one per reconstruction, one per batch).
+// Host responsibilities: argument validation, the workspace layout, the order
+// of the set-up (its tables and lists are built on the device), and replaying
+// iterations as HIP graphs (one per reconstruction, one per batch).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
-#include <complex>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -54,12 +52,10 @@ struct pmace_ctx {
   int device;
   Recon h;                        // host copy of the device descriptor
   Recon* dev;                     // device descriptor (in the workspace)
-  int2* items;                    // device: (0, j) agent work items
-  int2* gitems;                   // device: (0, tile) gather work items
   int2* ritems;                   // device: (0, b) NRMSE reduction items
   int* fitem;                     // device: {0}
-  int ngitems;
-  std::vector<int2> chunk_tiles;  // host: per chunk (first gather item, count)
+  int ngitems;                    // gather tiles of all chunks
+  std::vector<int2> chunk_tiles;  // host: per chunk (first gather tile, count)
   std::vector<int2> chunk_rows;   // host, row-spectrum states: per chunk (first row item, count)
   Graph graph;                    // one iteration
   Graph graph_k;                  // kGraphIters iterations back to back
@@ -167,7 +163,7 @@ pmace_status check_params(const pmace_params* p) {
 // Section offsets inside the workspace (relative to the aligned base).
 struct Layout {
   size_t t, ys, pos, d, pc, dinv, gw, omega64, laminv, num, sold, xbar, xhat, stage, tiles, list, status, desc,
-      items, gitems, ritems, red, tw, fit, dr, qtiles, qlist, citems, clist, total;
+      ritems, red, tw, fit, dr, qtiles, qlist, citems, clist, order, total;
 };
 
 // Patch sides whose default agent is the split (coset-block) one: a build
@@ -249,13 +245,10 @@ size_t stage_patches(const pmace_params& p) {
 // Data-fit partial sums per patch: one, or one per column block for Np > 128.
 int fit_bpp(const pmace_params& p) { return np_large(p.np) ? p.np / PMACE_CB : 1; }
 
-// Launch order of one row of tiles t[first, end), left to right. The
-// dispatcher sends workgroup b to XCD b mod 8, and each XCD has its own L2.
-// Side-by-side tiles read the same state lines at their common edge, so slot
-// b gets tile (b mod 8) * q + b / 8 of the row (q = n / 8; the last n mod 8
-// stay in place): each XCD runs q side-by-side tiles of every row, and the
-// second read of an edge line hits its L2. Only which workgroup sums which
-// pixel changes; every pixel's sum is the same.
+// Launch order of one row of the split consensus's base tiles t[first, end),
+// left to right, so that each XCD runs side-by-side tiles (as setup_tiles_k
+// does for the gather tiles).  Only which workgroup sums which pixel changes;
+// every pixel's sum is the same.
 void xcd_runs(std::vector<int4>& t, size_t first, size_t end) {
   const size_t q = (end - first) / 8;
   if (q == 0) return;
@@ -271,6 +264,9 @@ Layout layout_of(const pmace_params& p) {
   size_t o = 0;
   L.t = o;       o = align_up(o + P * 8);
   L.ys = o;      o = align_up(o + P * 4);
+  // status word, stop flag, finish item, track[8] at +32, list cursors at +96;
+  // the positions follow, so the set-up reads both back in one copy
+  L.status = o;  o += kAlign;
   L.pos = o;     o = align_up(o + (size_t)p.num_pos * 8);
   L.d = o;       o = align_up(o + np2 * 8);
   L.pc = o;      o = align_up(o + np2 * 16);
@@ -287,10 +283,7 @@ Layout layout_of(const pmace_params& p) {
   L.stage = o;   o = align_up(o + std::max(stage_patches(p) * np2 * 8, sp ? 4 * npx * 8 : (size_t)0));
   L.tiles = o;   o = align_up(o + max_tiles(p) * 16);
   L.list = o;    o = align_up(o + max_list(p) * 4);
-  L.status = o;  o = align_up(o + 128);  // status word, stop flag, finish item, track[8] at +32
   L.desc = o;    o = align_up(o + sizeof(Recon));
-  L.items = o;   o = align_up(o + (size_t)p.num_pos * 8);
-  L.gitems = o;  o = align_up(o + max_tiles(p) * 8);
   L.ritems = o;  o = align_up(o + (size_t)num_red(p) * 8);
   L.red = o;     o = align_up(o + (size_t)num_red(p) * 32);
   L.tw = o;      o = align_up(o + 256 * 8);
@@ -301,6 +294,7 @@ Layout layout_of(const pmace_params& p) {
   const bool rs = rowspec_allowed(p);
   L.citems = o;  o = align_up(o + (rs ? cr_items(p) * 16 : 0));
   L.clist = o;   o = align_up(o + (rs ? cr_list(p) * 16 : 0));
+  L.order = o;   o = align_up(o + (rs ? (size_t)p.num_pos * 16 : 0));
   L.total = o;
   return L;
 }
@@ -404,190 +398,8 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
 
   const int np = p.np, J = p.num_pos, n1 = p.n1, n2 = p.n2;
-  const size_t np2 = (size_t)np * np, npx = (size_t)n1 * n2;
-
-  // Small inputs come to the host for validation and the FP64 tables.
-  std::vector<std::complex<float>> probe(np2);
-  std::vector<int32_t> pos(2 * (size_t)J);
-  PM_HIP(hipMemcpyAsync(probe.data(), probe_d, np2 * 8, hipMemcpyDeviceToHost, st));
-  PM_HIP(hipMemcpyAsync(pos.data(), pos_d, (size_t)J * 8, hipMemcpyDeviceToHost, st));
-  PM_HIP(hipStreamSynchronize(st));
-  for (int j = 0; j < J; ++j) {
-    const int r = pos[2 * j], c = pos[2 * j + 1];
-    if (r < 0 || c < 0 || r > n1 - np || c > n2 - np) return PMACE_EINVAL;
-  }
-  for (auto& v : probe)
-    if (!std::isfinite(v.real()) || !std::isfinite(v.imag())) return PMACE_EINVAL;
-
-  // |d|^kappa, d^{-1} (scaled by 1/Np^2: the unnormalised forward+inverse
-  // DFT pair), the d == 0 mask, and Lambda^{-1} (0 where Lambda = 0).
-  // SHARP+ (eq. (15)): weights conj(d) over the normaliser sum_k P_k^t |d|^2.
   const bool sharp = p.method == PMACE_METHOD_SHARP_PLUS;
-  std::vector<float> pc(4 * np2), gw(2 * np2, 0.f), dinv(2 * np2, 0.f);
-  bool has_zero = false;
-  std::vector<double> omega(np2);
   const double inv_np2 = 1.0 / ((double)np * np);
-  for (size_t i = 0; i < np2; ++i) {
-    const std::complex<double> dd(probe[i].real(), probe[i].imag());
-    const double mag = std::abs(dd);
-    if (sharp) {
-      omega[i] = mag * mag;
-      pc[4 * i + 0] = (float)(dd.real() * inv_np2);
-      pc[4 * i + 1] = (float)(-dd.imag() * inv_np2);
-      pc[4 * i + 2] = (float)dd.real();
-      pc[4 * i + 3] = (float)(-dd.imag());
-      continue;
-    }
-    omega[i] = std::pow(mag, (double)p.kappa);
-    std::complex<double> di(0.0, 0.0);
-    if (mag != 0.0) {
-      di = inv_np2 / dd;
-      const std::complex<double> w = omega[i] / dd;  // weights on the stored d t
-      gw[2 * i + 0] = (float)w.real();
-      gw[2 * i + 1] = (float)w.imag();
-    } else {
-      has_zero = true;   // the stored state is t itself there: weight |d|^kappa (1 if kappa = 0)
-      gw[2 * i + 0] = (float)omega[i];
-    }
-    pc[4 * i + 0] = (float)di.real();
-    pc[4 * i + 1] = (float)di.imag();
-    dinv[2 * i + 0] = pc[4 * i + 0];
-    dinv[2 * i + 1] = pc[4 * i + 1];
-    // d != 0 must not round to the d == 0 marker: keep the smallest subnormal
-    if (mag != 0.0 && dinv[2 * i] == 0.f && dinv[2 * i + 1] == 0.f) dinv[2 * i] = 1e-45f;
-    pc[4 * i + 2] = (float)omega[i];
-    pc[4 * i + 3] = mag == 0.0 ? 1.f : 0.f;
-  }
-  // Lambda = sum_j P_j^t omega and its inverse are formed on the device from
-  // the FP64 weights and the consensus tile lists (see launch_init).
-
-  // Split layout: the window weights 2 rho d (FP64, rounded once) and the
-  // base tiles of its consensus.
-  const bool split = split_allowed(p) && !has_zero;
-  const int M = np / 2;
-  std::vector<float> dr;
-  std::vector<int4> qtiles;
-  std::vector<int> qlist;
-  if (split) {
-    dr.assign(2 * np2, 0.f);
-    for (size_t i = 0; i < np2; ++i) {
-      dr[2 * i] = (float)(2.0 * (double)p.rho * (double)probe[i].real());
-      dr[2 * i + 1] = (float)(2.0 * (double)p.rho * (double)probe[i].imag());
-    }
-    const int qr = split_rows(p) / pmace::QT_R, qc = split_cols(p) / pmace::QT_C;
-    std::vector<std::vector<int>> per_tile((size_t)qr * qc);
-    for (int j = 0; j < J; ++j) {
-      const int r = pos[2 * j], cc = pos[2 * j + 1];
-      for (int tr = r / pmace::QT_R; tr <= (r + M - 1) / pmace::QT_R && tr < qr; ++tr)
-        for (int tc = cc / pmace::QT_C; tc <= (cc + M - 1) / pmace::QT_C && tc < qc; ++tc)
-          per_tile[(size_t)tr * qc + tc].push_back(j);
-    }
-    for (int tr = 0; tr < qr; ++tr) {
-      const size_t row0 = qtiles.size();
-      for (int tc = 0; tc < qc; ++tc) {
-        const auto& l = per_tile[(size_t)tr * qc + tc];
-        qtiles.push_back(make_int4((int)qlist.size(), (int)l.size(), tr * pmace::QT_R, tc * pmace::QT_C));
-        qlist.insert(qlist.end(), l.begin(), l.end());
-      }
-      xcd_runs(qtiles, row0, qtiles.size());
-    }
-    if (qtiles.size() > split_tiles(p) || qlist.size() > split_list(p)) return PMACE_EDEVICE;
-  }
-
-  // Gather tables: per chunk, GT_R x GT_C tiles over the rows its patches
-  // cover, each with the chunk's positions overlapping it in ascending order.
-  const int chunk = chunk_of(p);
-  const int nch = num_chunks(p);
-  const int tiles_c = (n2 + pmace::GT_C - 1) / pmace::GT_C;
-  std::vector<int4> tiles;
-  std::vector<int> list;
-  std::vector<int2> gitems, chunk_tiles(nch);
-  {
-    std::vector<std::vector<int>> per_tile;
-    for (int g = 0; g < nch; ++g) {
-      const int ja = g * chunk, jb = std::min(J, ja + chunk);
-      int lo = n1, hi = 0;
-      for (int j = ja; j < jb; ++j) {
-        lo = std::min(lo, pos[2 * j]);
-        hi = std::max(hi, pos[2 * j] + np);
-      }
-      const int tiles_r = (hi - lo + pmace::GT_R - 1) / pmace::GT_R;
-      per_tile.assign((size_t)tiles_r * tiles_c, {});
-      for (int j = ja; j < jb; ++j) {
-        const int r = pos[2 * j] - lo, cc = pos[2 * j + 1];
-        for (int tr = r / pmace::GT_R; tr <= (r + np - 1) / pmace::GT_R; ++tr)
-          for (int tc = cc / pmace::GT_C; tc <= (cc + np - 1) / pmace::GT_C; ++tc)
-            per_tile[(size_t)tr * tiles_c + tc].push_back(j);
-      }
-      chunk_tiles[g] = make_int2((int)gitems.size(), 0);
-      size_t row0 = tiles.size();
-      for (size_t t = 0; t < per_tile.size(); ++t) {
-        if (t % tiles_c == 0) {
-          if (np_large(np)) xcd_runs(tiles, row0, tiles.size());
-          row0 = tiles.size();
-        }
-        if (per_tile[t].empty()) continue;
-        const int tr = (int)(t / tiles_c), tc = (int)(t % tiles_c);
-        gitems.push_back(make_int2(0, (int)tiles.size()));
-        tiles.push_back(make_int4((int)list.size(), (int)per_tile[t].size(), lo + tr * pmace::GT_R,
-                                  tc * pmace::GT_C));
-        list.insert(list.end(), per_tile[t].begin(), per_tile[t].end());
-      }
-      if (np_large(np)) xcd_runs(tiles, row0, tiles.size());
-      chunk_tiles[g].y = (int)gitems.size() - chunk_tiles[g].x;
-    }
-  }
-  if (tiles.size() > max_tiles(p) || list.size() > max_list(p)) return PMACE_EDEVICE;
-
-  // Row-spectrum states: per chunk, one item per object row its patches cover
-  // and CR_W-wide segment of that row, listing the chunk's positions whose
-  // patch covers the row and meets the segment, in ascending j.
-  const bool rowspec = rowspec_allowed(p) && (sharp || !has_zero);
-  std::vector<int4> citems, clist;
-  std::vector<int2> chunk_rows(nch, make_int2(0, 0));
-  if (rowspec) {
-    const int nseg = cr_segments(p);
-    const int rn = pmace::cr_round(np);
-    std::vector<std::vector<int4>> per_row;
-    for (int g = 0; g < nch; ++g) {
-      const int ja = g * chunk, jb = std::min(J, ja + chunk);
-      int lo = n1, hi = 0;
-      for (int j = ja; j < jb; ++j) {
-        lo = std::min(lo, pos[2 * j]);
-        hi = std::max(hi, pos[2 * j] + np);
-      }
-      per_row.assign((size_t)(hi - lo) * nseg, {});
-      for (int j = ja; j < jb; ++j) {
-        const int r = pos[2 * j], cc = pos[2 * j + 1];
-        for (int sg = cc / pmace::CR_W; sg <= (cc + np - 1) / pmace::CR_W; ++sg)
-          for (int rr = 0; rr < np; ++rr)
-            per_row[(size_t)(r + rr - lo) * nseg + sg].push_back(make_int4(j, rr, cc, 0));
-      }
-      chunk_rows[g] = make_int2((int)citems.size(), 0);
-      for (size_t t = 0; t < per_row.size(); ++t) {
-        if (per_row[t].empty()) continue;
-        // By patch row, so that a round's rows share few weight rows (read
-        // once into the cache), then each round by patch column, so the
-        // entries covering a run of pixels are consecutive in it; ties in
-        // ascending j.  The consensus sums each pixel in this order.
-        auto& l = per_row[t];
-        std::stable_sort(l.begin(), l.end(), [](const int4& a, const int4& b) { return a.y < b.y; });
-        for (size_t r0 = 0; r0 < l.size(); r0 += (size_t)rn)
-          std::stable_sort(l.begin() + r0, l.begin() + std::min(l.size(), r0 + (size_t)rn),
-                           [](const int4& a, const int4& b) { return a.z < b.z; });
-        citems.push_back(make_int4((int)clist.size(), (int)per_row[t].size(), lo + (int)(t / nseg),
-                                   (int)(t % nseg) * pmace::CR_W));
-        clist.insert(clist.end(), per_row[t].begin(), per_row[t].end());
-      }
-      chunk_rows[g].y = (int)citems.size() - chunk_rows[g].x;
-    }
-    if (citems.size() > cr_items(p) || clist.size() > cr_list(p)) return PMACE_EDEVICE;
-  }
-  std::vector<int2> items(J);
-  for (int j = 0; j < J; ++j) items[j] = make_int2(0, j);
-  const int nred = num_red(p);
-  std::vector<int2> ritems(nred);
-  for (int b = 0; b < nred; ++b) ritems[b] = make_int2(0, b);
 
   pmace_ctx* c = new (std::nothrow) pmace_ctx();
   if (!c) return PMACE_ENOMEM;
@@ -597,6 +409,10 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   c->graph_tried = false;
   c->resets = 0;
   if (hipGetDevice(&c->device) != hipSuccess) { delete c; return PMACE_EDEVICE; }
+  auto fail = [&](pmace_status e) {
+    pmace_destroy(c);
+    return e;
+  };
 
   const Layout L = layout_of(p);
   char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<size_t>(workspace_d)));
@@ -622,21 +438,19 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   h.done = reinterpret_cast<int*>(base + L.status + 4);
   c->fitem = reinterpret_cast<int*>(base + L.status + 8);
   h.track = reinterpret_cast<double*>(base + L.status + 32);
+  h.cursor = reinterpret_cast<int*>(base + L.status + 96);
   h.red = reinterpret_cast<double*>(base + L.red);
   h.twn = reinterpret_cast<float2*>(base + L.tw);
   h.fit = reinterpret_cast<double*>(base + L.fit);
-  h.fit_bpp = split ? 4 : fit_bpp(p);
-  h.split = split ? 1 : 0;
   h.dr = reinterpret_cast<float2*>(base + L.dr);
   h.part = h.stage;   // the split layout keeps its partial sums where the stage would be
   h.qtiles = reinterpret_cast<int4*>(base + L.qtiles);
   h.qlist = reinterpret_cast<int*>(base + L.qlist);
   h.qrows = split_rows(p);
   h.qcols = split_cols(p);
-  h.nqt = (int)qtiles.size();
-  h.rowspec = rowspec ? 1 : 0;
   h.citems = reinterpret_cast<int4*>(base + L.citems);
   h.clist = reinterpret_cast<int4*>(base + L.clist);
+  h.order = reinterpret_cast<int4*>(base + L.order);
   h.xref = nullptr;
   h.mask = nullptr;
   h.n1 = n1;
@@ -662,71 +476,110 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
     const double rho = p.rho, a = (double)p.alpha / (1.0 + (double)p.alpha);
     h.sb = (float)((1.0 - 2.0 * rho * a) * inv_np2);
     h.s2r = (float)(2.0 * rho * inv_np2);
-    h.has_zero = has_zero ? 1 : 0;
     h.cx = (float)(2.0 * (1.0 - rho));
     h.co = (float)((1.0 - rho) / rho);
     h.cn = (float)(1.0 / rho);
   }
+  const int chunk = chunk_of(p), nch = num_chunks(p);
   h.chunk = chunk;
-  h.nt_stage = rowspec && (double)std::min(chunk, p.num_pos) * np * np * 8.0 > 512.0 * (1 << 20) ? 1 : 0;
-  h.n_red = nred;
+  h.n_red = num_red(p);
   h.ppw = p.ppw > 0 ? p.ppw : pmace::default_ppw(p.np);
   c->dev = reinterpret_cast<Recon*>(base + L.desc);
-  c->items = reinterpret_cast<int2*>(base + L.items);
-  c->gitems = reinterpret_cast<int2*>(base + L.gitems);
   c->ritems = reinterpret_cast<int2*>(base + L.ritems);
-  c->ngitems = (int)gitems.size();
-  c->chunk_tiles = chunk_tiles;
-  c->chunk_rows = chunk_rows;
 
-  const int zero = 0;
-  std::vector<float> tw(512);
-  for (int m = 0; m < np; ++m) {
-    const double cv = std::cos(-2.0 * M_PI * m / np), sv = std::sin(-2.0 * M_PI * m / np);
-    tw[2 * m] = std::fabs(cv) < 1e-15 ? 0.f : (float)cv;       // exact zeros at quarter turns
-    tw[2 * m + 1] = std::fabs(sv) < 1e-15 ? 0.f : (float)sv;
-  }
-  auto fail = [&](pmace_status e) {
-    pmace_destroy(c);
-    return e;
+  // Everything that reads the caller's arrays; then the status word and the
+  // positions (checked on the device) come to the host in one copy.
+  pmace::SetupInputs in;
+  in.probe = reinterpret_cast<const float2*>(probe_d);
+  in.pos = reinterpret_cast<const int2*>(pos_d);
+  in.z = intensity_d;
+  in.x0 = reinterpret_cast<const float2*>(x0_d);
+  in.yscale = (float)((double)np / (sharp ? 1.0 : 1.0 + (double)p.alpha));
+  in.centered = (p.flags & PMACE_CENTERED_DC) ? 1 : 0;
+  in.kappa = (double)p.kappa;
+  in.rho = (double)p.rho;
+  in.split_allowed = split_allowed(p) ? 1 : 0;
+  in.rowspec_allowed = rowspec_allowed(p) ? 1 : 0;
+  if (pmace::launch_setup_inputs(h, in, c->fitem, st) != hipSuccess) return fail(PMACE_EDEVICE);
+  std::vector<int32_t> back(kAlign / 4 + 2 * (size_t)J);
+  const auto read_back = [&](size_t bytes) {
+    return hipMemcpyAsync(back.data(), base + L.status, bytes, hipMemcpyDeviceToHost, st) == hipSuccess &&
+           hipStreamSynchronize(st) == hipSuccess;
   };
-  if (hipMemcpyAsync(h.pos, pos.data(), (size_t)J * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.d, probe.data(), np2 * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.pc, pc.data(), np2 * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.gw, gw.data(), np2 * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.dinv, dinv.data(), np2 * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.omega64, omega.data(), np2 * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.tiles, tiles.data(), tiles.size() * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
-      (!list.empty() &&
-       hipMemcpyAsync(h.tile_list, list.data(), list.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess) ||
-      hipMemcpyAsync(c->items, items.data(), items.size() * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      (!gitems.empty() &&
-       hipMemcpyAsync(c->gitems, gitems.data(), gitems.size() * 8, hipMemcpyHostToDevice, st) != hipSuccess) ||
-      hipMemcpyAsync(c->ritems, ritems.data(), ritems.size() * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(c->fitem, &zero, 4, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(h.twn, tw.data(), (size_t)np * 8, hipMemcpyHostToDevice, st) != hipSuccess ||
-      (split &&
-       (hipMemcpyAsync(h.dr, dr.data(), dr.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(h.qtiles, qtiles.data(), qtiles.size() * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
+  if (!read_back(back.size() * 4)) return fail(PMACE_EDEVICE);
+  const int32_t* pos = back.data() + kAlign / 4;
+  constexpr unsigned kBad = pmace::kStatusBadIntensity | pmace::kStatusBadProbe | pmace::kStatusBadPosition;
+  unsigned status = (unsigned)back[0];
+  if (status & kBad) return fail(PMACE_EINVAL);
+  h.has_zero = !sharp && (status & pmace::kStatusProbeZero) ? 1 : 0;
+  h.split = in.split_allowed && !h.has_zero ? 1 : 0;
+  h.rowspec = in.rowspec_allowed && !h.has_zero ? 1 : 0;
+  h.fit_bpp = h.split ? 4 : fit_bpp(p);
+  h.nt_stage =
+      h.rowspec && (double)std::min(chunk, p.num_pos) * np * np * 8.0 > 512.0 * (1 << 20) ? 1 : 0;
+
+  // Split layout: the base tiles of its consensus, each with the positions
+  // whose quadrant-0 block meets it in ascending order.
+  const int M = np / 2;
+  std::vector<int4> qtiles;
+  std::vector<int> qlist;
+  if (h.split) {
+    const int qr = split_rows(p) / pmace::QT_R, qc = split_cols(p) / pmace::QT_C;
+    std::vector<std::vector<int>> per_tile((size_t)qr * qc);
+    for (int j = 0; j < J; ++j) {
+      const int r = pos[2 * j], cc = pos[2 * j + 1];
+      for (int tr = r / pmace::QT_R; tr <= (r + M - 1) / pmace::QT_R && tr < qr; ++tr)
+        for (int tc = cc / pmace::QT_C; tc <= (cc + M - 1) / pmace::QT_C && tc < qc; ++tc)
+          per_tile[(size_t)tr * qc + tc].push_back(j);
+    }
+    for (int tr = 0; tr < qr; ++tr) {
+      const size_t row0 = qtiles.size();
+      for (int tc = 0; tc < qc; ++tc) {
+        const auto& l = per_tile[(size_t)tr * qc + tc];
+        qtiles.push_back(make_int4((int)qlist.size(), (int)l.size(), tr * pmace::QT_R, tc * pmace::QT_C));
+        qlist.insert(qlist.end(), l.begin(), l.end());
+      }
+      xcd_runs(qtiles, row0, qtiles.size());
+    }
+    if (qtiles.size() > split_tiles(p) || qlist.size() > split_list(p)) return fail(PMACE_EDEVICE);
+    h.nqt = (int)qtiles.size();
+    if (hipMemcpyAsync(h.qtiles, qtiles.data(), qtiles.size() * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
         (!qlist.empty() &&
-         hipMemcpyAsync(h.qlist, qlist.data(), qlist.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess))) ||
-      (rowspec && !citems.empty() &&
-       (hipMemcpyAsync(h.citems, citems.data(), citems.size() * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(h.clist, clist.data(), clist.size() * 16, hipMemcpyHostToDevice, st) != hipSuccess)) ||
-      hipMemsetAsync(h.status, 0, 4, st) != hipSuccess ||
-      hipMemcpyAsync(c->dev, &c->h, sizeof(Recon), hipMemcpyHostToDevice, st) != hipSuccess)
+         hipMemcpyAsync(h.qlist, qlist.data(), qlist.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess))
+      return fail(PMACE_EDEVICE);
+  }
+  // (where the split agent is allowed the amplitudes and states had to wait)
+  if (in.split_allowed && pmace::launch_setup_states(h, in, st) != hipSuccess) return fail(PMACE_EDEVICE);
+
+  // The rows that each chunk covers give its gather tiles (GT_R x GT_C object
+  // pixels) and row items; their lists are built on the device.
+  const int tiles_c = (n2 + pmace::GT_C - 1) / pmace::GT_C, nseg = cr_segments(p);
+  std::vector<pmace::SetupChunk> chunks(nch);
+  c->chunk_tiles.assign(nch, make_int2(0, 0));
+  c->chunk_rows.assign(nch, make_int2(0, 0));
+  int tile0 = 0, item0 = 0;
+  for (int g = 0; g < nch; ++g) {
+    const int ja = g * chunk, jb = std::min(J, ja + chunk);
+    int lo = n1, hi = 0;
+    for (int j = ja; j < jb; ++j) {
+      lo = std::min(lo, pos[2 * j]);
+      hi = std::max(hi, pos[2 * j] + np);
+    }
+    const int tiles_r = (hi - lo + pmace::GT_R - 1) / pmace::GT_R, nitems = h.rowspec ? (hi - lo) * nseg : 0;
+    chunks[g] = {ja, jb, lo, tiles_r, tile0, nitems, item0};
+    c->chunk_tiles[g] = make_int2(tile0, tiles_r * tiles_c);
+    c->chunk_rows[g] = make_int2(item0, nitems);
+    tile0 += tiles_r * tiles_c;
+    item0 += nitems;
+  }
+  c->ngitems = tile0;
+  if (pmace::launch_setup_tables(h, c->dev, c->ritems, chunks.data(), nch, tiles_c, nseg, pmace::cr_round(np),
+                                 st) != hipSuccess)
     return fail(PMACE_EDEVICE);
-  hipLaunchKernelGGL(reset_tracking_k, dim3(1), dim3(1), 0, st, h.done, h.track);
-  const float yscale = (float)((double)np / (sharp ? 1.0 : 1.0 + (double)p.alpha));
-  if (hipGetLastError() != hipSuccess ||
-      pmace::launch_init(h, c->dev, intensity_d, yscale, (p.flags & PMACE_CENTERED_DC) ? 1 : 0,
-                         reinterpret_cast<const float2*>(x0_d), c->chunk_tiles.data(), st) != hipSuccess)
-    return fail(PMACE_EDEVICE);
-  unsigned status = 0;
-  if (hipMemcpyAsync(&status, h.status, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return fail(PMACE_EDEVICE);
-  if (status & 2u) return fail(PMACE_EINVAL);
+  if (in.split_allowed) {  // the inputs were still being read
+    if (!read_back(4)) return fail(PMACE_EDEVICE);
+    if ((unsigned)back[0] & kBad) return fail(PMACE_EINVAL);
+  }
   *out = c;
   return PMACE_OK;
 }

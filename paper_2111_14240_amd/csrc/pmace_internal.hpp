@@ -81,6 +81,11 @@ constexpr int CR_T = PMACE_CR_T, CR_W = PMACE_CR_W;
 int cr_round(int np);
 static_assert(CR_T % 64 == 0 && CR_T <= 1024 && CR_W % CR_T == 0 && CR_W >= 256, "row consensus shape");
 
+// Status word of a reconstruction: a non-finite consensus image, and what the
+// set-up found in the caller's arrays.
+constexpr unsigned kStatusNonFinite = 1, kStatusBadIntensity = 2, kStatusBadProbe = 4,
+                   kStatusProbeZero = 8, kStatusBadPosition = 16;
+
 // Device-resident description of one reconstruction.  It lives in the
 // reconstruction's workspace; batched launches read an array of them.
 struct Recon {
@@ -104,7 +109,7 @@ struct Recon {
   float2* twn;          // Np       W_Np^m = exp(-2 pi i m/Np), FP64-rounded twiddles
   int4* tiles;          // per gather tile: (list start, count, first row, first col)
   int* tile_list;       // positions overlapping each tile, ascending
-  unsigned* status;     // bit0: non-finite consensus image; bit1: bad intensity
+  unsigned* status;     // kStatus* bits
   int* done;            // stop flag: nonzero = skip this reconstruction's work
   float2* xref;         // NRMSE reference object, null if none
   unsigned char* mask;  // NRMSE region (nonzero = inside), null = every pixel
@@ -155,14 +160,40 @@ struct Recon {
   // from the cache on their way to the column pass)
   int nt_stage;
   int4* citems;         // per (chunk, object row, segment): (list start, count, row, first column)
-  int4* clist;          // per entry: (j, row of P_j on that object row, patch column, 0), ascending j
+  int4* clist;          // per entry: (j, row of P_j on that object row, patch column, 0), in summing order
+  // set-up only
+  int* cursor;          // {entries taken of tile_list, of clist}
+  int4* order;          // row-spectrum agent: a chunk's positions by descending row, (j, row, column, 0)
+};
+
+// What the set-up reads of the caller's (device arrays), and how.
+struct SetupInputs {
+  const float2* probe;
+  const int2* pos;
+  const float* z;
+  const float2* x0;     // null: 1 + 0i everywhere
+  float yscale;         // ys = yscale sqrt(z)
+  int centered;
+  double kappa, rho;
+  int split_allowed, rowspec_allowed;
+};
+// A chunk of positions [ja, jb): the object rows [lo, lo + tiles_r GT_R) that
+// its patches cover, its first gather tile and its row items.
+struct SetupChunk {
+  int ja, jb, lo, tiles_r, tile0, nitems, item0;
 };
 
 // Kernel launchers (stream-ordered; return the hipError_t of the launches).
 // `rec` / `recs` are device addresses of Recon descriptors, `h` a host copy.
-// PMACE also forms S of the initial states (per chunk, chunk_tiles as below).
-hipError_t launch_init(const Recon& h, const Recon* rec, const float* z, float scale, int centered,
-                       const float2* x0, const int2* chunk_tiles, hipStream_t st);
+// Set-up, in two groups (a host step between them reads the status word and
+// the positions): everything that reads the caller's arrays, then the
+// consensus lists, the normaliser and the images.  Where the split agent is
+// allowed, the amplitudes and states wait for the layout: launch_setup_states
+// between the two.
+hipError_t launch_setup_inputs(const Recon& h, const SetupInputs& in, int* fitem, hipStream_t st);
+hipError_t launch_setup_states(const Recon& h, const SetupInputs& in, hipStream_t st);
+hipError_t launch_setup_tables(const Recon& h, Recon* rec, int2* ritems, const SetupChunk* chunks, int nch,
+                               int tiles_c, int nseg, int rn, hipStream_t st);
 // Np <= 128, one reconstruction: fused agent over its J positions, then the
 // fused gather + image update over its ntiles tiles.
 hipError_t launch_small_iteration(int np, const Recon& h, int ntiles, hipStream_t st);
@@ -206,9 +237,4 @@ hipError_t launch_fft2(int np, int count, const float2* in, float2* out, int inv
 // consensus over the base tiles, image update), the descriptor h passed by
 // value; check_done: skip if the stop flag is set (batch members).
 hipError_t launch_split_iteration(const Recon& h, int check_done, hipStream_t st);
-// Split layout: the consensus sum of the current states into part, then
-// mode 0: sold = S (after init), mode 1: xhat = Lambda^{-1} S and sold = S
-// (after set_state).
-hipError_t launch_split_consensus(const Recon& h, const Recon* rec, int mode, hipStream_t st);
-
 }  // namespace pmace

@@ -684,7 +684,7 @@ __device__ __forceinline__ void finish_image(const Recon& g, size_t px, float2 S
   }
   g.xbar[px] = xb;
   g.xhat[px] = make_float2(fmaf(g.rho, xb.x - v.xh.x, v.xh.x), fmaf(g.rho, xb.y - v.xh.y, v.xh.y));
-  if (!(isfinite(xb.x) && isfinite(xb.y))) atomicOr(g.status, 1u);
+  if (!(isfinite(xb.x) && isfinite(xb.y))) atomicOr(g.status, kStatusNonFinite);
 }
 template <int METHOD>
 __device__ __forceinline__ void finish_image(const Recon& g, size_t px, float2 S) {
@@ -951,15 +951,6 @@ __global__ void image_from_num(const Recon* __restrict__ rec) {
   const float2 n = g.num[i];
   g.xhat[i] = make_float2(n.x * li, n.y * li);
   if (g.method == kPMACE) g.sold[i] = n;
-  g.num[i] = make_float2(0.f, 0.f);
-}
-
-// PMACE after init: S of the initial states; num <- 0.
-__global__ void sold_from_num(const Recon* __restrict__ rec) {
-  const Recon& g = *rec;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.n1 * g.n2) return;
-  g.sold[i] = g.num[i];
   g.num[i] = make_float2(0.f, 0.f);
 }
 
@@ -1243,95 +1234,8 @@ __global__ void tick_k(const Recon* __restrict__ recs, const int* __restrict__ i
 }
 
 // -------------------------------------------------------------------------
-// init / state kernels
+// state kernels
 // -------------------------------------------------------------------------
-__global__ void init_amplitudes_k(const Recon* __restrict__ rec, const float* z, float scale,
-                                  int centered) {
-  const Recon& g = *rec;
-  const long long per = (long long)g.np * g.np;
-  const long long total = per * g.J;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  long long src = i;
-  if (centered || g.split) {
-    const long long j = i / per;
-    const int rem = (int)(i - j * per);
-    int k = rem / g.np, l = rem - k * g.np;
-    if (g.split) {  // element m of coset block ab holds the frequency (2 m1 + a, 2 m2 + b)
-      const int M = g.np / 2, ab = rem / (M * M), m = rem - ab * M * M;
-      k = 2 * (m / M) + (ab >> 1);
-      l = 2 * (m % M) + (ab & 1);
-    }
-    const int h = centered ? g.np / 2 : 0;
-    src = j * per + (long long)((k + h) % g.np) * g.np + (l + h) % g.np;
-  }
-  const float zz = z[src];
-  if (!(zz >= 0.f) || isinf(zz)) atomicOr(g.status, 2u);
-  g.ys[i] = scale * sqrtf(fmaxf(zz, 0.f));
-}
-
-__global__ void init_patches_k(const Recon* __restrict__ rec, const float2* x0) {
-  const Recon& g = *rec;
-  const long long per = (long long)g.np * g.np;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= per * g.J) return;
-  const int j = (int)(i / per);
-  const int rem = (int)(i - (long long)j * per);
-  const int r = rem / g.np, c = rem - r * g.np;
-  const int2 pj = g.pos[j];
-  const float2 x = x0 ? x0[(size_t)(pj.x + r) * g.n2 + pj.y + c] : make_float2(1.f, 0.f);
-  // Alg. 1: v_j = P_j x0 (= t, xbar = 0), stored as d t (t where d == 0).
-  // Alg. 2: s_j = D P_j x0, held as t = s - 2 beta d P_j xbar with xbar = x0
-  // (the overlap image of consistent frames), i.e. (1 - 2 beta) d x0.
-  const float2 dd = g.d[rem];
-  if (g.method == kSharpPlus) g.t[i] = cscale(cmul(dd, x), 1.f - g.two_rho);
-  else g.t[i] = (dd.x != 0.f || dd.y != 0.f) ? cmul(dd, x) : x;
-}
-
-// Lambda = sum_j P_j^t omega (eq. (11)) in FP64 over one chunk's tiles, each
-// pixel adding its covering positions in ascending j (chunks run in order),
-// into `lam` (the accumulator image viewed as FP64, zeroed first).
-__global__ void __launch_bounds__(GT_THREADS) lambda_gather_k(const Recon* __restrict__ rec,
-                                                             int first_tile, double* __restrict__ lam) {
-  const Recon& g = *rec;
-  const int4 ti = g.tiles[first_tile + blockIdx.x];
-  const int np = g.np;
-  for (int px = threadIdx.x; px < GT_R * GT_C; px += blockDim.x) {
-    const int R = ti.z + px / GT_C, C = ti.w + px % GT_C;
-    if (R >= g.n1 || C >= g.n2) continue;
-    double acc = 0.0;
-    for (int i = 0; i < ti.y; ++i) {
-      const int2 pj = g.pos[g.tile_list[ti.x + i]];
-      const unsigned rr = (unsigned)(R - pj.x), cc = (unsigned)(C - pj.y);
-      if (rr < (unsigned)np && cc < (unsigned)np) acc += g.omega64[rr * np + cc];
-    }
-    lam[(size_t)R * g.n2 + C] += acc;
-  }
-}
-
-// Lambda^{-1}, 0 where Lambda = 0 (no patch, or only zero weights, covers the pixel).
-__global__ void laminv_k(const Recon* __restrict__ rec, const double* __restrict__ lam) {
-  const Recon& g = *rec;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.n1 * g.n2) return;
-  g.laminv[i] = lam[i] != 0.0 ? (float)(1.0 / lam[i]) : 0.f;
-}
-
-__global__ void zero_f64_k(double* __restrict__ a, long long n) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = 0.0;
-}
-
-__global__ void init_images_k(const Recon* __restrict__ rec, const float2* x0) {
-  const Recon& g = *rec;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.n1 * g.n2) return;
-  const float2 x = x0 ? x0[i] : make_float2(1.f, 0.f);
-  g.xhat[i] = g.laminv[i] > 0.f ? x : make_float2(0.f, 0.f);
-  g.xbar[i] = g.method == kSharpPlus ? g.xhat[i] : make_float2(0.f, 0.f);
-  g.num[i] = make_float2(0.f, 0.f);
-}
-
 // src: the probe-weighted states (t itself, or their row-spectrum form
 // already transformed back into v, which is then rewritten in place).
 __global__ void get_state_k(const Recon* __restrict__ rec, const float2* src, float2* v) {
@@ -1633,20 +1537,18 @@ __global__ void image_update_split(const Recon g, int check_done) {
   finish_image<kPMACE>(g, i, split_sum(g, i / g.n2, i % g.n2));
 }
 
-// After init (mode 0): S of the initial states; after set_state (mode 1):
-// also xhat = Lambda^{-1} S (xbar was cleared).
-__global__ void image_from_split(const Recon* __restrict__ rec, int mode) {
+// After set_state (xbar was cleared): S of the states and xhat = Lambda^{-1} S.
+__global__ void image_from_split(const Recon* __restrict__ rec) {
   const Recon& g = *rec;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.n1 * g.n2) return;
   const float2 S = split_sum(g, i / g.n2, i % g.n2);
   g.sold[i] = S;
-  if (mode == 1) g.xhat[i] = cscale(S, g.laminv[i]);
+  g.xhat[i] = cscale(S, g.laminv[i]);
 }
 
 // The split step of a frame f = d * (patch of img) for block ab at m:
 //   W_Np^{a m1 + b m2} sum_q (-1)^{a q1 + b q2} d[m + M q] img[p + m + M q].
-// img == nullptr stands for the object 1 + 0i (the default start).
 __device__ __forceinline__ float2 split_frame(const Recon& g, int2 pj, int ab, int m1, int m2,
                                               const float2* img) {
   const int M = g.np / 2, a = ab >> 1, b = ab & 1;
@@ -1655,23 +1557,10 @@ __device__ __forceinline__ float2 split_frame(const Recon& g, int2 pj, int ab, i
   for (int q = 0; q < 4; ++q) {
     const int q1 = q >> 1, q2 = q & 1;
     const int r = m1 + M * q1, c = m2 + M * q2;
-    const float2 x = img ? img[(size_t)(pj.x + r) * g.n2 + pj.y + c] : make_float2(1.f, 0.f);
-    const float2 f = cmul(g.d[r * g.np + c], x);
+    const float2 f = cmul(g.d[r * g.np + c], img[(size_t)(pj.x + r) * g.n2 + pj.y + c]);
     h = ((a * q1 + b * q2) & 1) ? csub(h, f) : cadd(h, f);
   }
   return cmul(h, g.twn[a * m1 + b * m2]);
-}
-
-// Split-layout states from an object (Alg. 1's initialisation, v_j = P_j x0, stored
-// as d v in blocks): element i of block ab of position j.
-__global__ void init_split_k(const Recon* __restrict__ rec, const float2* x0) {
-  const Recon& g = *rec;
-  const int M = g.np / 2, MM = M * M;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)g.J * 4 * MM) return;
-  const int j = (int)(i / (4 * MM)), rem = (int)(i - (long long)j * 4 * MM);
-  const int ab = rem / MM, m = rem - ab * MM;
-  g.t[i] = split_frame(g, g.pos[j], ab, m / M, m % M, x0);
 }
 
 // set_state in the split layout: blocks of d v from the given states v.
@@ -2032,15 +1921,15 @@ hipError_t launch_split_iteration(const Recon& h, int check_done, hipStream_t st
   return hipGetLastError();
 }
 
-hipError_t launch_split_consensus(const Recon& h, const Recon* rec, int mode, hipStream_t st) {
+static hipError_t split_consensus(const Recon& h, const Recon* rec, hipStream_t st) {
   switch (h.np) {
     case 128: hipLaunchKernelGGL(consensus_split<64>, dim3(h.nqt), dim3(QT_THREADS), 0, st, h, 0); break;
     case 192: hipLaunchKernelGGL(consensus_split<96>, dim3(h.nqt), dim3(QT_THREADS), 0, st, h, 0); break;
     case 256: hipLaunchKernelGGL(consensus_split<128>, dim3(h.nqt), dim3(QT_THREADS), 0, st, h, 0); break;
     default: return hipErrorInvalidValue;
   }
-  hipLaunchKernelGGL(image_from_split, dim3(blocks_for((long long)h.n1 * h.n2, 256)), dim3(256), 0, st, rec,
-                     mode);
+  hipLaunchKernelGGL(image_from_split, dim3(blocks_for((long long)h.n1 * h.n2, 256)), dim3(256), 0, st,
+                     rec);
   return hipGetLastError();
 }
 
@@ -2084,38 +1973,6 @@ static hipError_t states_to_rowspec(const Recon& h, hipStream_t st) {
   return launch_row_transform(h.np, h.J, h.t, h.t, false, 1.f / (float)h.np, st);
 }
 
-hipError_t launch_init(const Recon& h, const Recon* rec, const float* z, float scale,
-                       int centered, const float2* x0, const int2* chunk_tiles, hipStream_t st) {
-  const long long total = (long long)h.J * h.np * h.np;
-  const long long npx = (long long)h.n1 * h.n2;
-  hipLaunchKernelGGL(init_amplitudes_k, dim3(blocks_for(total, 256)), dim3(256), 0, st, rec, z, scale,
-                     centered);
-  if (h.split)
-    hipLaunchKernelGGL(init_split_k, dim3(blocks_for(total, 256)), dim3(256), 0, st, rec, x0);
-  else
-    hipLaunchKernelGGL(init_patches_k, dim3(blocks_for(total, 256)), dim3(256), 0, st, rec, x0);
-  // Lambda in FP64, accumulated in the (still unused) accumulator image
-  double* lam = reinterpret_cast<double*>(h.num);
-  hipLaunchKernelGGL(zero_f64_k, dim3(blocks_for(npx, 256)), dim3(256), 0, st, lam, npx);
-  for (int j0 = 0, g = 0; j0 < h.J; j0 += h.chunk, ++g)
-    if (chunk_tiles[g].y > 0)
-      hipLaunchKernelGGL(lambda_gather_k, dim3(chunk_tiles[g].y), dim3(GT_THREADS), 0, st, rec,
-                         chunk_tiles[g].x, lam);
-  hipLaunchKernelGGL(laminv_k, dim3(blocks_for(npx, 256)), dim3(256), 0, st, rec, lam);
-  hipLaunchKernelGGL(init_images_k, dim3(blocks_for(npx, 256)), dim3(256), 0, st, rec, x0);
-  if (h.split) return launch_split_consensus(h, rec, 0, st);
-  if (h.method == kPMACE) {
-    for (int j0 = 0, g = 0; j0 < h.J; j0 += h.chunk, ++g) {
-      const hipError_t e = gather_into_num(h, chunk_tiles[g], j0, st);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(sold_from_num, dim3(blocks_for(npx, 256)), dim3(256), 0, st, rec);
-  }
-  // S above was summed from the stored states themselves
-  if (h.rowspec) return states_to_rowspec(h, st);
-  return hipGetLastError();
-}
-
 hipError_t launch_get_state(const Recon& h, const Recon* rec, float2* v, hipStream_t st) {
   const long long total = (long long)h.J * h.np * h.np;
   if (h.split) {
@@ -2140,7 +1997,7 @@ hipError_t launch_set_state(const Recon& h, const Recon* rec, const float2* v,
   hipLaunchKernelGGL(zero_images_k, dim3(blocks_for(npx, 256)), dim3(256), 0, st, rec);
   if (h.split) {
     hipLaunchKernelGGL(set_state_split_k, dim3(blocks_for(per * h.J, 256)), dim3(256), 0, st, rec, v);
-    return launch_split_consensus(h, rec, 1, st);
+    return split_consensus(h, rec, st);
   }
   for (int j0 = 0, g = 0; j0 < h.J; j0 += h.chunk, ++g) {
     const int cnt = (h.J - j0 < h.chunk) ? (h.J - j0) : h.chunk;

@@ -1,0 +1,71 @@
+"""The set-up's device-built lists: one pass from a smooth start against the
+oracle, where a list can go wrong: more positions than a workgroup's batch of
+256, tile rows wider than a panel of 1024 tiles, several chunks with a ragged
+last one, equal columns and repeated positions (ties), rows that no patch
+covers, an object row in two segments.  The bar is that of the parity tests."""
+import numpy as np
+import pytest
+
+from oracle import pmace_oracle as O
+from paper_2111_14240_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2111_14240_amd import pmace
+    pmace.load_library()
+    return pmace
+
+
+def _smooth(n1, n2, rng):
+    x = synth.make_object(max(n1, 64), max(n2, 64), rng)
+    return x[:n1, :n2].astype(np.complex64)
+
+
+CASES = [
+    # np, n1, n2, J, chunk, where the positions go
+    (32, 70, 33000, 300, 0, "spread"),      # 1032 tile columns, two batches
+    (48, 150, 97, 1, 0, "spread"),
+    (64, 200, 131, 257, 0, "two columns"),
+    (128, 400, 300, 40, 0, "corners"),      # rows in the middle uncovered
+    (160, 300, 1300, 70, 33, "spread"),     # two segments, three chunks
+    (192, 260, 300, 65, 0, "same"),
+    (256, 300, 400, 17, 5, "two columns"),
+]
+
+
+@pytest.mark.parametrize("np_,n1,n2,J,chunk,where", CASES)
+def test_first_pass_matches_oracle(P, np_, n1, n2, J, chunk, where):
+    rng = np.random.default_rng(np_ + J)
+    pos = np.stack([rng.integers(0, n1 - np_ + 1, J), rng.integers(0, n2 - np_ + 1, J)], 1)
+    if where == "two columns":
+        pos[:, 1] = np.where(np.arange(J) % 3, 1, n2 - np_)
+    elif where == "same":
+        pos[:] = pos[0]
+    elif where == "corners":
+        pos = np.where(np.arange(J)[:, None] % 2, pos % 5, [n1 - np_, n2 - np_] - pos % 5)
+    pos = pos.astype(np.int32)
+    x, x0 = _smooth(n1, n2, rng), _smooth(n1, n2, rng)
+    d = (synth.make_probe(np_) * 30).astype(np.complex64)
+    z, _ = synth.simulate_intensities(x.astype(complex), d.astype(complex), pos, None, rng)
+    print("[gpu-setup]", np_, n1, n2, J, chunk, where, flush=True)
+    R = P.Reconstruction(n1, n2, d, pos, z, 0.5, 1.25, 0.5, x0=x0, chunk=chunk)
+    shape = (n1, n2)
+    covered = np.zeros(shape, bool)
+    for r, c in pos:
+        covered[r:r + np_, c:c + np_] = True
+    assert np.array_equal(R.reconstruct().cpu().numpy(), np.where(covered, x0, 0))
+    R.iterate(1)
+    st = O.pmace_init(x0.astype(complex), pos, np_)
+    st = O.pmace_iterate(st, d.astype(complex), O.amplitudes(z), pos, shape, 0.5, 1.25, 0.5, 1)
+    for got, ref in ((R.get_state(), st.v), (R.reconstruct(), O.reconstruct(st, d.astype(complex), pos, shape, 1.25))):
+        got = got.cpu().numpy()
+        e = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        print(f"[gpu-setup]   rel {e:.2e} max {np.abs(got - ref).max() / np.abs(ref).max():.2e}", flush=True)
+        assert e <= 1e-4 and np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+    R.close()
