@@ -57,9 +57,10 @@ struct pmace_ctx {
   int ngitems;                    // gather tiles of all chunks
   std::vector<int2> chunk_tiles;  // host: per chunk (first gather tile, count)
   std::vector<int2> chunk_rows;   // host, row-spectrum states: per chunk (first row item, count)
-  Graph graph;                    // one iteration
-  Graph graph_k;                  // kGraphIters iterations back to back
+  Graph graph;                    // several iterations back to back (pmace_iterate)
   bool graph_tried;
+  long long asked;                // iterations pmace_iterate has been asked for
+  bool batched;                   // has been a batch member: its stop flag may be set
   pmace_status sticky;            // first asynchronous failure seen
   unsigned long long resets;      // times the host cleared the stop flag
   // batches holding a copy of this context's descriptor (and its index there):
@@ -407,6 +408,8 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   c->stream = st;
   c->sticky = PMACE_OK;
   c->graph_tried = false;
+  c->asked = 0;
+  c->batched = false;
   c->resets = 0;
   if (hipGetDevice(&c->device) != hipSuccess) { delete c; return PMACE_EDEVICE; }
   auto fail = [&](pmace_status e) {
@@ -588,35 +591,37 @@ pmace_status pmace_iterate(pmace_ctx* c, int32_t n_iter) {
   if (!c) return PMACE_ESTATE;
   if (n_iter < 0) return PMACE_EINVAL;
   if (n_iter == 0) return PMACE_OK;
-  // a stop flag left by a batch would make the kernels skip this reconstruction
-  if (hipMemsetAsync(c->h.done, 0, 4, c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
+  // a stop flag left by a batch would make its kernels skip this reconstruction
+  if (c->batched && hipMemsetAsync(c->h.done, 0, 4, c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
   ++c->resets;
-  // One graph replays one iteration; a second replays kGraphIters of them in
-  // a row, so long runs pay one launch per kGraphIters iterations.
+  // Iterations are launched as they are: the host queues one in 8 to 12 us,
+  // the shortest (36 positions of 32^2) runs in 10.  A graph of kGraphIters of
+  // them closes the gaps between the smallest kernels (np 32: 10.9 -> 9.5 us
+  // per iteration; np 96: 24.7 -> 24.5; np 256: nothing, and a graph of one
+  // iteration is slower than its launches at every size), but costs 250 us to
+  // capture, so it is made for Np <= 64 once kCaptureFrom iterations have been
+  // asked for.
   constexpr int kGraphIters = 32;
-  if (!c->graph_tried && graphs_enabled()) {
+  constexpr long long kCaptureFrom = 256;
+  c->asked += n_iter;
+  if (!c->graph_tried && n_iter >= kGraphIters && c->asked >= kCaptureFrom && c->prm.np <= 64 &&
+      graphs_enabled()) {
     c->graph_tried = true;
-    (void)capture(c->graph, [&](hipStream_t cs) { return enqueue_iteration(c, cs); });
-    if (c->graph.x)
-      (void)capture(c->graph_k, [&](hipStream_t cs) {
-        for (int i = 0; i < kGraphIters; ++i) {
-          const pmace_status s = enqueue_iteration(c, cs);
-          if (s != PMACE_OK) return s;
-        }
-        return PMACE_OK;
-      });
+    (void)capture(c->graph, [&](hipStream_t cs) {
+      for (int i = 0; i < kGraphIters; ++i) {
+        const pmace_status s = enqueue_iteration(c, cs);
+        if (s != PMACE_OK) return s;
+      }
+      return PMACE_OK;
+    });
   }
   int k = 0;
-  if (c->graph_k.x)
+  if (c->graph.x)
     for (; k + kGraphIters <= n_iter; k += kGraphIters)
-      if (hipGraphLaunch(c->graph_k.x, c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
-  for (; k < n_iter; ++k) {
-    if (c->graph.x) {
       if (hipGraphLaunch(c->graph.x, c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
-    } else {
-      pmace_status s = enqueue_iteration(c, c->stream);
-      if (s != PMACE_OK) return record(c, s);
-    }
+  for (; k < n_iter; ++k) {
+    const pmace_status s = enqueue_iteration(c, c->stream);
+    if (s != PMACE_OK) return record(c, s);
   }
   return PMACE_OK;
 }
@@ -720,7 +725,6 @@ void pmace_destroy(pmace_ctx* c) {
   for (const auto& hb : c->holders) batch_forget(hb.first, hb.second);
   (void)hipStreamSynchronize(c->stream);
   c->graph.release();
-  c->graph_k.release();
   delete c;
 }
 
@@ -959,7 +963,10 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
     batch_release(b);
     return PMACE_EDEVICE;
   }
-  for (int i = 0; i < n; ++i) ctxs[i]->holders.emplace_back(b, i);
+  for (int i = 0; i < n; ++i) {
+    ctxs[i]->holders.emplace_back(b, i);
+    ctxs[i]->batched = true;
+  }
   *out = b;
   return PMACE_OK;
 }

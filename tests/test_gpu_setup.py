@@ -69,3 +69,18 @@ def test_first_pass_matches_oracle(P, np_, n1, n2, J, chunk, where):
         print(f"[gpu-setup]   rel {e:.2e} max {np.abs(got - ref).max() / np.abs(ref).max():.2e}", flush=True)
         assert e <= 1e-4 and np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
     R.close()
+
+
+def test_captured_iterations_equal_launched_ones(P):
+    """Np <= 64 replays a captured graph once 256 iterations have been asked
+    for; the same number of iterations, launched in small calls, gives the
+    same bits."""
+    prob = synth.make_problem(96, 32, 3, 20, 1e5, 5)
+    got = []
+    for calls in ([130, 131, 40], [1] * 301):
+        R = P.Reconstruction(prob.n1, prob.n2, prob.probe, prob.pos, prob.z, 0.5)
+        for n in calls:
+            R.iterate(n)
+        got.append((R.get_state().cpu().numpy(), R.reconstruct().cpu().numpy()))
+        R.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
