@@ -1236,26 +1236,72 @@ __global__ void tick_k(const Recon* __restrict__ recs, const int* __restrict__ i
 // -------------------------------------------------------------------------
 // state kernels
 // -------------------------------------------------------------------------
-// src: the probe-weighted states (t itself, or their row-spectrum form
-// already transformed back into v, which is then rewritten in place).
-__global__ void get_state_k(const Recon* __restrict__ rec, const float2* src, float2* v) {
-  const Recon& g = *rec;
-  const long long per = (long long)g.np * g.np;
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= per * g.J) return;
-  const int j = (int)(i / per);
-  const int rem = (int)(i - (long long)j * per);
-  const int r = rem / g.np, c = rem - r * g.np;
+// One element of the state v read out of the stored s: PMACE v = t + 2 rho P_j
+// xbar with t = d^{-1} s (dinv = d^{-1}/Np^2; s where d == 0); SHARP+
+// s = t + 2 beta d P_j xbar.
+__device__ __forceinline__ float2 state_out(const Recon& g, float2 s, float2 xb, int k) {
+  if (g.method == kSharpPlus) return mann_v(s, cmul(g.d[k], xb), g.two_rho);
+  const float2 di = g.dinv[k];
+  const float2 t = (di.x != 0.f || di.y != 0.f) ? cscale(cmul(di, s), g.np2f) : s;
+  return mann_v(t, xb, g.two_rho);
+}
+
+// The states read out (v, or s for SHARP+): workgroup b takes pixels
+// [256 GS (b mod per), ...) of patch b / per, GS to a thread, all loads ahead of
+// the stores.  Bound by memory (16 B per patch pixel).
+constexpr int GS = 4;
+__global__ void __launch_bounds__(256) get_state_k(const Recon g, float2* __restrict__ v, int per) {
+  const int j = blockIdx.x / per, k0 = (int)(blockIdx.x % per) * 256 * GS + threadIdx.x;
+  const int np2 = g.np * g.np;
   const int2 pj = g.pos[j];
-  const float2 xb = g.xbar[(size_t)(pj.x + r) * g.n2 + pj.y + c];
-  // PMACE: v = t + 2 rho P_j xbar with t = d^{-1} s (dinv = d^{-1}/Np^2; s where
-  // d == 0);  SHARP+: s = t + 2 beta d P_j xbar
-  if (g.method == kSharpPlus) {
-    v[i] = mann_v(src[i], cmul(g.d[rem], xb), g.two_rho);
-  } else {
-    const float2 di = g.dinv[rem], s = src[i];
-    const float2 t = (di.x != 0.f || di.y != 0.f) ? cscale(cmul(di, s), g.np2f) : s;
-    v[i] = mann_v(t, xb, g.two_rho);
+  const float2* x = g.xbar + (size_t)pj.x * g.n2 + pj.y;
+  const float2* t = g.t + (size_t)j * np2;
+  float2 s[GS], xb[GS];
+#pragma unroll
+  for (int i = 0; i < GS; ++i) {
+    const int k = k0 + 256 * i, kc = k < np2 ? k : 0, r = kc / g.np;
+    s[i] = t[kc];
+    xb[i] = x[(size_t)r * g.n2 + (kc - r * g.np)];
+  }
+  float2* o = v + (size_t)j * np2;
+#pragma unroll
+  for (int i = 0; i < GS; ++i) {
+    const int k = k0 + 256 * i;
+    if (k < np2) o[k] = state_out(g, s[i], xb[i], k);
+  }
+}
+
+// The same from row-spectrum states, s = F_r^*(H) formed here, a row block of
+// one patch per workgroup (transforming into v and finishing it in a second
+// pass moved 32 B per patch pixel: 790 us for 1600 positions of 256^2).
+template <int NP>
+__global__ void __launch_bounds__(row_threads<NP>()) get_state_rows(const Recon g, float2* __restrict__ v) {
+  constexpr int A = Geo<NP>::A, B = Geo<NP>::B, M = B / A, S = row_cap<NP>();
+  constexpr int RBn = rb_of<NP>();
+  __shared__ float2 tile[RBn * S];
+  __shared__ float2 tw[NP];
+  const int tid = threadIdx.x;
+  const int j = blockIdx.x / (NP / RBn), rb = blockIdx.x % (NP / RBn);
+  const int rl = tid / A, p = tid % A, r = rb * RBn + rl;
+  const size_t base = ((size_t)j * NP + r) * NP;
+  TwiddleFetch<NP, RBn * A> twf;
+  twf.fetch(g.twn, tid);
+  const int2 pj = g.pos[j];
+  const float2* xrow = g.xbar + (size_t)(pj.x + r) * g.n2 + pj.y;
+  float2 x[B], xb[B];
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int ka = 0; ka < A; ++ka) x[m * A + ka] = g.t[base + p + A * m + B * ka];
+#pragma unroll
+  for (int nb = 0; nb < B; ++nb) xb[nb] = xrow[p + A * nb];
+  twf.store(tw, tid);
+  __syncthreads();
+  row_inv<NP>(x, tile + rl * S, p, tw);
+#pragma unroll
+  for (int nb = 0; nb < B; ++nb) {
+    const int c = p + A * nb;
+    v[base + c] = state_out(g, x[nb], xb[nb], r * NP + c);
   }
 }
 
@@ -1945,47 +1991,42 @@ static hipError_t launch_fit_split(const Recon& h, int check_done, hipStream_t s
   return hipGetLastError();
 }
 
-// Row DFTs of `count` Np x Np patches (in may equal out: each row is read
-// whole before it is written): out = scale F_r(in), or scale F_r^*(in).
+// Row-spectrum states from the ones in t (PMACE: probe-weighted): F_r(t)/Np
+// (each row is read whole before it is written).
 template <int NP>
-static void row_transform(int count, const float2* in, float2* out, bool inverse, float scale,
-                          hipStream_t st) {
-  const dim3 rgrid(count * (NP / rb_of<NP>()));
-  if (inverse)
-    hipLaunchKernelGGL((fft_rows<NP, true>), rgrid, dim3(row_threads<NP>()), 0, st, in, out, scale);
-  else
-    hipLaunchKernelGGL((fft_rows<NP, false>), rgrid, dim3(row_threads<NP>()), 0, st, in, out, scale);
+static void states_to_rowspec(const Recon& h, hipStream_t st) {
+  hipLaunchKernelGGL((fft_rows<NP, false>), dim3(h.J * (NP / rb_of<NP>())), dim3(row_threads<NP>()), 0, st, h.t,
+                     h.t, 1.f / (float)NP);
 }
-
-static hipError_t launch_row_transform(int np, int count, const float2* in, float2* out, bool inverse,
-                                       float scale, hipStream_t st) {
-  switch (np) {
-    case 160: row_transform<160>(count, in, out, inverse, scale, st); break;
-    case 192: row_transform<192>(count, in, out, inverse, scale, st); break;
-    case 256: row_transform<256>(count, in, out, inverse, scale, st); break;
+static hipError_t states_to_rowspec(const Recon& h, hipStream_t st) {
+  switch (h.np) {
+    case 160: states_to_rowspec<160>(h, st); break;
+    case 192: states_to_rowspec<192>(h, st); break;
+    case 256: states_to_rowspec<256>(h, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Row-spectrum states from the ones in t (PMACE: probe-weighted): F_r(t)/Np.
-static hipError_t states_to_rowspec(const Recon& h, hipStream_t st) {
-  return launch_row_transform(h.np, h.J, h.t, h.t, false, 1.f / (float)h.np, st);
+template <int NP>
+static void get_rowspec(const Recon& h, float2* v, hipStream_t st) {
+  hipLaunchKernelGGL(get_state_rows<NP>, dim3(h.J * (NP / rb_of<NP>())), dim3(row_threads<NP>()), 0, st, h, v);
 }
 
 hipError_t launch_get_state(const Recon& h, const Recon* rec, float2* v, hipStream_t st) {
-  const long long total = (long long)h.J * h.np * h.np;
+  const int np2 = h.np * h.np;
   if (h.split) {
-    hipLaunchKernelGGL(get_state_split_k, dim3(blocks_for(total, 256)), dim3(256), 0, st, rec, v);
+    hipLaunchKernelGGL(get_state_split_k, dim3(blocks_for((long long)h.J * np2, 256)), dim3(256), 0, st, rec, v);
   } else if (h.rowspec) {
-    // s = F_r^*(H) into v, then v from s in place
-    const hipError_t e = launch_row_transform(h.np, h.J, h.t, v, true, 1.f, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(get_state_k, dim3(blocks_for(total, 256)), dim3(256), 0, st, rec,
-                       static_cast<const float2*>(v), v);
+    switch (h.np) {
+      case 160: get_rowspec<160>(h, v, st); break;
+      case 192: get_rowspec<192>(h, v, st); break;
+      case 256: get_rowspec<256>(h, v, st); break;
+      default: return hipErrorInvalidValue;
+    }
   } else {
-    hipLaunchKernelGGL(get_state_k, dim3(blocks_for(total, 256)), dim3(256), 0, st, rec,
-                       static_cast<const float2*>(h.t), v);
+    const int per = (np2 + 256 * GS - 1) / (256 * GS);
+    hipLaunchKernelGGL(get_state_k, dim3((unsigned)h.J * per), dim3(256), 0, st, h, v, per);
   }
   return hipGetLastError();
 }
