@@ -81,6 +81,7 @@ struct pmace_batch {
   int2* ritems;                // device: (member, block) NRMSE items
   int nritems;
   int* fitems;                 // device: member indices
+  pmace::PollItem* polled;     // device: what a poll reads of each member
   pmace_stop_rule rule;
   hipStream_t lanes[4];
   hipEvent_t fork, join[4];
@@ -753,7 +754,7 @@ int class_of(int np) {
 }
 
 struct BatchLayout {
-  size_t recs, items[kClasses], gitems[kClasses], ritems, fitems, total;
+  size_t recs, items[kClasses], gitems[kClasses], ritems, fitems, polled, total;
   int nitems[kClasses], ngitems[kClasses], nritems;
 };
 
@@ -775,6 +776,7 @@ BatchLayout batch_layout(pmace_ctx* const* ctxs, int n) {
   }
   L.ritems = o;  o = align_up(o + (size_t)L.nritems * 8);
   L.fitems = o;  o = align_up(o + (size_t)n * 4);
+  L.polled = o;  o = align_up(o + (size_t)n * sizeof(pmace::PollItem));
   L.total = o;
   return L;
 }
@@ -954,6 +956,7 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   b->ritems = reinterpret_cast<int2*>(base + L.ritems);
   b->nritems = (int)ritems.size();
   b->fitems = reinterpret_cast<int*>(base + L.fitems);
+  b->polled = reinterpret_cast<pmace::PollItem*>(base + L.polled);
   ok = ok && hipMemcpyAsync(b->ritems, ritems.data(), ritems.size() * 8, hipMemcpyHostToDevice, st) ==
                  hipSuccess;
   ok = ok && hipMemcpyAsync(b->fitems, fitems.data(), (size_t)n * 4, hipMemcpyHostToDevice, st) ==
@@ -1014,27 +1017,25 @@ pmace_status pmace_batch_step(pmace_batch* b, int32_t n_iter) {
 pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, int32_t* iters,
                                   double* data_fit) {
   if (!b) return PMACE_ESTATE;
-  std::vector<int> dn(b->n);
-  std::vector<double> tr(8 * (size_t)b->n);
-  for (int i = 0; i < b->n; ++i) {
-    if (hipMemcpyAsync(&dn[i], b->ctxs[i]->h.done, 4, hipMemcpyDeviceToHost, b->stream) != hipSuccess ||
-        hipMemcpyAsync(&tr[8 * i], b->ctxs[i]->h.track, 64, hipMemcpyDeviceToHost, b->stream) != hipSuccess)
-      return PMACE_EDEVICE;
-  }
-  if (hipStreamSynchronize(b->stream) != hipSuccess) return PMACE_EDEVICE;
+  std::vector<pmace::PollItem> got(b->n);
+  if (pmace::launch_poll(b->recs, b->n, b->polled, b->stream) != hipSuccess ||
+      hipMemcpyAsync(got.data(), b->polled, got.size() * sizeof(pmace::PollItem), hipMemcpyDeviceToHost,
+                     b->stream) != hipSuccess ||
+      hipStreamSynchronize(b->stream) != hipSuccess)
+    return PMACE_EDEVICE;
   bool changed = false;
   for (int i = 0; i < b->n; ++i)
-    if (dn[i] && own_chain(b->ctxs[i]) && !b->pruned[i]) {
+    if (got[i].done && own_chain(b->ctxs[i]) && !b->pruned[i]) {
       b->pruned[i] = 1;
       b->pruned_at[i] = b->ctxs[i]->resets;
       changed = true;
     }
   if (changed && drop_graphs(b) != PMACE_OK) return PMACE_EDEVICE;
   for (int i = 0; i < b->n; ++i) {
-    if (done) done[i] = dn[i];
-    if (nrmse) nrmse[i] = tr[8 * i + 1];
-    if (iters) iters[i] = (int32_t)tr[8 * i + 3];
-    if (data_fit) data_fit[i] = tr[8 * i + 4];
+    if (done) done[i] = got[i].done;
+    if (nrmse) nrmse[i] = got[i].nrmse;
+    if (iters) iters[i] = (int32_t)got[i].iters;
+    if (data_fit) data_fit[i] = got[i].fit;
   }
   return PMACE_OK;
 }

@@ -232,6 +232,12 @@ hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int u
 // rule is evaluated); cap = 1: stop running members that reached max_iter.
 hipError_t launch_tick(const Recon* recs, const int* fitems, int nf, int max_iter, int cap,
                        hipStream_t st);
+// A member's stop flag and figures, for all members of a batch into out[n].
+struct PollItem {
+  double nrmse, iters, fit;
+  int done, pad;
+};
+hipError_t launch_poll(const Recon* recs, int n, PollItem* out, hipStream_t st);
 hipError_t launch_fft2(int np, int count, const float2* in, float2* out, int inverse, hipStream_t st);
 // Split layout (h.split): one iteration (agent on every (position, coset),
 // consensus over the base tiles, image update), the descriptor h passed by
