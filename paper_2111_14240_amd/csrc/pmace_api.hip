@@ -284,7 +284,7 @@ Layout layout_of(const pmace_params& p) {
   const bool sp = split_allowed(p);
   L.stage = o;   o = align_up(o + std::max(stage_patches(p) * np2 * 8, sp ? 4 * npx * 8 : (size_t)0));
   L.tiles = o;   o = align_up(o + max_tiles(p) * 16);
-  L.list = o;    o = align_up(o + max_list(p) * 4);
+  L.list = o;    o = align_up(o + max_list(p) * 8);
   L.desc = o;    o = align_up(o + sizeof(Recon));
   L.ritems = o;  o = align_up(o + (size_t)num_red(p) * 8);
   L.red = o;     o = align_up(o + (size_t)num_red(p) * 32);
@@ -437,7 +437,7 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   h.xhat = reinterpret_cast<float2*>(base + L.xhat);
   h.stage = reinterpret_cast<float2*>(base + L.stage);
   h.tiles = reinterpret_cast<int4*>(base + L.tiles);
-  h.tile_list = reinterpret_cast<int*>(base + L.list);
+  h.tile_list = reinterpret_cast<int2*>(base + L.list);
   h.status = reinterpret_cast<unsigned*>(base + L.status);
   h.done = reinterpret_cast<int*>(base + L.status + 4);
   c->fitem = reinterpret_cast<int*>(base + L.status + 8);

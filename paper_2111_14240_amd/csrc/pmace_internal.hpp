@@ -108,7 +108,8 @@ struct Recon {
                         //   the weighted frames conj(d) P_a s the overlap projection sums
   float2* twn;          // Np       W_Np^m = exp(-2 pi i m/Np), FP64-rounded twiddles
   int4* tiles;          // per gather tile: (list start, count, first row, first col)
-  int* tile_list;       // positions overlapping each tile, ascending
+  int2* tile_list;      // positions overlapping each tile, ascending: (j, origin of P_j relative
+                        //   to the tile's, row << 16 | column & 0xffff)
   unsigned* status;     // kStatus* bits
   int* done;            // stop flag: nonzero = skip this reconstruction's work
   float2* xref;         // NRMSE reference object, null if none

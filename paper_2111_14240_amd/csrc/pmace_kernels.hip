@@ -47,6 +47,48 @@ constexpr int kPMACE = 0, kSharpPlus = 1, kRowSpec = 2, kSharpRowSpec = 3;
 template <int METHOD> constexpr bool row_spec() { return METHOD == kRowSpec || METHOD == kSharpRowSpec; }
 template <int METHOD> constexpr bool sharp() { return METHOD == kSharpPlus || METHOD == kSharpRowSpec; }
 
+// A descriptor read from device memory (batch members).  The pointers of a
+// descriptor passed by value are known to be global; read from memory they are
+// generic, and every access through them is a flat one, which also counts as
+// an LDS access and serialises with the kernel's own.  Passing them through
+// an address_space(1) value (which the compiler may not look through, or it
+// folds the two casts) makes them global again.  UNIFORM: the index is the
+// same in the whole wave, so they stay scalars.
+template <bool UNIFORM, class T> __device__ __forceinline__ void mark_global(T*& p) {
+  auto q = (__attribute__((address_space(1))) T*)p;
+  if constexpr (UNIFORM) asm("" : "+s"(q));
+  else asm("" : "+v"(q));
+  p = (T*)q;
+}
+template <bool UNIFORM = true>
+__device__ __forceinline__ Recon member(const Recon* __restrict__ recs, int i) {
+  Recon g = recs[i];
+  mark_global<UNIFORM>(g.t);
+  mark_global<UNIFORM>(g.ys);
+  mark_global<UNIFORM>(g.pos);
+  mark_global<UNIFORM>(g.d);
+  mark_global<UNIFORM>(g.pc);
+  mark_global<UNIFORM>(g.dinv);
+  mark_global<UNIFORM>(g.gw);
+  mark_global<UNIFORM>(g.laminv);
+  mark_global<UNIFORM>(g.num);
+  mark_global<UNIFORM>(g.sold);
+  mark_global<UNIFORM>(g.xbar);
+  mark_global<UNIFORM>(g.xhat);
+  mark_global<UNIFORM>(g.stage);
+  mark_global<UNIFORM>(g.twn);
+  mark_global<UNIFORM>(g.tiles);
+  mark_global<UNIFORM>(g.tile_list);
+  mark_global<UNIFORM>(g.status);
+  mark_global<UNIFORM>(g.done);
+  mark_global<UNIFORM>(g.xref);
+  mark_global<UNIFORM>(g.mask);
+  mark_global<UNIFORM>(g.red);
+  mark_global<UNIFORM>(g.track);
+  mark_global<UNIFORM>(g.fit);
+  return g;
+}
+
 // Fourier-domain prox of eq. (9): U = W * (a + ys / |W|), 0 where W == 0.
 __device__ __forceinline__ float2 fourier_prox(float2 W, float ysv, float a) {
   const float m2 = fmaf(W.x, W.x, W.y * W.y);
@@ -239,7 +281,7 @@ __global__ void __launch_bounds__(PPW * NP * Geo<NP>::A) agent_fused_batch(
   constexpr int NT = NP * Geo<NP>::A;
   if constexpr (PPW == 1) {
     const int2 it = items[blockIdx.x];
-    const Recon& g = recs[it.x];
+    const Recon g = member(recs, it.x);
     if (*g.done) return;
     agent_fused_body<NP, kPMACE>(g, it.y);
   } else {
@@ -249,7 +291,7 @@ __global__ void __launch_bounds__(PPW * NP * Geo<NP>::A) agent_fused_batch(
     if (!any) return;
     const int i = i0 + (int)threadIdx.x / NT;
     const int2 it = items[i < nitems ? i : nitems - 1];
-    const Recon& g = recs[it.x];
+    const Recon g = member<false>(recs, it.x);
     agent_fused_body<NP, kPMACE, PPW>(g, it.y, i < nitems && *g.done == 0);
   }
 }
@@ -691,18 +733,17 @@ __device__ __forceinline__ void finish_image(const Recon& g, size_t px, float2 S
   finish_image<METHOD>(g, px, S, load_image_in<METHOD>(g, px));
 }
 
-#define PM_STR(x) #x
-#define PM_UNROLL(n) _Pragma(PM_STR(unroll n))
-
 template <int NP, bool FUSE, int METHOD>
 __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int tile, const int jbase) {
-  constexpr int NPX = GT_R * GT_C, NT = GT_THREADS, LIST = 256;
-  __shared__ int3 sl[LIST];  // (patch slot, row, col) of the listed positions
+  constexpr int NPX = GT_R * GT_C, U = PMACE_GATHER_UNROLL;
   const int tid = threadIdx.x;
-  // GT_K threads share a pixel: part k sums list entries k, k + GT_K, ...
-  const int pxl = tid % NPX, part = tid / NPX;
+  // GT_K threads share a pixel: part k sums list entries k, k + GT_K, ...  A
+  // part is whole waves, so its entries are scalars (read by scalar loads, no
+  // LDS list and no barrier ahead of the sums).
+  static_assert(NPX % 64 == 0, "a part is whole waves");
+  const int pxl = tid % NPX, part = __builtin_amdgcn_readfirstlane(tid / NPX);
   const int4 ti = g.tiles[tile];
-  const int R = ti.z + pxl / GT_C, C = ti.w + pxl % GT_C;
+  const int lr = pxl / GT_C, lc = pxl % GT_C, R = ti.z + lr, C = ti.w + lc;
   // the pixel's thread (part 0) loads what it combines the sum with now, so
   // those loads overlap the list and state loads instead of following them
   const bool own = part == 0 && R < g.n1 && C < g.n2;
@@ -715,31 +756,33 @@ __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int 
   }
   const float2* src = METHOD == kPMACE ? g.t : g.stage;
   const int jb = METHOD == kPMACE ? 0 : jbase;
+  const int2* list = g.tile_list + ti.x;
   float ax = 0.f, ay = 0.f;
-  for (int b0 = 0; b0 < ti.y; b0 += LIST) {
-    const int nb = ti.y - b0 < LIST ? ti.y - b0 : LIST;
-    if (b0 > 0) __syncthreads();
-    for (int i = tid; i < nb; i += NT) {
-      const int j = g.tile_list[ti.x + b0 + i];
-      const int2 pj = g.pos[j];
-      sl[i] = make_int3(j - jb, pj.x, pj.y);
-    }
-    __syncthreads();
-    PM_UNROLL(PMACE_GATHER_UNROLL)
-    for (int i = part; i < nb; i += GT_K) {
-      const int3 e = sl[i];
-      const unsigned rr = (unsigned)(R - e.y), cc = (unsigned)(C - e.z);
-      const bool in = rr < (unsigned)NP && cc < (unsigned)NP;
+  // U entries at a time, all their loads ahead of the sums; the last group is
+  // filled up with its last entry at weight zero (left to a remainder loop, up
+  // to U - 1 entries were loaded one after the other)
+  for (int i0 = part; i0 < ti.y; i0 += U * GT_K) {
+    float2 u[U], w[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int i = i0 + k * GT_K;
+      const int2 e = list[i < ti.y ? i : ti.y - 1];  // (j, patch origin relative to the tile's)
+      const unsigned rr = (unsigned)(lr - (e.y >> 16)), cc = (unsigned)(lc - (int)(short)e.y);
+      const bool in = rr < (unsigned)NP && cc < (unsigned)NP && i < ti.y;
       // lanes outside the patch read its first pixel and discard it
       const unsigned o = in ? rr * NP + cc : 0u;
-      const float2 u = src[(size_t)e.x * NP * NP + o];
+      u[k] = src[(size_t)(e.x - jb) * NP * NP + o];
+      if constexpr (METHOD == kPMACE) w[k] = in ? g.gw[o] : make_float2(0.f, 0.f);
+      else if (!in) u[k] = make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
       if constexpr (METHOD == kPMACE) {
-        const float2 w = in ? g.gw[o] : make_float2(0.f, 0.f);
-        ax = fmaf(w.x, u.x, fmaf(-w.y, u.y, ax));
-        ay = fmaf(w.x, u.y, fmaf(w.y, u.x, ay));
+        ax = fmaf(w[k].x, u[k].x, fmaf(-w[k].y, u[k].y, ax));
+        ay = fmaf(w[k].x, u[k].y, fmaf(w[k].y, u[k].x, ay));
       } else {
-        ax += in ? u.x : 0.f;
-        ay += in ? u.y : 0.f;
+        ax += u[k].x;
+        ay += u[k].y;
       }
     }
   }
@@ -784,7 +827,7 @@ __global__ void __launch_bounds__(GT_THREADS) consensus_gather_batch(const Recon
                                                                       const int2* __restrict__ items,
                                                                       int jbase) {
   const int2 it = items[blockIdx.x];
-  const Recon& g = recs[it.x];
+  const Recon g = member(recs, it.x);
   if (*g.done) return;
   consensus_gather_body<NP, FUSE, kPMACE>(g, it.y, jbase);
 }
@@ -992,7 +1035,7 @@ __device__ __forceinline__ void block_sum(double (&v)[N]) {
 __global__ void __launch_bounds__(RED_T) nrmse_partial(const Recon* __restrict__ recs,
                                                        const int2* __restrict__ items, int update_stop) {
   const int2 it = items[blockIdx.x];
-  const Recon& g = recs[it.x];
+  const Recon g = member(recs, it.x);
   if ((update_stop && *g.done) || !g.xref) return;
   const int npx = g.n1 * g.n2;
   const int base = it.y * RED_PX;
@@ -1027,7 +1070,7 @@ __global__ void __launch_bounds__(RED_T) nrmse_partial(const Recon* __restrict__
 __global__ void __launch_bounds__(RED_T) nrmse_finish(const Recon* __restrict__ recs,
                                                       const int* __restrict__ items, int update_stop,
                                                       float tol, int min_iter) {
-  const Recon& g = recs[items[blockIdx.x]];
+  const Recon g = member(recs, items[blockIdx.x]);
   if ((update_stop && *g.done) || !g.xref) return;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < g.n_red; b += RED_T)
@@ -1115,14 +1158,14 @@ __device__ __forceinline__ void fit_small_body(const Recon& g, const int j) {
 
 template <int NP>
 __global__ void __launch_bounds__(NP * Geo<NP>::A) fit_small(const Recon* __restrict__ rec) {
-  fit_small_body<NP>(*rec, blockIdx.x);
+  fit_small_body<NP>(member(rec, 0), blockIdx.x);
 }
 
 template <int NP>
 __global__ void __launch_bounds__(NP * Geo<NP>::A) fit_small_batch(const Recon* __restrict__ recs,
                                                                    const int2* __restrict__ items) {
   const int2 it = items[blockIdx.x];
-  const Recon& g = recs[it.x];
+  const Recon g = member(recs, it.x);
   if (*g.done) return;
   fit_small_body<NP>(g, it.y);
 }
@@ -1131,7 +1174,7 @@ __global__ void __launch_bounds__(NP * Geo<NP>::A) fit_small_batch(const Recon* 
 template <int NP>
 __global__ void __launch_bounds__(row_threads<NP>()) fit_rows(const Recon* __restrict__ rec, int j0,
                                                                int check_done) {
-  const Recon& g = *rec;
+  const Recon g = member(rec, 0);
   if (check_done && *g.done) return;
   constexpr int A = Geo<NP>::A, B = Geo<NP>::B, M = B / A, S = row_cap<NP>();
   constexpr int RBn = rb_of<NP>();
@@ -1163,7 +1206,7 @@ __global__ void __launch_bounds__(row_threads<NP>()) fit_rows(const Recon* __res
 template <int NP>
 __global__ void __launch_bounds__(col_threads<NP>()) fit_cols(const Recon* __restrict__ rec, int j0,
                                                                int check_done) {
-  const Recon& g = *rec;
+  const Recon g = member(rec, 0);
   if (check_done && *g.done) return;
   constexpr int A = Geo<NP>::A, B = Geo<NP>::B, M = B / A;
   __shared__ float2 tile[col_rows<NP>() * CB];
@@ -1199,7 +1242,7 @@ __global__ void __launch_bounds__(col_threads<NP>()) fit_cols(const Recon* __res
 __global__ void __launch_bounds__(RED_T) fit_finish(const Recon* __restrict__ recs,
                                                     const int* __restrict__ items, int update_stop,
                                                     float tol, int min_iter) {
-  const Recon& g = recs[items[blockIdx.x]];
+  const Recon g = member(recs, items[blockIdx.x]);
   if (update_stop && *g.done) return;
   const int n = g.J * g.fit_bpp;
   double acc[1] = {0.0};

@@ -251,7 +251,7 @@ __device__ __forceinline__ bool meets(int p, int np, int a, int w) { return p < 
 constexpr int kPanel = 1024;
 __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int jb, int lo, int tiles_c,
                                                      int tile0, int xcd) {
-  __shared__ int lj[256], lc[256], wsum[4];
+  __shared__ int lj[256], lr[256], lc[256], wsum[4];
   __shared__ int count[kPanel], at[kPanel];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = lo + (int)blockIdx.x * GT_R, tc0 = (int)blockIdx.y * kPanel;
@@ -274,6 +274,7 @@ __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int 
       if (in) {
         const int k = base + __popcll(m & ((1ull << lane) - 1));
         lj[k] = j;
+        lr[k] = (p.x - row) * 65536;
         lc[k] = p.y;
       }
       __syncthreads();
@@ -284,7 +285,9 @@ __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int 
           const int k = k0 + lane;
           const bool hit = k < n && meets(lc[k], g.np, c0, GT_C);
           const unsigned long long h = __ballot(hit);
-          if (pass && hit) g.tile_list[cur + __popcll(h & ((1ull << lane) - 1))] = lj[k];
+          if (pass && hit)
+            g.tile_list[cur + __popcll(h & ((1ull << lane) - 1))] =
+                make_int2(lj[k], lr[k] | ((lc[k] - c0) & 0xffff));
           cur += __popcll(h);
         }
         // each tile column belongs to one wave
@@ -383,34 +386,39 @@ __global__ void __launch_bounds__(256) setup_row_items_k(const Recon g, int ja, 
 // the entries k, k + GT_K, ...; their sums are added in order.  Bound by the
 // L2 reads of the tables (24 B per patch pixel).
 __global__ void __launch_bounds__(GT_THREADS) setup_sums_k(const Recon g, int first_tile) {
-  constexpr int NPX = GT_R * GT_C, LIST = 256;
-  __shared__ int2 sl[LIST];
+  constexpr int NPX = GT_R * GT_C, U = 8;
   __shared__ double ps[GT_K > 1 ? (GT_K - 1) * NPX : 1];
   __shared__ float2 pt[GT_K > 1 ? (GT_K - 1) * NPX : 1];
-  const int tid = threadIdx.x, pxl = tid % NPX, part = tid / NPX, np = g.np;
+  const int tid = threadIdx.x, pxl = tid % NPX, np = g.np;
+  const int part = __builtin_amdgcn_readfirstlane(tid / NPX);
   const int4 ti = g.tiles[first_tile + blockIdx.x];
-  const int R = ti.z + pxl / GT_C, C = ti.w + pxl % GT_C;
+  const int lr = pxl / GT_C, lc = pxl % GT_C, R = ti.z + lr, C = ti.w + lc;
   const bool inside = R < g.n1 && C < g.n2;
   const size_t px = inside ? (size_t)R * g.n2 + C : 0;
   const float2 x = g.xhat[px];
+  const int2* list = g.tile_list + ti.x;
   double acc = 0.0;
   float ax = 0.f, ay = 0.f;
-  for (int b0 = 0; b0 < ti.y; b0 += LIST) {
-    const int nb = ti.y - b0 < LIST ? ti.y - b0 : LIST;
-    __syncthreads();
-    for (int i = tid; i < nb; i += GT_THREADS) sl[i] = g.pos[g.tile_list[ti.x + b0 + i]];
-    __syncthreads();
-#pragma unroll 8
-    for (int i = part; i < nb; i += GT_K) {
-      const unsigned rr = (unsigned)(R - sl[i].x), cc = (unsigned)(C - sl[i].y);
-      const bool in = rr < (unsigned)np && cc < (unsigned)np;
+  for (int i0 = part; i0 < ti.y; i0 += U * GT_K) {
+    double om[U];
+    float2 d[U], w[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int i = i0 + k * GT_K;
+      const int2 e = list[i < ti.y ? i : ti.y - 1];
+      const unsigned rr = (unsigned)(lr - (e.y >> 16)), cc = (unsigned)(lc - (int)(short)e.y);
+      const bool in = rr < (unsigned)np && cc < (unsigned)np && i < ti.y;
       const unsigned o = in ? rr * np + cc : 0u;
-      const double om = g.omega64[o];
-      const float2 u = start_state(g, g.d[o], x);
-      const float2 w = in ? g.gw[o] : make_float2(0.f, 0.f);
-      acc += in ? om : 0.0;
-      ax = fmaf(w.x, u.x, fmaf(-w.y, u.y, ax));
-      ay = fmaf(w.x, u.y, fmaf(w.y, u.x, ay));
+      om[k] = in ? g.omega64[o] : 0.0;
+      d[k] = g.d[o];
+      w[k] = in ? g.gw[o] : make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const float2 u = start_state(g, d[k], x);
+      acc += om[k];
+      ax = fmaf(w[k].x, u.x, fmaf(-w[k].y, u.y, ax));
+      ay = fmaf(w[k].x, u.y, fmaf(w[k].y, u.x, ay));
     }
   }
   if constexpr (GT_K > 1) {
