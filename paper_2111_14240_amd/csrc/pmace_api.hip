@@ -75,6 +75,7 @@ struct pmace_batch {
   Recon* recs;                 // device: member descriptors
   int2* items[kClasses];       // device: agent items per fused patch size (kSmallNp)
   int nitems[kClasses];
+  bool zeros[kClasses];        // some member's probe has exact zeros
   int ppw[kClasses];           // patches per workgroup of each class's merged agent launch
   int2* gitems[kClasses];      // device: gather items per class
   int ngitems[kClasses];
@@ -165,7 +166,7 @@ pmace_status check_params(const pmace_params* p) {
 // Section offsets inside the workspace (relative to the aligned base).
 struct Layout {
   size_t t, ys, pos, d, pc, dinv, gw, omega64, laminv, num, sold, xbar, xhat, stage, tiles, list, status, desc,
-      ritems, red, tw, fit, dr, qtiles, qlist, citems, clist, order, total;
+      ritems, red, tw, fit, dr, zmask, qtiles, qlist, citems, clist, order, total;
 };
 
 // Patch sides whose default agent is the split (coset-block) one: a build
@@ -291,6 +292,7 @@ Layout layout_of(const pmace_params& p) {
   L.tw = o;      o = align_up(o + 256 * 8);
   L.fit = o;     o = align_up(o + (size_t)p.num_pos * std::max(fit_bpp(p), sp ? 4 : 0) * 8);
   L.dr = o;      o = align_up(o + (sp ? np2 * 8 : 0));
+  L.zmask = o;   o = align_up(o + (size_t)p.np * 16 * 8);
   L.qtiles = o;  o = align_up(o + (sp ? split_tiles(p) * 16 : 0));
   L.qlist = o;   o = align_up(o + (sp ? split_list(p) * 4 : 0));
   const bool rs = rowspec_allowed(p);
@@ -447,6 +449,7 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   h.twn = reinterpret_cast<float2*>(base + L.tw);
   h.fit = reinterpret_cast<double*>(base + L.fit);
   h.dr = reinterpret_cast<float2*>(base + L.dr);
+  h.zmask = reinterpret_cast<unsigned long long*>(base + L.zmask);
   h.part = h.stage;   // the split layout keeps its partial sums where the stage would be
   h.qtiles = reinterpret_cast<int4*>(base + L.qtiles);
   h.qlist = reinterpret_cast<int*>(base + L.qlist);
@@ -807,7 +810,7 @@ pmace_status enqueue_batch_iteration(pmace_batch* b, hipStream_t st, bool lanes,
   for (int k = 0; k < kClasses; ++k)
     if (b->nitems[k] > 0)
       PM_HIP(pmace::launch_small_batch(kSmallNp[k], b->recs, b->items[k], b->nitems[k], b->gitems[k],
-                                       b->ngitems[k], b->ppw[k], st));
+                                       b->ngitems[k], b->ppw[k], b->zeros[k], st));
   int lane = 0;
   for (int i = 0; i < b->n; ++i) {
     pmace_ctx* c = b->ctxs[i];
@@ -923,6 +926,7 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
     for (int r = 0; r < c->h.n_red; ++r) ritems.push_back(make_int2(i, r));
     const int k = own_chain(c) ? -1 : class_of(c->prm.np);
     if (k < 0) continue;
+    b->zeros[k] = b->zeros[k] || c->h.has_zero;
     if (items[k].empty()) b->ppw[k] = c->h.ppw;   // the class takes its first member's choice
     for (int j = 0; j < c->prm.num_pos; ++j) items[k].push_back(make_int2(i, j));
     for (int t = 0; t < c->ngitems; ++t) gitems[k].push_back(make_int2(i, t));

@@ -134,6 +134,8 @@ struct Recon {
                         //   (X - 2 rho U)/Np^2 = X (sb - s2r ys/|X|)
   float np2f;           // Np^2
   int has_zero;         // the probe has exact zeros (the agent's d == 0 rule applies)
+  unsigned long long* zmask;  // then: bit nb of word r A + p marks d == 0 at row r, column p + A nb
+                        //   (A threads per line of the side's transform), one word per thread of a row
   float cx, co, cn;     // PMACE: xbar' = cx xbar + Lambda^{-1} (co S_old - cn S_new):
                         //   cx = 2 (1 - rho), co = (1 - rho)/rho, cn = 1/rho
   // Split (coset) layout, PMACE with Np = 2M and a probe without zeros: each
@@ -202,7 +204,7 @@ hipError_t launch_small_iteration(int np, const Recon& h, int ntiles, hipStream_
 // per workgroup, and the fused gather + image update over `gitems` (recon
 // index, tile).
 hipError_t launch_small_batch(int np, const Recon* recs, const int2* items, int nitems,
-                              const int2* gitems, int ngitems, int ppw, hipStream_t st);
+                              const int2* gitems, int ngitems, int ppw, bool zeros, hipStream_t st);
 // Np > 128, one reconstruction, chunk by chunk; chunk_tiles[g] = (first tile,
 // tile count) of chunk g (host array); the descriptor h passed by value.
 // batch_rec non-null: run as a batch member (its kernels honour the stop

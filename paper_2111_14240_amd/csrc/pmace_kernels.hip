@@ -43,7 +43,9 @@ namespace pmace {
 // kRowSpec / kSharpRowSpec: PMACE / SHARP+ on the Np > 128 passes with
 // every state kept as the row spectrum of the stored state (see
 // agent_rows_body).
-constexpr int kPMACE = 0, kSharpPlus = 1, kRowSpec = 2, kSharpRowSpec = 3;
+// kNoZeros: PMACE on the whole-patch agent with a probe without exact zeros
+// (without the rule for them it needs fewer registers and instructions).
+constexpr int kPMACE = 0, kSharpPlus = 1, kRowSpec = 2, kSharpRowSpec = 3, kNoZeros = 4;
 template <int METHOD> constexpr bool row_spec() { return METHOD == kRowSpec || METHOD == kSharpRowSpec; }
 template <int METHOD> constexpr bool sharp() { return METHOD == kSharpPlus || METHOD == kSharpRowSpec; }
 
@@ -67,6 +69,7 @@ __device__ __forceinline__ Recon member(const Recon* __restrict__ recs, int i) {
   mark_global<UNIFORM>(g.ys);
   mark_global<UNIFORM>(g.pos);
   mark_global<UNIFORM>(g.d);
+  mark_global<UNIFORM>(g.zmask);
   mark_global<UNIFORM>(g.pc);
   mark_global<UNIFORM>(g.dinv);
   mark_global<UNIFORM>(g.gw);
@@ -136,10 +139,8 @@ __device__ __forceinline__ float2 agent_input(float2 s, float2 xb, float2 d, flo
 
 // Epilogue (a6-a8) from the unnormalised inverse transform z of the spectrum
 // step's output, for probe pixel k.
-//   PMACE : z = F^*((W - 2 rho U)/Np^2) is the new d t, stored as it is.  Where
-//           d == 0 the agent returns its input, w = v, so the state there is
-//           t <- (1 - 2 rho) v (the old state and xbar are read only at such
-//           pixels, and only for a probe with zeros).  No u is written.
+//   PMACE : z = F^*((W - 2 rho U)/Np^2) is the new d t, stored as it is, except
+//           where d == 0 (zero_rule below).  No u is written.
 //   SHARP+: a = z/Np^2 = P_a s; the next state t = (1 - 2 beta) a + beta s -
 //           beta d P_j xbar (P_Q s of this iteration is d P_j xbar of the last
 //           one: P_Q is a projection, so P_Q s_{k+1} = P_Q P_a s_k), and the
@@ -156,15 +157,40 @@ __device__ __forceinline__ void sharp_output(float2 z, float2 t_old, float2* tp,
 template <int METHOD>
 __device__ __forceinline__ void agent_output(float2 z, float2* tp, const float2* xp, int k,
                                              const Recon& g, float2* u_out) {
-  if constexpr (METHOD == kPMACE) {
-    float2 sn = z;
-    if (g.has_zero) {
-      const float2 dk = g.d[k];
-      if (dk.x == 0.f && dk.y == 0.f) sn = cscale(mann_v(*tp, *xp, g.two_rho), 1.f - g.two_rho);
+  if constexpr (METHOD == kPMACE || METHOD == kNoZeros) *tp = z;
+  else sharp_output(z, *tp, tp, xp, k, g, u_out);
+}
+
+// PMACE where d == 0: the agent returns its input, w = v, so the state there is
+// t <- (1 - 2 rho) v, v = t + 2 rho P_j xbar (the old state and xbar are read only
+// at such pixels).  m: the zeros among this thread's pixels c = p + A nb of its
+// row (bit nb; see Recon::zmask), all 0 for a probe without zeros.  The loads
+// of eight pixels go out together; tested and loaded pixel by pixel, the
+// inverse row pass of 300 positions of 160^2 behind an aperture took 53 us
+// against the forward one's 34.
+template <int NP>
+__device__ __forceinline__ unsigned long long zero_bits(const Recon& g, int r, int p) {
+  return g.has_zero ? g.zmask[r * Geo<NP>::A + p] : 0ull;
+}
+template <int NP>
+__device__ __forceinline__ void zero_rule(float2 (&x)[Geo<NP>::B], unsigned long long m, const float2* trow,
+                                          const float2* xrow, int p, float two_rho) {
+  constexpr int A = Geo<NP>::A, B = Geo<NP>::B, U = B < 8 ? B : 8;
+  if (m == 0) return;
+#pragma unroll
+  for (int n0 = 0; n0 < B; n0 += U) {
+    float2 t[U], xb[U];
+#pragma unroll
+    for (int k = 0; k < U && n0 + k < B; ++k) {
+      t[k] = xb[k] = make_float2(0.f, 0.f);
+      if (m >> (n0 + k) & 1) {
+        t[k] = trow[p + A * (n0 + k)];
+        xb[k] = xrow[p + A * (n0 + k)];
+      }
     }
-    *tp = sn;
-  } else {
-    sharp_output(z, *tp, tp, xp, k, g, u_out);
+#pragma unroll
+    for (int k = 0; k < U && n0 + k < B; ++k)
+      if (m >> (n0 + k) & 1) x[n0 + k] = cscale(mann_v(t[k], xb[k], two_rho), 1.f - two_rho);
   }
 }
 
@@ -220,6 +246,8 @@ __device__ __forceinline__ void agent_fused_body(const Recon& g, const int j, co
   for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int ka = 0; ka < A; ++ka) yv[m * A + ka] = yc[(size_t)(q + A * m + B * ka) * NP];
+  unsigned long long zeros = 0;
+  if constexpr (METHOD == kPMACE) zeros = zero_bits<NP>(g, r, p);
   __syncthreads();
   float2* row = tile + r * S;
   row_fwd<NP>(x, row, p, tw);
@@ -249,6 +277,7 @@ __device__ __forceinline__ void agent_fused_body(const Recon& g, const int j, co
     for (int ka = 0; ka < A; ++ka) x[m * A + ka] = row[p + A * m + B * ka];
   row_inv<NP>(x, row, p, tw);
   if (!live) return;   // no barrier follows
+  if constexpr (METHOD == kPMACE) zero_rule<NP>(x, zeros, trow, xrow, p, two_rho);
 
   float2* urow = g.stage + pb + (size_t)r * NP;  // SHARP+ only
 #pragma unroll
@@ -275,7 +304,7 @@ __global__ void __launch_bounds__(PPW * NP * Geo<NP>::A) agent_fused(const Recon
 // Batched: block b handles work items (reconstruction, position) b PPW ...
 // b PPW + PPW - 1 of the nitems; a block all of whose items belong to stopped
 // members returns at once (the test is the same in every thread).
-template <int NP, int PPW>
+template <int NP, int METHOD, int PPW>
 __global__ void __launch_bounds__(PPW * NP * Geo<NP>::A) agent_fused_batch(
     const Recon* __restrict__ recs, const int2* __restrict__ items, int nitems) {
   constexpr int NT = NP * Geo<NP>::A;
@@ -283,7 +312,7 @@ __global__ void __launch_bounds__(PPW * NP * Geo<NP>::A) agent_fused_batch(
     const int2 it = items[blockIdx.x];
     const Recon g = member(recs, it.x);
     if (*g.done) return;
-    agent_fused_body<NP, kPMACE>(g, it.y);
+    agent_fused_body<NP, METHOD>(g, it.y);
   } else {
     const int i0 = (int)blockIdx.x * PPW;
     bool any = false;
@@ -292,7 +321,7 @@ __global__ void __launch_bounds__(PPW * NP * Geo<NP>::A) agent_fused_batch(
     const int i = i0 + (int)threadIdx.x / NT;
     const int2 it = items[i < nitems ? i : nitems - 1];
     const Recon g = member<false>(recs, it.x);
-    agent_fused_body<NP, kPMACE, PPW>(g, it.y, i < nitems && *g.done == 0);
+    agent_fused_body<NP, METHOD, PPW>(g, it.y, i < nitems && *g.done == 0);
   }
 }
 
@@ -660,9 +689,14 @@ __device__ __forceinline__ void agent_rowsinv_body(const Recon& g, const int j0)
 #pragma unroll
     for (int nb = 0; nb < B; ++nb) t_old[nb] = trow[p + A * nb];
   }
-  if constexpr (METHOD == kPMACE) twf.store(tw, tid);
+  unsigned long long zeros = 0;
+  if constexpr (METHOD == kPMACE) {
+    zeros = zero_bits<NP>(g, r, p);
+    twf.store(tw, tid);
+  }
   __syncthreads();
   row_inv<NP>(x, tile + rl * S, p, tw);
+  if constexpr (METHOD == kPMACE) zero_rule<NP>(x, zeros, trow, xrow, p, g.two_rho);
 #pragma unroll
   for (int nb = 0; nb < B; ++nb) {
     const int c = p + A * nb;
@@ -1780,8 +1814,10 @@ static void small_agent(const Recon& h, hipStream_t st) {
     const dim3 grid((h.J + PPW - 1) / PPW), block(PPW * N * Geo<N>::A);
     if (h.method == kSharpPlus)
       hipLaunchKernelGGL((agent_fused<N, kSharpPlus, PPW>), grid, block, 0, st, h);
-    else
+    else if (h.has_zero)
       hipLaunchKernelGGL((agent_fused<N, kPMACE, PPW>), grid, block, 0, st, h);
+    else
+      hipLaunchKernelGGL((agent_fused<N, kNoZeros, PPW>), grid, block, 0, st, h);
   }
 }
 
@@ -1822,26 +1858,30 @@ hipError_t launch_small_iteration(int np, const Recon& h, int ntiles, hipStream_
 }
 
 template <int N, int PPW>
-static void small_batch_agent(const Recon* recs, const int2* items, int nitems, hipStream_t st) {
-  if constexpr (PPW * N * Geo<N>::A <= 1024)
-    hipLaunchKernelGGL((agent_fused_batch<N, PPW>), dim3((nitems + PPW - 1) / PPW),
-                       dim3(PPW * N * Geo<N>::A), 0, st, recs, items, nitems);
+static void small_batch_agent(const Recon* recs, const int2* items, int nitems, bool zeros, hipStream_t st) {
+  if constexpr (PPW * N * Geo<N>::A <= 1024) {
+    const dim3 grid((nitems + PPW - 1) / PPW), block(PPW * N * Geo<N>::A);
+    if (zeros)
+      hipLaunchKernelGGL((agent_fused_batch<N, kPMACE, PPW>), grid, block, 0, st, recs, items, nitems);
+    else
+      hipLaunchKernelGGL((agent_fused_batch<N, kNoZeros, PPW>), grid, block, 0, st, recs, items, nitems);
+  }
 }
 
 template <int N>
 static hipError_t small_batch(const Recon* recs, const int2* items, int nitems, const int2* gitems,
-                              int ngitems, int ppw, hipStream_t st) {
+                              int ngitems, int ppw, bool zeros, hipStream_t st) {
   if constexpr (N <= 64) {
     switch (ppw) {
-      case 1: small_batch_agent<N, 1>(recs, items, nitems, st); break;
-      case 2: small_batch_agent<N, 2>(recs, items, nitems, st); break;
-      case 4: small_batch_agent<N, 4>(recs, items, nitems, st); break;
-      case 8: small_batch_agent<N, 8>(recs, items, nitems, st); break;
+      case 1: small_batch_agent<N, 1>(recs, items, nitems, zeros, st); break;
+      case 2: small_batch_agent<N, 2>(recs, items, nitems, zeros, st); break;
+      case 4: small_batch_agent<N, 4>(recs, items, nitems, zeros, st); break;
+      case 8: small_batch_agent<N, 8>(recs, items, nitems, zeros, st); break;
       default: return hipErrorInvalidValue;
     }
   } else {
     if (ppw != 1) return hipErrorInvalidValue;
-    small_batch_agent<N, 1>(recs, items, nitems, st);
+    small_batch_agent<N, 1>(recs, items, nitems, zeros, st);
   }
   if (ngitems > 0)
     hipLaunchKernelGGL((consensus_gather_batch<N, true>), dim3(ngitems), dim3(GT_THREADS), 0, st, recs, gitems,
@@ -1850,15 +1890,15 @@ static hipError_t small_batch(const Recon* recs, const int2* items, int nitems, 
 }
 
 hipError_t launch_small_batch(int np, const Recon* recs, const int2* items, int nitems,
-                              const int2* gitems, int ngitems, int ppw, hipStream_t st) {
+                              const int2* gitems, int ngitems, int ppw, bool zeros, hipStream_t st) {
   if (nitems <= 0) return hipSuccess;
   if (ppw < 1 || ppw > max_ppw(np)) return hipErrorInvalidValue;
   switch (np) {
-    case 32: return small_batch<32>(recs, items, nitems, gitems, ngitems, ppw, st);
-    case 48: return small_batch<48>(recs, items, nitems, gitems, ngitems, ppw, st);
-    case 64: return small_batch<64>(recs, items, nitems, gitems, ngitems, ppw, st);
-    case 96: return small_batch<96>(recs, items, nitems, gitems, ngitems, ppw, st);
-    case 128: return small_batch<128>(recs, items, nitems, gitems, ngitems, ppw, st);
+    case 32: return small_batch<32>(recs, items, nitems, gitems, ngitems, ppw, zeros, st);
+    case 48: return small_batch<48>(recs, items, nitems, gitems, ngitems, ppw, zeros, st);
+    case 64: return small_batch<64>(recs, items, nitems, gitems, ngitems, ppw, zeros, st);
+    case 96: return small_batch<96>(recs, items, nitems, gitems, ngitems, ppw, zeros, st);
+    case 128: return small_batch<128>(recs, items, nitems, gitems, ngitems, ppw, zeros, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -108,6 +108,33 @@ __global__ void __launch_bounds__(256) setup_tables_k(const Recon g, const float
   raise(g.status, flag);
 }
 
+// The exact zeros of the probe by the threads of the row transforms (A to a
+// row), see Recon::zmask.
+__global__ void __launch_bounds__(256) setup_zeros_k(const Recon g, int A) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= g.np * A) return;
+  const float2* row = g.d + (size_t)(i / A) * g.np + i % A;
+  unsigned long long m = 0;
+  for (int nb = 0; nb < g.np / A; ++nb) {
+    const float2 d = row[A * nb];
+    if (d.x == 0.f && d.y == 0.f) m |= 1ull << nb;
+  }
+  g.zmask[i] = m;
+}
+
+int line_threads(int np) {
+  switch (np) {
+    case 32: return Geo<32>::A;
+    case 48: return Geo<48>::A;
+    case 64: return Geo<64>::A;
+    case 96: return Geo<96>::A;
+    case 128: return Geo<128>::A;
+    case 160: return Geo<160>::A;
+    case 192: return Geo<192>::A;
+    default: return Geo<256>::A;
+  }
+}
+
 // ys = scale sqrt(z), four to a thread.  Bound by memory (8 B per patch pixel).
 __global__ void __launch_bounds__(256) setup_amplitudes4_k(const Recon g, const float4* __restrict__ z,
                                                            float scale, long long total4) {
@@ -512,6 +539,10 @@ hipError_t launch_setup_tables(const Recon& h, Recon* rec, int2* ritems, const S
                          k.lo, k.nitems, nseg, k.item0, rn);
     }
     hipLaunchKernelGGL(setup_sums_k, dim3(k.tiles_r * tiles_c), dim3(GT_THREADS), 0, st, h, k.tile0);
+  }
+  if (h.has_zero) {
+    const int A = line_threads(h.np);
+    hipLaunchKernelGGL(setup_zeros_k, dim3(blocks_for(h.np * A, 256)), dim3(256), 0, st, h, A);
   }
   const long long n = (long long)h.n1 * h.n2;
   hipLaunchKernelGGL(setup_images_k, dim3(blocks_for(n, 256)), dim3(256), 0, st, h, rec, ritems);
