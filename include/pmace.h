@@ -126,8 +126,9 @@ size_t pmace_footprint(const pmace_params* params);
  *               by the caller and kept alive until pmace_destroy
  *   hip_stream  hipStream_t the context queues all its work on (NULL = the
  *               null stream)
- * Inputs are read during this call's stream work; this call synchronises the
- * stream before returning, so the caller may free them afterwards.
+ * Inputs are read during this call's stream work, which this call waits for
+ * before returning, so the caller may free them afterwards; the rest of the
+ * set-up (from the workspace alone) is stream-ordered.
  * Errors: EINVAL (bad sizes/ranges, non-finite or negative intensity, position
  * outside the object), EUNSUPPORTED (np), ENOMEM (ws_bytes too small),
  * EDEVICE.  On error *out is NULL. */
@@ -260,7 +261,8 @@ void pmace_batch_destroy(pmace_batch* batch);
  *   workspace_d >= pmace_simulate_footprint(np, num_pos) bytes (caller-owned);
  *   scale_out (host, may be NULL) receives peak_photons / max I (1 if
  *   noise-free): multiply the probe by sqrt(scale) to keep the object's units.
- * Synchronises (positions are validated on the host). */
+ * Synchronises.  A position whose patch leaves the object is found on the
+ * device: EINVAL, and z_d's contents are then undefined. */
 size_t pmace_simulate_footprint(int32_t np, int32_t num_pos);
 pmace_status pmace_simulate(int32_t n1, int32_t n2, int32_t np, int32_t num_pos,
                             const void* probe_d, const int32_t* pos_d, const void* x_d,

@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <utility>
 #include <vector>
@@ -17,6 +18,39 @@
 #include "pmace_internal.hpp"
 
 using pmace::Recon;
+
+namespace {
+std::mutex g_slots_mu;
+void* g_slots[pmace::kHostSlotsKept];
+size_t g_nslots = 0;
+}  // namespace
+
+namespace pmace {
+void* take_host_slot() {
+  {
+    std::lock_guard<std::mutex> lk(g_slots_mu);
+    if (g_nslots > 0) return g_slots[--g_nslots];
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kHostSlot, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return p;
+}
+
+void give_host_slot(void* slot) {
+  if (!slot) return;
+  {
+    std::lock_guard<std::mutex> lk(g_slots_mu);
+    if (g_nslots < kHostSlotsKept) {
+      g_slots[g_nslots++] = slot;
+      return;
+    }
+  }
+  (void)hipHostFree(slot);
+}
+}  // namespace pmace
 
 namespace {
 
@@ -62,6 +96,7 @@ struct pmace_ctx {
   long long asked;                // iterations pmace_iterate has been asked for
   bool batched;                   // has been a batch member: its stop flag may be set
   pmace_status sticky;            // first asynchronous failure seen
+  void* slot;                     // pinned host memory for read-backs, or null
   unsigned long long resets;      // times the host cleared the stop flag
   // batches holding a copy of this context's descriptor (and its index there):
   // pmace_set_reference updates those copies too
@@ -70,6 +105,7 @@ struct pmace_ctx {
 
 struct pmace_batch {
   int n;
+  void* slot;                  // pinned host memory for read-backs, or null
   hipStream_t stream;
   std::vector<pmace_ctx*> ctxs;
   Recon* recs;                 // device: member descriptors
@@ -314,6 +350,16 @@ pmace_status record(pmace_ctx* c, pmace_status s) {
   return s;
 }
 
+// Waits for a figure that the last launch wrote to `host` (null: reads it back
+// from the device word it also left it in).
+pmace_status read_figure(pmace_ctx* c, const double* host, const double* dev, double* out) {
+  if (!host && hipMemcpyAsync(out, dev, 8, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+    return record(c, PMACE_EDEVICE);
+  if (hipStreamSynchronize(c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
+  if (host) *out = *host;
+  return PMACE_OK;
+}
+
 // A member that runs as its own chain of kernels (three-pass or split agent).
 bool own_chain(const pmace_ctx* c) { return np_large(c->prm.np) || c->h.split; }
 
@@ -414,7 +460,9 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   c->asked = 0;
   c->batched = false;
   c->resets = 0;
+  c->slot = nullptr;
   if (hipGetDevice(&c->device) != hipSuccess) { delete c; return PMACE_EDEVICE; }
+  c->slot = pmace::take_host_slot();
   auto fail = [&](pmace_status e) {
     pmace_destroy(c);
     return e;
@@ -508,13 +556,19 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   in.split_allowed = split_allowed(p) ? 1 : 0;
   in.rowspec_allowed = rowspec_allowed(p) ? 1 : 0;
   if (pmace::launch_setup_inputs(h, in, c->fitem, st) != hipSuccess) return fail(PMACE_EDEVICE);
-  std::vector<int32_t> back(kAlign / 4 + 2 * (size_t)J);
+  const size_t back_bytes = kAlign + (size_t)J * 8;
+  std::vector<int32_t> pageable;
+  int32_t* back = static_cast<int32_t*>(c->slot);
+  if (!back || back_bytes > pmace::kHostSlot) {
+    pageable.resize(back_bytes / 4);
+    back = pageable.data();
+  }
   const auto read_back = [&](size_t bytes) {
-    return hipMemcpyAsync(back.data(), base + L.status, bytes, hipMemcpyDeviceToHost, st) == hipSuccess &&
+    return hipMemcpyAsync(back, base + L.status, bytes, hipMemcpyDeviceToHost, st) == hipSuccess &&
            hipStreamSynchronize(st) == hipSuccess;
   };
-  if (!read_back(back.size() * 4)) return fail(PMACE_EDEVICE);
-  const int32_t* pos = back.data() + kAlign / 4;
+  if (!read_back(back_bytes)) return fail(PMACE_EDEVICE);
+  const int32_t* pos = back + kAlign / 4;
   constexpr unsigned kBad = pmace::kStatusBadIntensity | pmace::kStatusBadProbe | pmace::kStatusBadPosition;
   unsigned status = (unsigned)back[0];
   if (status & kBad) return fail(PMACE_EINVAL);
@@ -676,12 +730,10 @@ pmace_status pmace_nrmse(pmace_ctx* c, double* out) {
   if (!c) return PMACE_ESTATE;
   if (!out) return PMACE_EINVAL;
   if (!c->h.xref) return PMACE_ESTATE;
-  if (pmace::launch_nrmse(c->dev, c->ritems, c->h.n_red, c->fitem, 1, 0, 0.f, 0, c->stream) !=
-          hipSuccess ||
-      hipMemcpyAsync(out, c->h.track + 1, 8, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-      hipStreamSynchronize(c->stream) != hipSuccess)
+  double* host = static_cast<double*>(c->slot);
+  if (pmace::launch_nrmse(c->dev, c->ritems, c->h.n_red, c->fitem, 1, 0, 0.f, 0, host, c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
-  return PMACE_OK;
+  return read_figure(c, host, c->h.track + 1, out);
 }
 
 pmace_status pmace_set_stream(pmace_ctx* c, void* hip_stream) {
@@ -697,22 +749,22 @@ pmace_status pmace_set_stream(pmace_ctx* c, void* hip_stream) {
 pmace_status pmace_data_fit(pmace_ctx* c, double* out) {
   if (!c) return PMACE_ESTATE;
   if (!out) return PMACE_EINVAL;
+  double* host = static_cast<double*>(c->slot);
   if (pmace::launch_fit_member(c->h, c->dev, 0, c->stream) != hipSuccess ||
-      pmace::launch_fit_finish(c->dev, c->fitem, 1, 0, 0.f, 0, c->stream) != hipSuccess ||
-      hipMemcpyAsync(out, c->h.track + 6, 8, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-      hipStreamSynchronize(c->stream) != hipSuccess)
+      pmace::launch_fit_finish(c->dev, c->fitem, 1, 0, 0.f, 0, host, c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
-  return PMACE_OK;
+  return read_figure(c, host, c->h.track + 6, out);
 }
 
 pmace_status pmace_sync(pmace_ctx* c) {
   if (!c) return PMACE_ESTATE;
-  unsigned status = 0;
-  if (hipMemcpyAsync(&status, c->h.status, 4, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+  unsigned word = 0;
+  unsigned* status = c->slot ? static_cast<unsigned*>(c->slot) : &word;
+  if (hipMemcpyAsync(status, c->h.status, 4, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
   if (c->sticky != PMACE_OK) return c->sticky;
-  if (status & 1u) return record(c, PMACE_EDIVERGED);
+  if (*status & pmace::kStatusNonFinite) return record(c, PMACE_EDIVERGED);
   return PMACE_OK;
 }
 
@@ -729,6 +781,7 @@ void pmace_destroy(pmace_ctx* c) {
   for (const auto& hb : c->holders) batch_forget(hb.first, hb.second);
   (void)hipStreamSynchronize(c->stream);
   c->graph.release();
+  pmace::give_host_slot(c->slot);
   delete c;
 }
 
@@ -833,14 +886,14 @@ pmace_status enqueue_batch_iteration(pmace_batch* b, hipStream_t st, bool lanes,
   PM_HIP(pmace::launch_tick(b->recs, b->fitems, b->n, b->rule.max_iter, 0, st));
   if (check && b->rule.criterion == PMACE_STOP_NRMSE) {
     PM_HIP(pmace::launch_nrmse(b->recs, b->ritems, b->nritems, b->fitems, b->n, 1, b->rule.tol,
-                               b->rule.min_iter, st));
+                               b->rule.min_iter, nullptr, st));
   } else if (check) {
     for (int k = 0; k < kClasses; ++k)
       PM_HIP(pmace::launch_fit_batch(kSmallNp[k], b->recs, b->items[k], b->nitems[k], st));
     for (int i = 0; i < b->n; ++i)
       if (own_chain(b->ctxs[i]) && !b->pruned[i])
         PM_HIP(pmace::launch_fit_member(b->ctxs[i]->h, b->recs + i, 1, st));
-    PM_HIP(pmace::launch_fit_finish(b->recs, b->fitems, b->n, 1, b->rule.tol, b->rule.min_iter, st));
+    PM_HIP(pmace::launch_fit_finish(b->recs, b->fitems, b->n, 1, b->rule.tol, b->rule.min_iter, nullptr, st));
   }
   PM_HIP(pmace::launch_tick(b->recs, b->fitems, b->n, b->rule.max_iter, 1, st));
   return PMACE_OK;
@@ -878,6 +931,7 @@ void batch_release(pmace_batch* b) {
     if (b->join[l]) (void)hipEventDestroy(b->join[l]);
   }
   if (b->fork) (void)hipEventDestroy(b->fork);
+  pmace::give_host_slot(b->slot);
   delete b;
 }
 
@@ -905,6 +959,7 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   pmace_batch* b = new (std::nothrow) pmace_batch();
   if (!b) return PMACE_ENOMEM;
   b->n = n;
+  b->slot = pmace::take_host_slot();
   b->stream = ctxs[0]->stream;
   b->ctxs.assign(ctxs, ctxs + n);
   b->rule = *rule;
@@ -1021,10 +1076,13 @@ pmace_status pmace_batch_step(pmace_batch* b, int32_t n_iter) {
 pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, int32_t* iters,
                                   double* data_fit) {
   if (!b) return PMACE_ESTATE;
-  std::vector<pmace::PollItem> got(b->n);
-  if (pmace::launch_poll(b->recs, b->n, b->polled, b->stream) != hipSuccess ||
-      hipMemcpyAsync(got.data(), b->polled, got.size() * sizeof(pmace::PollItem), hipMemcpyDeviceToHost,
-                     b->stream) != hipSuccess ||
+  const size_t bytes = (size_t)b->n * sizeof(pmace::PollItem);
+  const bool pinned = b->slot && bytes <= pmace::kHostSlot;  // the kernel then writes there itself
+  std::vector<pmace::PollItem> pageable(pinned ? 0 : b->n);
+  const pmace::PollItem* got = pinned ? static_cast<pmace::PollItem*>(b->slot) : pageable.data();
+  if (pmace::launch_poll(b->recs, b->n, pinned ? static_cast<pmace::PollItem*>(b->slot) : b->polled, b->stream) !=
+          hipSuccess ||
+      (!pinned && hipMemcpyAsync(pageable.data(), b->polled, bytes, hipMemcpyDeviceToHost, b->stream) != hipSuccess) ||
       hipStreamSynchronize(b->stream) != hipSuccess)
     return PMACE_EDEVICE;
   bool changed = false;

@@ -7,6 +7,17 @@
 
 namespace pmace {
 
+// Pinned host memory for what a call reads back (device-mapped, usable from any
+// device): slots of kHostSlot bytes kept for reuse, at most kHostSlotsKept of
+// them while unused (2 MiB), handed out under a lock.  A small read-back through
+// pageable memory takes 22 us from the launch before it to the host, through a
+// slot 15, and written there by the kernel itself 11.  take() returns null if
+// the memory cannot be had; callers then read back through pageable memory.
+constexpr size_t kHostSlot = 32768;
+constexpr size_t kHostSlotsKept = 64;
+void* take_host_slot();
+void give_host_slot(void* slot);  // null: nothing
+
 // Launch-shape parameters.  The defaults are overridden at build time by the
 // values the tuner picked (tuned.json beside the package, passed as -D flags).
 #ifndef PMACE_GT_K
@@ -218,9 +229,10 @@ hipError_t launch_set_state(const Recon& h, const Recon* rec, const float2* v,
 // a10: NRMSE of xhat against xref for the reconstructions in `ritems`
 // (recon index, reduction block); `fitems` lists the recon indices to finish.
 // With update_stop, a member whose NRMSE changed by less than tol once
-// min_iter iterations have been counted is stopped.
+// min_iter iterations have been counted is stopped.  host (device-mapped, may
+// be null): the last listed reconstruction's NRMSE, for one on demand.
 hipError_t launch_nrmse(const Recon* recs, const int2* ritems, int nritems, const int* fitems,
-                        int nf, int update_stop, float tol, int min_iter, hipStream_t st);
+                        int nf, int update_stop, float tol, int min_iter, double* host, hipStream_t st);
 // Data-fit cost of eq. (4) at xhat: partials of one reconstruction (all Np;
 // rec = its device descriptor, check_done: skip if stopped), or of the
 // batched Np <= 128 positions `items` (recon index, position).
@@ -228,9 +240,9 @@ hipError_t launch_fit_member(const Recon& h, const Recon* rec, int check_done, h
 hipError_t launch_fit_batch(int np, const Recon* recs, const int2* items, int nitems, hipStream_t st);
 // Sum the partials: with update_stop into track[4] (previous value to
 // track[5]), stopping members whose cost changed by at most tol (relative);
-// without, into track[6] only.
+// without, into track[6] only.  host as for launch_nrmse.
 hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int update_stop, float tol,
-                             int min_iter, hipStream_t st);
+                             int min_iter, double* host, hipStream_t st);
 // cap = 0: count one iteration for each running member (before the stop
 // rule is evaluated); cap = 1: stop running members that reached max_iter.
 hipError_t launch_tick(const Recon* recs, const int* fitems, int nf, int max_iter, int cap,

@@ -1103,7 +1103,7 @@ __global__ void __launch_bounds__(RED_T) nrmse_partial(const Recon* __restrict__
 
 __global__ void __launch_bounds__(RED_T) nrmse_finish(const Recon* __restrict__ recs,
                                                       const int* __restrict__ items, int update_stop,
-                                                      float tol, int min_iter) {
+                                                      float tol, int min_iter, double* host) {
   const Recon g = member(recs, items[blockIdx.x]);
   if ((update_stop && *g.done) || !g.xref) return;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1119,6 +1119,7 @@ __global__ void __launch_bounds__(RED_T) nrmse_finish(const Recon* __restrict__ 
   g.track[0] = sref;
   g.track[2] = prev;
   g.track[1] = e;
+  if (host) *host = e;
   // stop rule: NRMSE change below tol once min_iter iterations have run
   if (update_stop && g.track[3] >= (double)min_iter && fabs(e - prev) < (double)tol) *g.done = 1;
 }
@@ -1275,7 +1276,7 @@ __global__ void __launch_bounds__(col_threads<NP>()) fit_cols(const Recon* __res
 // |C_k - C_{k-1}| <= tol C_{k-1} once min_iter iterations have run.
 __global__ void __launch_bounds__(RED_T) fit_finish(const Recon* __restrict__ recs,
                                                     const int* __restrict__ items, int update_stop,
-                                                    float tol, int min_iter) {
+                                                    float tol, int min_iter, double* host) {
   const Recon g = member(recs, items[blockIdx.x]);
   if (update_stop && *g.done) return;
   const int n = g.J * g.fit_bpp;
@@ -1286,6 +1287,7 @@ __global__ void __launch_bounds__(RED_T) fit_finish(const Recon* __restrict__ re
   const double cst = acc[0];
   if (!update_stop) {  // on demand: leaves the stop rule's history alone
     g.track[6] = cst;
+    if (host) *host = cst;
     return;
   }
   const double prev = g.track[4];
@@ -2149,12 +2151,12 @@ hipError_t launch_set_state(const Recon& h, const Recon* rec, const float2* v,
 }
 
 hipError_t launch_nrmse(const Recon* recs, const int2* ritems, int nritems, const int* fitems, int nf,
-                        int update_stop, float tol, int min_iter, hipStream_t st) {
+                        int update_stop, float tol, int min_iter, double* host, hipStream_t st) {
   if (nritems > 0)
     hipLaunchKernelGGL(nrmse_partial, dim3(nritems), dim3(RED_T), 0, st, recs, ritems, update_stop);
   if (nf > 0)
     hipLaunchKernelGGL(nrmse_finish, dim3(nf), dim3(RED_T), 0, st, recs, fitems, update_stop, tol,
-                       min_iter);
+                       min_iter, host);
   return hipGetLastError();
 }
 
@@ -2211,10 +2213,10 @@ hipError_t launch_fit_batch(int np, const Recon* recs, const int2* items, int ni
 }
 
 hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int update_stop, float tol,
-                             int min_iter, hipStream_t st) {
+                             int min_iter, double* host, hipStream_t st) {
   if (nf > 0)
     hipLaunchKernelGGL(fit_finish, dim3(nf), dim3(RED_T), 0, st, recs, fitems, update_stop, tol,
-                       min_iter);
+                       min_iter, host);
   return hipGetLastError();
 }
 

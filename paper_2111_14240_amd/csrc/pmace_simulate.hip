@@ -17,7 +17,6 @@
 #include <cstdint>
 #include <cstring>
 #include <mutex>
-#include <new>
 #include <type_traits>
 
 #include "pmace.h"
@@ -159,11 +158,21 @@ __device__ __forceinline__ void block_max_to(float v, unsigned* maxbits) {
   }
 }
 
-// Np <= 128: one position per workgroup, the whole frame in LDS.
+// A position as the frame kernels use it: one outside the object raises the
+// flag ctl[1] and is moved inside, so nothing is read out of range (the call
+// then fails; what it wrote is meaningless).
+__device__ __forceinline__ int2 inside(int2 p, int n1, int n2, int np, unsigned* ctl) {
+  const int2 q = make_int2(min(max(p.x, 0), n1 - np), min(max(p.y, 0), n2 - np));
+  if ((q.x != p.x || q.y != p.y) && threadIdx.x == 0) atomicOr(ctl + 1, 1u);
+  return q;
+}
+
+// Np <= 128: one position per workgroup, the whole frame in LDS.  ctl: the
+// maximum's bits, the position flag.
 template <int NP>
 __global__ void __launch_bounds__(NP * Geo<NP>::A)
 sim_small_k(const float2* __restrict__ d, const int2* __restrict__ pos, const float2* __restrict__ x,
-            int n2, float* __restrict__ z, unsigned* __restrict__ maxbits) {
+            int n1, int n2, float* __restrict__ z, unsigned* __restrict__ ctl) {
   constexpr int A = Geo<NP>::A, B = Geo<NP>::B, S = NP + A, NT = NP * A, M = B / A;
   static_assert(exch_phases<NP>() == 1, "the whole-frame tile exchanges in one round");
   __shared__ float2 tile[NP * S];
@@ -171,7 +180,7 @@ sim_small_k(const float2* __restrict__ d, const int2* __restrict__ pos, const fl
   const int tid = threadIdx.x;
   fill_twiddles<NP>(tw, tid, NT);
   const int j = blockIdx.x;
-  const int2 pj = pos[j];
+  const int2 pj = inside(pos[j], n1, n2, NP, ctl);
   const int r = tid / A, p = tid % A, c = tid % NP, q = tid / NP;
   const float2* xrow = x + (size_t)(pj.x + r) * n2 + pj.y;
   float2* row = tile + r * S;
@@ -204,14 +213,14 @@ sim_small_k(const float2* __restrict__ d, const int2* __restrict__ pos, const fl
       zj[(size_t)(q + A * m + B * ka) * NP + c] = e;
       mx = fmaxf(mx, e);
     }
-  block_max_to<NT>(mx, maxbits);
+  block_max_to<NT>(mx, ctl);
 }
 
 // Np > 128, row pass: frames and forward row DFTs (scaled 1/sqrt(Np)) to fr.
 template <int NP>
 __global__ void __launch_bounds__(kSimRB * Geo<NP>::A)
 sim_rows_k(const float2* __restrict__ d, const int2* __restrict__ pos, const float2* __restrict__ x,
-           int n2, float2* __restrict__ fr, float sc) {
+           int n1, int n2, float2* __restrict__ fr, unsigned* __restrict__ ctl, float sc) {
   constexpr int A = Geo<NP>::A, B = Geo<NP>::B, M = B / A, S = row_cap<NP>();
   __shared__ float2 tile[kSimRB * S];
   __shared__ float2 tw[NP];
@@ -219,7 +228,7 @@ sim_rows_k(const float2* __restrict__ d, const int2* __restrict__ pos, const flo
   fill_twiddles<NP>(tw, tid, kSimRB * A);
   const int j = blockIdx.x / (NP / kSimRB), rb = blockIdx.x % (NP / kSimRB);
   const int rl = tid / A, p = tid % A, r = rb * kSimRB + rl;
-  const int2 pj = pos[j];
+  const int2 pj = inside(pos[j], n1, n2, NP, ctl);
   const float2* xrow = x + (size_t)(pj.x + r) * n2 + pj.y;
   float2 v[B];
 #pragma unroll
@@ -268,16 +277,16 @@ sim_cols_k(const float2* __restrict__ fr, float* __restrict__ z, unsigned* __res
 }
 
 template <int NP>
-hipError_t launch_sim_intensities(int J, const float2* d, const int2* pos, const float2* x, int n2,
-                                  float2* fr, float* z, unsigned* maxbits, hipStream_t st) {
+hipError_t launch_sim_intensities(int J, const float2* d, const int2* pos, const float2* x, int n1, int n2,
+                                  float2* fr, float* z, unsigned* ctl, hipStream_t st) {
   if constexpr (NP <= 128) {
-    hipLaunchKernelGGL(sim_small_k<NP>, dim3(J), dim3(NP * Geo<NP>::A), 0, st, d, pos, x, n2, z, maxbits);
+    hipLaunchKernelGGL(sim_small_k<NP>, dim3(J), dim3(NP * Geo<NP>::A), 0, st, d, pos, x, n1, n2, z, ctl);
   } else {
     const float sc = 1.f / sqrtf((float)NP);  // 1/sqrt(Np) per pass
     hipLaunchKernelGGL(sim_rows_k<NP>, dim3(J * (NP / kSimRB)), dim3(kSimRB * Geo<NP>::A), 0, st, d, pos,
-                       x, n2, fr, sc);
+                       x, n1, n2, fr, ctl, sc);
     hipLaunchKernelGGL(sim_cols_k<NP>, dim3(J * (NP / kSimCB)), dim3(kSimCB * Geo<NP>::A), 0, st, fr, z,
-                       maxbits, sc);
+                       ctl, sc);
   }
   return hipGetLastError();
 }
@@ -476,15 +485,6 @@ __global__ void sim_clear_k(unsigned* __restrict__ ctl) {
   if (threadIdx.x < 2) ctl[threadIdx.x] = 0u;
 }
 
-// Flags (ctl[1] = 1) any position whose patch leaves the object.
-__global__ void sim_check_pos_k(const int2* __restrict__ pos, int J, int n1, int n2, int np,
-                                unsigned* __restrict__ ctl) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= J) return;
-  const int2 p = pos[j];
-  if (p.x < 0 || p.y < 0 || p.x > n1 - np || p.y > n2 - np) atomicOr(ctl + 1, 1u);
-}
-
 // Scratch of the allocation-free entry point: the maximum and the position
 // flag in the first 256 bytes, then (Np > 128) the frames' row transforms.
 // One copy per device, held until the process ends.
@@ -498,39 +498,43 @@ inline unsigned nblocks(long long n, int bs) { return (unsigned)((n + bs - 1) / 
 inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Intensities, optional Poisson draws and the scale, into z_d; `fr` holds the
-// row transforms (Np > 128), `maxbits` the cleared maximum.  Stream-ordered;
-// synchronises only to return the scale.
-pmace_status run_simulation(int32_t n2, int32_t np, int32_t num_pos, const void* probe_d,
+// row transforms (Np > 128), `ctl` the maximum and the position flag, read back
+// through `host` (two words).  Synchronises.
+pmace_status run_simulation(int32_t n1, int32_t n2, int32_t np, int32_t num_pos, const void* probe_d,
                             const int32_t* pos_d, const void* x_d, double peak_photons, uint64_t seed,
-                            float* z_d, float2* fr, unsigned* maxbits, double* scale_out,
+                            float* z_d, float2* fr, unsigned* ctl, unsigned* host, double* scale_out,
                             hipStream_t st) {
   const long long total = (long long)num_pos * np * np;
   const float2* dd = reinterpret_cast<const float2*>(probe_d);
   const int2* pp = reinterpret_cast<const int2*>(pos_d);
   const float2* xx = reinterpret_cast<const float2*>(x_d);
+  hipLaunchKernelGGL(pmace::sim_clear_k, dim3(1), dim3(64), 0, st, ctl);
   hipError_t e = hipErrorInvalidValue;
   switch (np) {
-    case 32: e = pmace::launch_sim_intensities<32>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 48: e = pmace::launch_sim_intensities<48>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 64: e = pmace::launch_sim_intensities<64>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 96: e = pmace::launch_sim_intensities<96>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 128: e = pmace::launch_sim_intensities<128>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 160: e = pmace::launch_sim_intensities<160>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 192: e = pmace::launch_sim_intensities<192>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
-    case 256: e = pmace::launch_sim_intensities<256>(num_pos, dd, pp, xx, n2, fr, z_d, maxbits, st); break;
+#define PMACE_SIM(N) \
+  case N: e = pmace::launch_sim_intensities<N>(num_pos, dd, pp, xx, n1, n2, fr, z_d, ctl, st); break;
+    PMACE_SIM(32)
+    PMACE_SIM(48)
+    PMACE_SIM(64)
+    PMACE_SIM(96)
+    PMACE_SIM(128)
+    PMACE_SIM(160)
+    PMACE_SIM(192)
+    PMACE_SIM(256)
+#undef PMACE_SIM
     default: break;
   }
   if (e != hipSuccess) return PMACE_EDEVICE;
   if (peak_photons > 0.0)
-    pmace::launch_poisson(z_d, maxbits, peak_photons, seed, total, st);
-  if (hipGetLastError() != hipSuccess) return PMACE_EDEVICE;
+    pmace::launch_poisson(z_d, ctl, peak_photons, seed, total, st);
+  if (hipGetLastError() != hipSuccess ||
+      hipMemcpyAsync(host, ctl, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+      hipStreamSynchronize(st) != hipSuccess)
+    return PMACE_EDEVICE;
+  if (host[1]) return PMACE_EINVAL;
   if (scale_out) {
-    unsigned mb = 0;
-    if (hipMemcpyAsync(&mb, maxbits, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-      return PMACE_EDEVICE;
     float mx;
-    std::memcpy(&mx, &mb, 4);
+    std::memcpy(&mx, &host[0], 4);
     *scale_out = (peak_photons > 0.0 && mx > 0.f) ? peak_photons / (double)mx : 1.0;
   }
   return PMACE_OK;
@@ -572,27 +576,15 @@ pmace_status pmace_simulate(int32_t n1, int32_t n2, int32_t np, int32_t num_pos,
     return PMACE_EUNSUPPORTED;
   if (ws_bytes < pmace_simulate_footprint(np, num_pos)) return PMACE_ENOMEM;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  // positions are checked on the host: the frame gather reads the object there
-  const size_t J = (size_t)num_pos;
-  int32_t* pos = new (std::nothrow) int32_t[2 * J];
-  if (!pos) return PMACE_ENOMEM;
-  if (hipMemcpyAsync(pos, pos_d, J * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess) {
-    delete[] pos;
-    return PMACE_EDEVICE;
-  }
-  bool ok = true;
-  for (size_t j = 0; j < J; ++j)
-    if (pos[2 * j] < 0 || pos[2 * j + 1] < 0 || pos[2 * j] > n1 - np || pos[2 * j + 1] > n2 - np) ok = false;
-  delete[] pos;
-  if (!ok) return PMACE_EINVAL;
-
   char* base = reinterpret_cast<char*>(up256(reinterpret_cast<size_t>(workspace_d)));
   float2* fr = reinterpret_cast<float2*>(base);
-  unsigned* maxbits = reinterpret_cast<unsigned*>(base + up256(J * np * np * 8));
-  if (hipMemsetAsync(maxbits, 0, 4, st) != hipSuccess) return PMACE_EDEVICE;
-  return run_simulation(n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, maxbits,
-                        scale_out, st);
+  unsigned* ctl = reinterpret_cast<unsigned*>(base + up256((size_t)num_pos * np * np * 8));
+  unsigned words[2];
+  void* slot = pmace::take_host_slot();
+  const pmace_status s = run_simulation(n1, n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl,
+                                        slot ? static_cast<unsigned*>(slot) : words, scale_out, st);
+  pmace::give_host_slot(slot);
+  return s;
 }
 
 size_t pmace_simulate_static_max_bytes(void) { return pmace::kSimScratchBytes - 256; }
@@ -614,18 +606,8 @@ pmace_status pmace_simulate_static(int32_t n1, int32_t n2, int32_t np, int32_t n
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   unsigned* ctl = reinterpret_cast<unsigned*>(sp);  // [0] maximum bits, [1] position flag
   float2* fr = reinterpret_cast<float2*>(sp + 256);
-  // positions are checked on the device (no host buffer): the frame gather
-  // reads the object there, so nothing is launched until they are known good
-  hipLaunchKernelGGL(pmace::sim_clear_k, dim3(1), dim3(64), 0, st, ctl);
-  hipLaunchKernelGGL(pmace::sim_check_pos_k, dim3(nblocks(num_pos, 256)), dim3(256), 0, st,
-                     reinterpret_cast<const int2*>(pos_d), num_pos, n1, n2, np, ctl);
-  unsigned bad = 0;
-  if (hipGetLastError() != hipSuccess ||
-      hipMemcpyAsync(&bad, ctl + 1, 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return PMACE_EDEVICE;
-  if (bad) return PMACE_EINVAL;
-  return run_simulation(n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl,
+  unsigned words[2];   // (no pinned slot: this entry point allocates nothing at all)
+  return run_simulation(n1, n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl, words,
                         scale_out, st);
 }
 
