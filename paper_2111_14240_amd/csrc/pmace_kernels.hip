@@ -35,6 +35,8 @@
 // Every kernel reads its reconstruction from a device descriptor (Recon) and
 // returns at once when that reconstruction's stop flag is set, so many
 // reconstructions can share one launch (work items name the reconstruction).
+#include <algorithm>
+
 #include "pmace_dft.hpp"
 #include "pmace_internal.hpp"
 
@@ -554,6 +556,78 @@ __device__ __forceinline__ void agent_rows_body(const Recon& g, const int j0) {
       if constexpr (NT) store_nt(out + p + A * m + B * ka, x[m * A + ka]);
       else out[p + A * m + B * ka] = x[m * A + ka];
     }
+}
+
+// The row-spectrum row pass for Np = 256, several positions per workgroup:
+// workgroup b takes row block b mod (NP / RBn) of the positions j0 + q, j0 + q +
+// groups, ..., q = b / (NP / RBn), so the block's probe rows stay in registers
+// and the twiddle table is set up once for all of them, and the next position's
+// loads are issued behind the stores of the last.  Each row is transformed
+// within one wave, so there is no barrier in the loop and the waves drift
+// apart: some load while others transform.  The same arithmetic as
+// agent_rows_body.  Measured, 4 iterations and a checkpoint of 1600 positions
+// with 1 position per workgroup 4085 us, 2 4020, 3.1 (512 groups) 3973, 3
+// (534) 3998, 4 4020, 6.3 4012, 25 4057; of 900 positions of SHARP+, 1 3134, 1.8
+// 3093, 3 3069, 3.5 3081, 14 3113.  (Np = 192 and 160, with 32
+// rows of 24 and 40 points a thread to a block, were 2% to 9% slower with
+// several: they hold fewer waves, and the probe rows cost another.)
+template <int NP, int METHOD, bool NT>
+__device__ __forceinline__ void agent_rows_loop(const Recon& g, const int j0, const int cnt, const int groups) {
+  static_assert(row_spec<METHOD>(), "row-spectrum states");
+  constexpr int A = Geo<NP>::A, B = Geo<NP>::B, M = B / A, S = row_cap<NP>();
+  constexpr int RBn = rb_of<NP>();
+  __shared__ float2 tile[RBn * S];
+  __shared__ float2 tw[NP];
+  const int tid = threadIdx.x;
+  TwiddleFetch<NP, RBn * A> twf;
+  twf.fetch(g.twn, tid);
+  const int rb = blockIdx.x % (NP / RBn), first = blockIdx.x / (NP / RBn);
+  const int rl = tid / A, p = tid % A, r = rb * RBn + rl;
+  float2 d[B], h[B], xb[B];
+#pragma unroll
+  for (int nb = 0; nb < B; ++nb) d[nb] = g.d[r * NP + p + A * nb];
+  const auto fetch = [&](int jl) {
+    const int2 pj = g.pos[j0 + jl];
+    const float2* trow = g.t + (size_t)(j0 + jl) * NP * NP + (size_t)r * NP;
+    const float2* xrow = g.xbar + (size_t)(pj.x + r) * g.n2 + pj.y;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int ka = 0; ka < A; ++ka) h[m * A + ka] = trow[p + A * m + B * ka];
+#pragma unroll
+    for (int nb = 0; nb < B; ++nb) xb[nb] = xrow[p + A * nb];
+  };
+  fetch(first);
+  twf.store(tw, tid);
+  __syncthreads();
+  for (int jl = first;;) {
+    float2 x[B];
+#pragma unroll
+    for (int nb = 0; nb < B; ++nb) x[nb] = cscale(cmul(d[nb], xb[nb]), g.two_rho);
+    row_fwd<NP>(x, tile + rl * S, p, tw);
+    constexpr float fnp = (float)NP;
+    float2* out = g.stage + ((size_t)jl * NP + r) * NP;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int ka = 0; ka < A; ++ka) {
+        const int k = m * A + ka;
+        const float2 v = make_float2(fmaf(fnp, h[k].x, x[k].x), fmaf(fnp, h[k].y, x[k].y));
+        if constexpr (NT) store_nt(out + p + A * m + B * ka, v);
+        else out[p + A * m + B * ka] = v;
+      }
+    jl += groups;
+    if (jl >= cnt) break;
+    fetch(jl);
+  }
+}
+
+template <int NP, int METHOD, bool NT, bool CHECK>
+__global__ void __launch_bounds__(row_threads<NP>()) agent_rows_multi(const Recon g, int j0, int cnt, int groups) {
+  if constexpr (CHECK) {
+    if (*g.done) return;
+  }
+  agent_rows_loop<NP, METHOD, NT>(g, j0, cnt, groups);
 }
 
 // NT: the stage (and, in the column pass, the new row-spectrum states) written
@@ -1905,6 +1979,24 @@ hipError_t launch_small_batch(int np, const Recon* recs, const int2* items, int 
   }
 }
 
+// The row pass of the row-spectrum agent over cnt positions from j0.
+template <int NP, int METHOD, bool NT, bool CHECK>
+static void rowspec_rows(const Recon& h, int j0, int cnt, hipStream_t st) {
+  constexpr int NB = NP / rb_of<NP>(), RT = row_threads<NP>();
+  if constexpr (NP == 256) {
+    // about three positions per workgroup, in whole rounds of the 1024
+    // workgroups (16 to a position) that the chip holds; one for fewer than
+    // two rounds of them
+    const int groups = cnt >= 128 ? std::max(64, (cnt / 3 + 32) / 64 * 64) : cnt;
+    hipLaunchKernelGGL((agent_rows_multi<NP, METHOD, NT, CHECK>), dim3(groups * NB), dim3(RT), 0, st, h, j0, cnt,
+                       groups);
+  } else if constexpr (CHECK) {
+    hipLaunchKernelGGL((agent_rows_batch<NP, METHOD, NT>), dim3(cnt * NB), dim3(RT), 0, st, h, j0);
+  } else {
+    hipLaunchKernelGGL((agent_rows<NP, METHOD, NT>), dim3(cnt * NB), dim3(RT), 0, st, h, j0);
+  }
+}
+
 template <int NP>
 static void large_iteration(const Recon& h, const Recon* batch_rec, const int2* chunk_tiles,
                             const int2* chunk_rows, hipStream_t st) {
@@ -1922,10 +2014,10 @@ static void large_iteration(const Recon& h, const Recon* batch_rec, const int2* 
       const dim3 crb(cr_threads<NP>()), cg(cr.y);
       if (batch_rec) {
         if (h.nt_stage) {
-          hipLaunchKernelGGL((agent_rows_batch<NP, kRowSpec, true>), rgrid, dim3(RT), 0, st, h, j0);
+          rowspec_rows<NP, kRowSpec, true, true>(h, j0, cnt, st);
           hipLaunchKernelGGL((agent_cols_batch<NP, kRowSpec, true>), cgrid, dim3(CT), 0, st, h, j0);
         } else {
-          hipLaunchKernelGGL((agent_rows_batch<NP, kRowSpec>), rgrid, dim3(RT), 0, st, h, j0);
+          rowspec_rows<NP, kRowSpec, false, true>(h, j0, cnt, st);
           hipLaunchKernelGGL((agent_cols_batch<NP, kRowSpec>), cgrid, dim3(CT), 0, st, h, j0);
         }
         if (cr.y > 0 && one_chunk)
@@ -1934,9 +2026,9 @@ static void large_iteration(const Recon& h, const Recon* batch_rec, const int2* 
           hipLaunchKernelGGL((consensus_rows<NP, true, kRowSpec, false>), cg, crb, 0, st, h, cr.x, j0);
       } else if (h.method == kSharpPlus) {
         if (h.nt_stage)
-          hipLaunchKernelGGL((agent_rows<NP, kSharpRowSpec, true>), rgrid, dim3(RT), 0, st, h, j0);
+          rowspec_rows<NP, kSharpRowSpec, true, false>(h, j0, cnt, st);
         else
-          hipLaunchKernelGGL((agent_rows<NP, kSharpRowSpec>), rgrid, dim3(RT), 0, st, h, j0);
+          rowspec_rows<NP, kSharpRowSpec, false, false>(h, j0, cnt, st);
         if (h.nt_stage)
           hipLaunchKernelGGL((agent_cols<NP, kSharpRowSpec, true>), cgrid, dim3(CT), 0, st, h, j0);
         else
@@ -1947,10 +2039,10 @@ static void large_iteration(const Recon& h, const Recon* batch_rec, const int2* 
           hipLaunchKernelGGL((consensus_rows<NP, false, kSharpRowSpec, false>), cg, crb, 0, st, h, cr.x, j0);
       } else {
         if (h.nt_stage) {
-          hipLaunchKernelGGL((agent_rows<NP, kRowSpec, true>), rgrid, dim3(RT), 0, st, h, j0);
+          rowspec_rows<NP, kRowSpec, true, false>(h, j0, cnt, st);
           hipLaunchKernelGGL((agent_cols<NP, kRowSpec, true>), cgrid, dim3(CT), 0, st, h, j0);
         } else {
-          hipLaunchKernelGGL((agent_rows<NP, kRowSpec>), rgrid, dim3(RT), 0, st, h, j0);
+          rowspec_rows<NP, kRowSpec, false, false>(h, j0, cnt, st);
           hipLaunchKernelGGL((agent_cols<NP, kRowSpec>), cgrid, dim3(CT), 0, st, h, j0);
         }
         if (cr.y > 0 && one_chunk)

@@ -140,7 +140,7 @@ __device__ double poisson_draw(double lam, Uniforms& u) {
 // one atomic (non-negative floats order as their bit patterns, so an
 // unsigned max is a float max).
 // ---------------------------------------------------------------------------
-constexpr int kSimRB = PMACE_RB;   // rows per workgroup of the row pass (Np > 128)
+constexpr int kSimRB = 16;         // rows per workgroup of the row pass (Np > 128)
 constexpr int kSimCB = PMACE_CB;   // columns per workgroup of the column pass
 static_assert(160 % kSimRB == 0 && 192 % kSimRB == 0 && 256 % kSimRB == 0, "row block");
 static_assert(160 % kSimCB == 0 && 192 % kSimCB == 0 && 256 % kSimCB == 0, "column block");
@@ -217,32 +217,41 @@ sim_small_k(const float2* __restrict__ d, const int2* __restrict__ pos, const fl
 }
 
 // Np > 128, row pass: frames and forward row DFTs (scaled 1/sqrt(Np)) to fr.
+// A workgroup takes one row block of several positions (j, j + groups, ...), so
+// the block's probe rows stay in registers, the twiddles are made once, and,
+// with no barrier in the loop (a row is transformed within a wave), some waves
+// load while others transform.  Simulate call, 900 positions of 256^2: 615 us
+// with one position and 32 rows per workgroup, 574 with 16 rows of 3 or 4.
 template <int NP>
 __global__ void __launch_bounds__(kSimRB * Geo<NP>::A)
-sim_rows_k(const float2* __restrict__ d, const int2* __restrict__ pos, const float2* __restrict__ x,
-           int n1, int n2, float2* __restrict__ fr, unsigned* __restrict__ ctl, float sc) {
+sim_rows_k(const float2* __restrict__ d, const int2* __restrict__ pos, const float2* __restrict__ x, int J,
+           int groups, int n1, int n2, float2* __restrict__ fr, unsigned* __restrict__ ctl, float sc) {
   constexpr int A = Geo<NP>::A, B = Geo<NP>::B, M = B / A, S = row_cap<NP>();
   __shared__ float2 tile[kSimRB * S];
   __shared__ float2 tw[NP];
   const int tid = threadIdx.x;
-  fill_twiddles<NP>(tw, tid, kSimRB * A);
-  const int j = blockIdx.x / (NP / kSimRB), rb = blockIdx.x % (NP / kSimRB);
+  const int first = blockIdx.x / (NP / kSimRB), rb = blockIdx.x % (NP / kSimRB);
   const int rl = tid / A, p = tid % A, r = rb * kSimRB + rl;
-  const int2 pj = inside(pos[j], n1, n2, NP, ctl);
-  const float2* xrow = x + (size_t)(pj.x + r) * n2 + pj.y;
-  float2 v[B];
+  float2 dv[B], v[B];
 #pragma unroll
-  for (int nb = 0; nb < B; ++nb) {
-    const int cc = p + A * nb;
-    v[nb] = cmul(d[r * NP + cc], xrow[cc]);
-  }
+  for (int nb = 0; nb < B; ++nb) dv[nb] = d[r * NP + p + A * nb];
+  fill_twiddles<NP>(tw, tid, kSimRB * A);
   __syncthreads();
-  row_fwd<NP>(v, tile + rl * S, p, tw);
-  float2* out = fr + ((size_t)j * NP + r) * NP;
+#pragma unroll 1
+  for (int j = first; j < J; j += groups) {
+    const int2 pj = inside(pos[j], n1, n2, NP, ctl);
+    const float2* xrow = x + (size_t)(pj.x + r) * n2 + pj.y;
 #pragma unroll
-  for (int m = 0; m < M; ++m)
+    for (int nb = 0; nb < B; ++nb) v[nb] = xrow[p + A * nb];
 #pragma unroll
-    for (int ka = 0; ka < A; ++ka) out[p + A * m + B * ka] = cscale(v[m * A + ka], sc);
+    for (int nb = 0; nb < B; ++nb) v[nb] = cmul(dv[nb], v[nb]);
+    row_fwd<NP>(v, tile + rl * S, p, tw);
+    float2* out = fr + ((size_t)j * NP + r) * NP;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int ka = 0; ka < A; ++ka) out[p + A * m + B * ka] = cscale(v[m * A + ka], sc);
+  }
 }
 
 // Np > 128, column pass: forward column DFTs (scaled 1/sqrt(Np)) and the
@@ -283,8 +292,9 @@ hipError_t launch_sim_intensities(int J, const float2* d, const int2* pos, const
     hipLaunchKernelGGL(sim_small_k<NP>, dim3(J), dim3(NP * Geo<NP>::A), 0, st, d, pos, x, n1, n2, z, ctl);
   } else {
     const float sc = 1.f / sqrtf((float)NP);  // 1/sqrt(Np) per pass
-    hipLaunchKernelGGL(sim_rows_k<NP>, dim3(J * (NP / kSimRB)), dim3(kSimRB * Geo<NP>::A), 0, st, d, pos,
-                       x, n1, n2, fr, ctl, sc);
+    const int groups = J < 256 ? J : 256;  // (each CU holds 4 of the 16 x 256 workgroups at a time)
+    hipLaunchKernelGGL(sim_rows_k<NP>, dim3(groups * (NP / kSimRB)), dim3(kSimRB * Geo<NP>::A), 0, st, d, pos,
+                       x, J, groups, n1, n2, fr, ctl, sc);
     hipLaunchKernelGGL(sim_cols_k<NP>, dim3(J * (NP / kSimCB)), dim3(kSimCB * Geo<NP>::A), 0, st, fr, z,
                        ctl, sc);
   }
