@@ -278,7 +278,9 @@ __device__ __forceinline__ bool meets(int p, int np, int a, int w) { return p < 
 // dispatcher sends workgroup b to XCD b mod 8, and each XCD has its own L2:
 // slot b gets tile (b mod 8) q + b / 8 of the row (q = n / 8; the last n mod 8
 // stay in place), and the second read of an edge line shared by two tiles
-// hits its L2.
+// hits its L2.  Without it (one launch, Np <= 128), rows of a multiple of 8
+// tiles are rotated by their number, or the short lists of the object's edge
+// columns would all be two XCDs' share.
 constexpr int kPanel = 1024;
 __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int jb, int lo, int tiles_c,
                                                      int tile0, int xcd) {
@@ -334,7 +336,8 @@ __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int 
       for (int t = tid; t < nt; t += 256) {
         const int n = count[t], start = n ? atomicAdd(g.cursor, n) : 0, tc = tc0 + t;
         at[t] = start;
-        const int slot = xcd && tc < 8 * q ? (tc % q) * 8 + tc / q : tc;
+        int slot = xcd && tc < 8 * q ? (tc % q) * 8 + tc / q : tc;
+        if (!xcd && tiles_c % 8 == 0) slot = (tc + (int)blockIdx.x) % tiles_c;
         g.tiles[(size_t)tile0 + (size_t)blockIdx.x * tiles_c + slot] = make_int4(start, n, row, tc * GT_C);
       }
       __syncthreads();
@@ -379,7 +382,11 @@ __global__ void __launch_bounds__(256) setup_row_items_k(const Recon g, int ja, 
   const int lane = threadIdx.x & 63;
   const int item = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= nitems) return;
-  const int row = lo + item / nseg, col = (item % nseg) * CR_W;
+  // segment by segment: row by row, the two segments of a 1280-wide object
+  // alternated, and as workgroup b runs on XCD b mod 8 the long first ones all
+  // fell to the even XCDs (960 positions of 192^2: consensus 162 -> 101 us)
+  const int nrows = nitems / nseg;
+  const int row = lo + item % nrows, col = (item / nrows) * CR_W;
   __shared__ int4 pend[4][128];  // per wave: entries not yet written, in order
   int4* pw = pend[threadIdx.x >> 6];
   const auto covers = [&](const int4& e, int k) {
