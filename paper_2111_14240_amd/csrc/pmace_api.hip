@@ -731,7 +731,7 @@ pmace_status pmace_nrmse(pmace_ctx* c, double* out) {
   if (!out) return PMACE_EINVAL;
   if (!c->h.xref) return PMACE_ESTATE;
   double* host = static_cast<double*>(c->slot);
-  if (pmace::launch_nrmse(c->dev, c->ritems, c->h.n_red, c->fitem, 1, 0, 0.f, 0, host, c->stream) != hipSuccess)
+  if (pmace::launch_nrmse(c->dev, c->ritems, c->h.n_red, c->fitem, 1, 0, 0.f, 0, 0, host, c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
   return read_figure(c, host, c->h.track + 1, out);
 }
@@ -751,7 +751,7 @@ pmace_status pmace_data_fit(pmace_ctx* c, double* out) {
   if (!out) return PMACE_EINVAL;
   double* host = static_cast<double*>(c->slot);
   if (pmace::launch_fit_member(c->h, c->dev, 0, c->stream) != hipSuccess ||
-      pmace::launch_fit_finish(c->dev, c->fitem, 1, 0, 0.f, 0, host, c->stream) != hipSuccess)
+      pmace::launch_fit_finish(c->dev, c->fitem, 1, 0, 0.f, 0, 0, host, c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
   return read_figure(c, host, c->h.track + 6, out);
 }
@@ -883,19 +883,20 @@ pmace_status enqueue_batch_iteration(pmace_batch* b, hipStream_t st, bool lanes,
       PM_HIP(hipEventRecord(b->join[l], b->lanes[l]));
       PM_HIP(hipStreamWaitEvent(st, b->join[l], 0));
     }
-  PM_HIP(pmace::launch_tick(b->recs, b->fitems, b->n, b->rule.max_iter, 0, st));
   if (check && b->rule.criterion == PMACE_STOP_NRMSE) {
     PM_HIP(pmace::launch_nrmse(b->recs, b->ritems, b->nritems, b->fitems, b->n, 1, b->rule.tol,
-                               b->rule.min_iter, nullptr, st));
+                               b->rule.min_iter, b->rule.max_iter, nullptr, st));
   } else if (check) {
     for (int k = 0; k < kClasses; ++k)
       PM_HIP(pmace::launch_fit_batch(kSmallNp[k], b->recs, b->items[k], b->nitems[k], st));
     for (int i = 0; i < b->n; ++i)
       if (own_chain(b->ctxs[i]) && !b->pruned[i])
         PM_HIP(pmace::launch_fit_member(b->ctxs[i]->h, b->recs + i, 1, st));
-    PM_HIP(pmace::launch_fit_finish(b->recs, b->fitems, b->n, 1, b->rule.tol, b->rule.min_iter, nullptr, st));
+    PM_HIP(pmace::launch_fit_finish(b->recs, b->fitems, b->n, 1, b->rule.tol, b->rule.min_iter, b->rule.max_iter,
+                                    nullptr, st));
+  } else {
+    PM_HIP(pmace::launch_tick(b->recs, b->n, b->rule.max_iter, st));
   }
-  PM_HIP(pmace::launch_tick(b->recs, b->fitems, b->n, b->rule.max_iter, 1, st));
   return PMACE_OK;
 }
 

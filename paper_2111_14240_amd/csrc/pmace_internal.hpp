@@ -229,10 +229,11 @@ hipError_t launch_set_state(const Recon& h, const Recon* rec, const float2* v,
 // a10: NRMSE of xhat against xref for the reconstructions in `ritems`
 // (recon index, reduction block); `fitems` lists the recon indices to finish.
 // With update_stop, a member whose NRMSE changed by less than tol once
-// min_iter iterations have been counted is stopped.  host (device-mapped, may
+// min_iter iterations have been counted is stopped; the iteration is counted
+// first, for every listed member (stopped at max_iter).  host (device-mapped, may
 // be null): the last listed reconstruction's NRMSE, for one on demand.
 hipError_t launch_nrmse(const Recon* recs, const int2* ritems, int nritems, const int* fitems,
-                        int nf, int update_stop, float tol, int min_iter, double* host, hipStream_t st);
+                        int nf, int update_stop, float tol, int min_iter, int max_iter, double* host, hipStream_t st);
 // Data-fit cost of eq. (4) at xhat: partials of one reconstruction (all Np;
 // rec = its device descriptor, check_done: skip if stopped), or of the
 // batched Np <= 128 positions `items` (recon index, position).
@@ -242,11 +243,10 @@ hipError_t launch_fit_batch(int np, const Recon* recs, const int2* items, int ni
 // track[5]), stopping members whose cost changed by at most tol (relative);
 // without, into track[6] only.  host as for launch_nrmse.
 hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int update_stop, float tol,
-                             int min_iter, double* host, hipStream_t st);
-// cap = 0: count one iteration for each running member (before the stop
-// rule is evaluated); cap = 1: stop running members that reached max_iter.
-hipError_t launch_tick(const Recon* recs, const int* fitems, int nf, int max_iter, int cap,
-                       hipStream_t st);
+                             int min_iter, int max_iter, double* host, hipStream_t st);
+// Count one iteration for each running member (no stop-rule evaluation after
+// it), stopping those that reached max_iter.
+hipError_t launch_tick(const Recon* recs, int n, int max_iter, hipStream_t st);
 // A member's stop flag and figures, for all members of a batch into out[n].
 struct PollItem {
   double nrmse, iters, fit;

@@ -1139,6 +1139,15 @@ __device__ __forceinline__ void block_sum(double (&v)[N]) {
     }
 }
 
+// One iteration done: counts it for a member that ran it, stops the member if
+// that was the last allowed; returns the count.
+__device__ __forceinline__ double count_iteration(const Recon& g, int max_iter) {
+  const double n = g.track[3] + 1.0;
+  g.track[3] = n;
+  if (n >= (double)max_iter) *g.done = 1;
+  return n;
+}
+
 // update_stop = 0 evaluates on demand, also for stopped reconstructions.
 __global__ void __launch_bounds__(RED_T) nrmse_partial(const Recon* __restrict__ recs,
                                                        const int2* __restrict__ items, int update_stop) {
@@ -1177,9 +1186,13 @@ __global__ void __launch_bounds__(RED_T) nrmse_partial(const Recon* __restrict__
 
 __global__ void __launch_bounds__(RED_T) nrmse_finish(const Recon* __restrict__ recs,
                                                       const int* __restrict__ items, int update_stop,
-                                                      float tol, int min_iter, double* host) {
+                                                      float tol, int min_iter, int max_iter, double* host) {
   const Recon g = member(recs, items[blockIdx.x]);
-  if ((update_stop && *g.done) || !g.xref) return;
+  if (update_stop && *g.done) return;
+  if (!g.xref) {
+    if (update_stop && threadIdx.x == 0) count_iteration(g, max_iter);
+    return;
+  }
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < g.n_red; b += RED_T)
     for (int q = 0; q < 4; ++q) acc[q] += g.red[4 * b + q];
@@ -1195,7 +1208,8 @@ __global__ void __launch_bounds__(RED_T) nrmse_finish(const Recon* __restrict__ 
   g.track[1] = e;
   if (host) *host = e;
   // stop rule: NRMSE change below tol once min_iter iterations have run
-  if (update_stop && g.track[3] >= (double)min_iter && fabs(e - prev) < (double)tol) *g.done = 1;
+  if (update_stop && count_iteration(g, max_iter) >= (double)min_iter && fabs(e - prev) < (double)tol)
+    *g.done = 1;
 }
 
 // -------------------------------------------------------------------------
@@ -1350,7 +1364,7 @@ __global__ void __launch_bounds__(col_threads<NP>()) fit_cols(const Recon* __res
 // |C_k - C_{k-1}| <= tol C_{k-1} once min_iter iterations have run.
 __global__ void __launch_bounds__(RED_T) fit_finish(const Recon* __restrict__ recs,
                                                     const int* __restrict__ items, int update_stop,
-                                                    float tol, int min_iter, double* host) {
+                                                    float tol, int min_iter, int max_iter, double* host) {
   const Recon g = member(recs, items[blockIdx.x]);
   if (update_stop && *g.done) return;
   const int n = g.J * g.fit_bpp;
@@ -1367,23 +1381,17 @@ __global__ void __launch_bounds__(RED_T) fit_finish(const Recon* __restrict__ re
   const double prev = g.track[4];
   g.track[5] = prev;
   g.track[4] = cst;
-  if (g.track[3] >= (double)min_iter && isfinite(prev) && fabs(cst - prev) <= (double)tol * prev)
+  if (count_iteration(g, max_iter) >= (double)min_iter && isfinite(prev) && fabs(cst - prev) <= (double)tol * prev)
     *g.done = 1;
 }
 
-// One iteration done: count it for every member that ran it (before the
-// stop rule is evaluated), or (cap) stop members that reached max_iter.
-__global__ void tick_k(const Recon* __restrict__ recs, const int* __restrict__ items, int n,
-                       int max_iter, int cap) {
+// An iteration without an evaluation of the stop rule (the kernels that finish
+// an evaluation count theirs).
+__global__ void tick_k(const Recon* __restrict__ recs, int n, int max_iter) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const Recon& g = recs[items[i]];
-  if (*g.done) return;
-  if (cap) {
-    if (g.track[3] >= (double)max_iter) *g.done = 1;
-  } else {
-    g.track[3] += 1.0;
-  }
+  const Recon& g = recs[i];
+  if (!*g.done) count_iteration(g, max_iter);
 }
 
 // What a poll reads of each batch member, collected so that it comes to the
@@ -2243,12 +2251,12 @@ hipError_t launch_set_state(const Recon& h, const Recon* rec, const float2* v,
 }
 
 hipError_t launch_nrmse(const Recon* recs, const int2* ritems, int nritems, const int* fitems, int nf,
-                        int update_stop, float tol, int min_iter, double* host, hipStream_t st) {
+                        int update_stop, float tol, int min_iter, int max_iter, double* host, hipStream_t st) {
   if (nritems > 0)
     hipLaunchKernelGGL(nrmse_partial, dim3(nritems), dim3(RED_T), 0, st, recs, ritems, update_stop);
   if (nf > 0)
     hipLaunchKernelGGL(nrmse_finish, dim3(nf), dim3(RED_T), 0, st, recs, fitems, update_stop, tol,
-                       min_iter, host);
+                       min_iter, max_iter, host);
   return hipGetLastError();
 }
 
@@ -2305,18 +2313,15 @@ hipError_t launch_fit_batch(int np, const Recon* recs, const int2* items, int ni
 }
 
 hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int update_stop, float tol,
-                             int min_iter, double* host, hipStream_t st) {
+                             int min_iter, int max_iter, double* host, hipStream_t st) {
   if (nf > 0)
     hipLaunchKernelGGL(fit_finish, dim3(nf), dim3(RED_T), 0, st, recs, fitems, update_stop, tol,
-                       min_iter, host);
+                       min_iter, max_iter, host);
   return hipGetLastError();
 }
 
-hipError_t launch_tick(const Recon* recs, const int* fitems, int nf, int max_iter, int cap,
-                       hipStream_t st) {
-  if (nf > 0)
-    hipLaunchKernelGGL(tick_k, dim3(blocks_for(nf, 256)), dim3(256), 0, st, recs, fitems, nf, max_iter,
-                       cap);
+hipError_t launch_tick(const Recon* recs, int n, int max_iter, hipStream_t st) {
+  hipLaunchKernelGGL(tick_k, dim3(blocks_for(n, 64)), dim3(64), 0, st, recs, n, max_iter);
   return hipGetLastError();
 }
 
