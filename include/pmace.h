@@ -107,8 +107,8 @@ typedef struct pmace_batch pmace_batch;  /* several reconstructions stepped toge
  * Layout: agent states J*Np^2*8, amplitudes J*Np^2*4, object images N1*N2*36,
  * probe tables Np^2*48, positions J*8, a staging buffer of chunk*Np^2*8
  * bytes (Np > 128: the chunk's spectra; SHARP+ with Np <= 128: all J frames;
- * PMACE with Np <= 128: none), data-fit partials and the consensus tile
- * tables; each section 256-byte aligned. */
+ * PMACE with Np <= 128: none), data-fit partials, the probe's zero mask
+ * and the consensus tables; each section 256-byte aligned. */
 size_t pmace_footprint(const pmace_params* params);
 
 /* Alg. 1 initialisation: v_j = P_j x0 for every j.  Also computes
@@ -278,7 +278,7 @@ pmace_status pmace_simulate(int32_t n1, int32_t n2, int32_t np, int32_t num_pos,
  * num_pos*np*np*8 <= pmace_simulate_static_max_bytes() (64 MiB - 256 B, e.g.
  * 127 positions of 256 x 256), else ENOMEM; np <= 128 has no such limit.
  * Positions are validated on the device (EINVAL if a patch leaves the
- * object).  Every call on one GPU shares that GPU's array: calls that overlap
+ * object; z_d's contents are then undefined).  Every call on one GPU shares that GPU's array: calls that overlap
  * on one GPU (other streams, other threads) race; serialise them.
  * Synchronises hip_stream (the position check; and scale_out as in
  * pmace_simulate). */

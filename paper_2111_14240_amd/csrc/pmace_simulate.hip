@@ -319,7 +319,7 @@ hipError_t launch_sim_intensities(int J, const float2* d, const int2* pos, const
 // the counts are poisson_draw's, bit for bit.  Bound by the generator's
 // integer multiplies (about 17 64-bit products per element: 200 us for 900
 // patterns of 256^2) and the latency of the bright workgroups' draws.  The
-// simulate call on those: 1189 us with one element per thread, 645 now.
+// simulate call on those: 1189 us with one element per thread, 645 with this.
 constexpr int kPoisT = 256;
 // 8 waves per SIMD (64 VGPRs): the rare draws spill, the common path does not.
 // Measured, simulate call of 900 patterns of 256^2 at peak 1e6: 1122 us without
