@@ -600,7 +600,7 @@ def main():
                    "chunk": args.chunk,
                    **({"ppw": args.ppw} if args.ppw else {}),
                    "agent": agent,
-                   "iteration_graph": "HIP graphs of 32 iterations (single-iteration graph for the rest)"},
+                   "iteration_graph": "launched one by one (Np <= 64: HIP graphs of 32 once 256 have been asked for)"},
         "roofline": {"bound": "hbm", "kernel": iteration_kernels(np_, J, args.method, agent),
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(key),

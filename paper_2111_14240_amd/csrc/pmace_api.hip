@@ -576,8 +576,14 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   h.split = in.split_allowed && !h.has_zero ? 1 : 0;
   h.rowspec = in.rowspec_allowed && !h.has_zero ? 1 : 0;
   h.fit_bpp = h.split ? 4 : fit_bpp(p);
-  h.nt_stage =
-      h.rowspec && (double)std::min(chunk, p.num_pos) * np * np * 8.0 > 512.0 * (1 << 20) ? 1 : 0;
+  // Non-temporal stage: for 256-point rows from three quarters of the 256 MB
+  // Infinity Cache on (4 iterations: 200 positions, 100 MiB, 501 us without and
+  // 520 with it; 300, 150 MiB, 764 and 772; 600, 300 MiB, 1566 and 1499; 900,
+  // 450 MiB, 2341 and 2256; a solve of 400, 200 MiB, 1542 and 1519); for the
+  // shorter rows of the other sides only from twice the cache on (960 of 192^2,
+  // 270 MiB: 1484 and 1532).
+  const double stage_mib = (double)std::min(chunk, p.num_pos) * np * np * 8.0 / (1 << 20);
+  h.nt_stage = h.rowspec && stage_mib > (np == 256 ? 192.0 : 512.0) ? 1 : 0;
 
   // Split layout: the base tiles of its consensus, each with the positions
   // whose quadrant-0 block meets it in ascending order.

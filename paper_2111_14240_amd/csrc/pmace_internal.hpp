@@ -168,10 +168,10 @@ struct Recon {
   // state over Np, each row in natural frequency order.  The column pass then
   // writes the new state directly, and the consensus inverts the rows.
   int rowspec;
-  // Row-spectrum agent: when a chunk's stage is over twice the 256 MB
-  // Infinity Cache, the row pass writes it, and the column pass the new
-  // states (PMACE and SHARP+), with non-temporal stores (smaller stages gain
-  // from the cache on their way to the column pass)
+  // Row-spectrum agent: the row pass writes a large chunk's stage, and the
+  // column pass the new states (PMACE and SHARP+), with non-temporal stores
+  // (smaller stages gain from the Infinity Cache on their way to the column
+  // pass; the bound is set at init)
   int nt_stage;
   int4* citems;         // per (chunk, object row, segment): (list start, count, row, first column)
   int4* clist;          // per entry: (j, row of P_j on that object row, patch column, 0), in summing order
