@@ -2,7 +2,9 @@
 oracle, where a list can go wrong: more positions than a workgroup's batch of
 256, tile rows wider than a panel of 1024 tiles, several chunks with a ragged
 last one, equal columns and repeated positions (ties), rows that no patch
-covers, an object row in two segments.  The bar is that of the parity tests."""
+covers, an object row in two segments; and the 256-point row pass where it
+starts to take several positions per workgroup.  The bar is that of the parity
+tests."""
 import numpy as np
 import pytest
 
@@ -36,6 +38,10 @@ CASES = [
     (160, 300, 1300, 70, 33, "spread"),     # two segments, three chunks
     (192, 260, 300, 65, 0, "same"),
     (256, 300, 400, 17, 5, "two columns"),
+    # row passes of several positions per workgroup: from 128 on, and a remainder
+    (256, 300, 330, 127, 0, "spread"),
+    (256, 300, 330, 128, 0, "spread"),
+    (256, 300, 330, 201, 0, "spread"),
 ]
 
 
