@@ -448,7 +448,9 @@ __global__ void __launch_bounds__(256) setup_row_items_k(const Recon g, int ja, 
 // the accumulator image viewed as FP64, and (PMACE) the consensus sum S of the
 // starting states.  These are patches of one object (xhat holds it), so S
 // needs the probe tables only; its terms and their order are those of the
-// gather over the stored states.  GT_K threads share a pixel, thread k adding
+// gather over the stored states.  An entry that does not cover the pixel adds
+// exactly zero: the object there may be anything (a pixel that no patch covers
+// may hold NaN, and 0 NaN is not 0).  GT_K threads share a pixel, thread k adding
 // the entries k, k + GT_K, ...; their sums are added in order.  Bound by the
 // L2 reads of the tables (24 B per patch pixel).
 __global__ void __launch_bounds__(GT_THREADS) setup_sums_k(const Recon g, int first_tile) {
@@ -468,20 +470,22 @@ __global__ void __launch_bounds__(GT_THREADS) setup_sums_k(const Recon g, int fi
   for (int i0 = part; i0 < ti.y; i0 += U * GT_K) {
     double om[U];
     float2 d[U], w[U];
+    bool in[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int i = i0 + k * GT_K;
       const int2 e = list[i < ti.y ? i : ti.y - 1];
       const unsigned rr = (unsigned)(lr - (e.y >> 16)), cc = (unsigned)(lc - (int)(short)e.y);
-      const bool in = rr < (unsigned)np && cc < (unsigned)np && i < ti.y;
-      const unsigned o = in ? rr * np + cc : 0u;
-      om[k] = in ? g.omega64[o] : 0.0;
+      in[k] = rr < (unsigned)np && cc < (unsigned)np && i < ti.y;
+      const unsigned o = in[k] ? rr * np + cc : 0u;
+      om[k] = in[k] ? g.omega64[o] : 0.0;
       d[k] = g.d[o];
-      w[k] = in ? g.gw[o] : make_float2(0.f, 0.f);
+      w[k] = in[k] ? g.gw[o] : make_float2(0.f, 0.f);
     }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const float2 u = start_state(g, d[k], x);
+      float2 u = start_state(g, d[k], x);
+      if (!in[k]) u = make_float2(0.f, 0.f);
       acc += om[k];
       ax = fmaf(w[k].x, u.x, fmaf(-w[k].y, u.y, ax));
       ay = fmaf(w[k].x, u.y, fmaf(w[k].y, u.x, ay));
@@ -528,7 +532,7 @@ __global__ void __launch_bounds__(256) setup_images_k(const Recon g, Recon* rec,
 }
 
 hipError_t launch_setup_inputs(const Recon& h, const SetupInputs& in, int* fitem, hipStream_t st) {
-  const int np2 = h.np * h.np, per = (np2 + 255) / 256;
+  const int np2 = h.np * h.np;
   hipLaunchKernelGGL(setup_clear_k, dim3(1), dim3(256), 0, st, h, fitem);
   hipLaunchKernelGGL(setup_tables_k, dim3(blocks_for(np2 > h.J ? np2 : h.J, 256)), dim3(256), 0, st, h, in.probe,
                      in.pos, in.kappa, in.rho, in.split_allowed);
