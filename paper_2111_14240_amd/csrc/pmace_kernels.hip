@@ -867,8 +867,9 @@ __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int 
   const int2* list = g.tile_list + ti.x;
   float ax = 0.f, ay = 0.f;
   // U entries at a time, all their loads ahead of the sums; the last group is
-  // filled up with its last entry at weight zero (left to a remainder loop, up
-  // to U - 1 entries were loaded one after the other)
+  // filled up at weight zero (left to a remainder loop, up to U - 1 entries
+  // were loaded one after the other) with a finite value, the first twiddle: a
+  // state's element may be NaN, and 0 NaN is not 0
   for (int i0 = part; i0 < ti.y; i0 += U * GT_K) {
     float2 u[U], w[U];
 #pragma unroll
@@ -879,7 +880,8 @@ __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int 
       const bool in = rr < (unsigned)NP && cc < (unsigned)NP && i < ti.y;
       // lanes outside the patch read its first pixel and discard it
       const unsigned o = in ? rr * NP + cc : 0u;
-      u[k] = src[(size_t)(e.x - jb) * NP * NP + o];
+      const float2* patch = i < ti.y ? src + (size_t)(e.x - jb) * NP * NP : g.twn;
+      u[k] = patch[o];
       if constexpr (METHOD == kPMACE) w[k] = in ? g.gw[o] : make_float2(0.f, 0.f);
       else if (!in) u[k] = make_float2(0.f, 0.f);
     }

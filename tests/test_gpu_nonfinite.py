@@ -1,7 +1,10 @@
 """NaN and Inf that take no part in a result must not reach it.
 
 * a starting object whose unscanned pixels are NaN or Inf: only its covered
-  pixels are read, so the run equals, bit for bit, the one with zeros there."""
+  pixels are read, so the run equals, bit for bit, the one with zeros there;
+* a state with a NaN in its first element: of the patch's other pixels, none
+  reads that element (the gather's last group of list entries is filled up,
+  and what fills it must not be read from a patch)."""
 import numpy as np
 import pytest
 
@@ -53,3 +56,27 @@ def test_unscanned_start_pixels_are_not_read(P, np_, agent, chunk, bad):
         R.close()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
     assert np.isfinite(got[1][1]).all()
+
+
+@pytest.mark.parametrize("np_,chunk,J", [(32, 0, 1), (32, 0, 5), (48, 0, 8), (64, 0, 9), (128, 0, 7), (160, 3, 7)])
+def test_first_element_of_a_state_stays_its_own(P, np_, chunk, J):
+    n1, n2 = np_ + 40, np_ + 90
+    rng = np.random.default_rng(J)
+    pos = np.stack([rng.integers(0, 41, J), rng.integers(0, 91, J)], 1).astype(np.int32)
+    d, z, x0 = _inputs(n1, n2, np_, pos, 7 * np_)
+    print("[gpu-nonfinite] first element", np_, chunk, J, flush=True)
+    R = P.Reconstruction(n1, n2, d, pos, z, 0.5, flags=P.PMACE_STAGED_AGENT if np_ > 128 else 0, chunk=chunk)
+    v = np.stack([x0[r:r + np_, c:c + np_] for r, c in pos])
+    for j in range(J):
+        R.set_state(v)
+        ref = R.reconstruct().cpu().numpy()
+        w = v.copy()
+        w[j, 0, 0] = np.nan
+        R.set_state(w)
+        got = R.reconstruct().cpu().numpy()
+        r, c = pos[j]
+        own = np.zeros((n1, n2), bool)
+        own[r:r + np_, c:c + np_] = True
+        own[r, c] = False
+        assert np.array_equal(got[own], ref[own]), j
+    R.close()
