@@ -261,8 +261,9 @@ void pmace_batch_destroy(pmace_batch* batch);
  *   workspace_d >= pmace_simulate_footprint(np, num_pos) bytes (caller-owned);
  *   scale_out (host, may be NULL) receives peak_photons / max I (1 if
  *   noise-free): multiply the probe by sqrt(scale) to keep the object's units.
- * Synchronises.  A position whose patch leaves the object is found on the
- * device: EINVAL, and z_d's contents are then undefined. */
+ * Positions are validated on the device, before anything is written: EINVAL
+ * if a patch leaves the object, and z_d is then as it was.  Synchronises: with
+ * scale_out for the whole simulation, without it for the validation only. */
 size_t pmace_simulate_footprint(int32_t np, int32_t num_pos);
 pmace_status pmace_simulate(int32_t n1, int32_t n2, int32_t np, int32_t num_pos,
                             const void* probe_d, const int32_t* pos_d, const void* x_d,
@@ -278,7 +279,7 @@ pmace_status pmace_simulate(int32_t n1, int32_t n2, int32_t np, int32_t num_pos,
  * num_pos*np*np*8 <= pmace_simulate_static_max_bytes() (64 MiB - 256 B, e.g.
  * 127 positions of 256 x 256), else ENOMEM; np <= 128 has no such limit.
  * Positions are validated on the device (EINVAL if a patch leaves the
- * object; z_d's contents are then undefined).  Every call on one GPU shares that GPU's array: calls that overlap
+ * object; z_d is then as it was).  Every call on one GPU shares that GPU's array: calls that overlap
  * on one GPU (other streams, other threads) race; serialise them.
  * Synchronises hip_stream (the position check; and scale_out as in
  * pmace_simulate). */
