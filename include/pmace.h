@@ -18,7 +18,10 @@
  *     a non-finite state) surface at the next pmace_sync().
  *   - All persistent state lives in a caller-owned device workspace of
  *     pmace_footprint() bytes; the library never allocates device memory.
- *     It keeps a small host-side context (malloc) per reconstruction.
+ *     It keeps a small host-side context (malloc) per reconstruction, and
+ *     for the life of the process up to 2 MiB of pinned host memory that
+ *     calls read their figures back through (32 KiB for each thread that is in
+ *     such a call at a time; pmace_simulate_static uses none).
  *   - No C++ exception crosses this boundary; every call returns a status.
  *   - A context is not thread-safe; distinct contexts are.
  */

@@ -21,34 +21,30 @@ using pmace::Recon;
 
 namespace {
 std::mutex g_slots_mu;
-void* g_slots[pmace::kHostSlotsKept];
-size_t g_nslots = 0;
+void* g_slots[pmace::kHostSlots];   // the free ones
+size_t g_free_slots = 0, g_made_slots = 0;
 }  // namespace
 
 namespace pmace {
 void* take_host_slot() {
   {
     std::lock_guard<std::mutex> lk(g_slots_mu);
-    if (g_nslots > 0) return g_slots[--g_nslots];
+    if (g_free_slots > 0) return g_slots[--g_free_slots];
+    if (g_made_slots == kHostSlots) return nullptr;
+    ++g_made_slots;
   }
   void* p = nullptr;
-  if (hipHostMalloc(&p, kHostSlot, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  return p;
+  if (hipHostMalloc(&p, kHostSlot, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
+  (void)hipGetLastError();
+  std::lock_guard<std::mutex> lk(g_slots_mu);
+  --g_made_slots;
+  return nullptr;
 }
 
 void give_host_slot(void* slot) {
   if (!slot) return;
-  {
-    std::lock_guard<std::mutex> lk(g_slots_mu);
-    if (g_nslots < kHostSlotsKept) {
-      g_slots[g_nslots++] = slot;
-      return;
-    }
-  }
-  (void)hipHostFree(slot);
+  std::lock_guard<std::mutex> lk(g_slots_mu);
+  g_slots[g_free_slots++] = slot;
 }
 }  // namespace pmace
 
@@ -96,7 +92,6 @@ struct pmace_ctx {
   long long asked;                // iterations pmace_iterate has been asked for
   bool batched;                   // has been a batch member: its stop flag may be set
   pmace_status sticky;            // first asynchronous failure seen
-  void* slot;                     // pinned host memory for read-backs, or null
   unsigned long long resets;      // times the host cleared the stop flag
   // batches holding a copy of this context's descriptor (and its index there):
   // pmace_set_reference updates those copies too
@@ -105,7 +100,6 @@ struct pmace_ctx {
 
 struct pmace_batch {
   int n;
-  void* slot;                  // pinned host memory for read-backs, or null
   hipStream_t stream;
   std::vector<pmace_ctx*> ctxs;
   Recon* recs;                 // device: member descriptors
@@ -350,13 +344,13 @@ pmace_status record(pmace_ctx* c, pmace_status s) {
   return s;
 }
 
-// Waits for a figure that the last launch wrote to `host` (null: reads it back
-// from the device word it also left it in).
-pmace_status read_figure(pmace_ctx* c, const double* host, const double* dev, double* out) {
-  if (!host && hipMemcpyAsync(out, dev, 8, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+// Waits for a figure that the last launch wrote to the slot (none: reads it
+// back from the device word it also left it in).
+pmace_status read_figure(pmace_ctx* c, pmace::HostSlot& slot, const double* dev, double* out) {
+  if (!slot.p && hipMemcpyAsync(out, dev, 8, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
-  if (host) *out = *host;
+  if (!slot.wait(c->stream)) return record(c, PMACE_EDEVICE);
+  if (slot.p) *out = *static_cast<const double*>(slot.p);
   return PMACE_OK;
 }
 
@@ -460,9 +454,7 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   c->asked = 0;
   c->batched = false;
   c->resets = 0;
-  c->slot = nullptr;
   if (hipGetDevice(&c->device) != hipSuccess) { delete c; return PMACE_EDEVICE; }
-  c->slot = pmace::take_host_slot();
   auto fail = [&](pmace_status e) {
     pmace_destroy(c);
     return e;
@@ -558,14 +550,15 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   if (pmace::launch_setup_inputs(h, in, c->fitem, st) != hipSuccess) return fail(PMACE_EDEVICE);
   const size_t back_bytes = kAlign + (size_t)J * 8;
   std::vector<int32_t> pageable;
-  int32_t* back = static_cast<int32_t*>(c->slot);
-  if (!back || back_bytes > pmace::kHostSlot) {
+  pmace::HostSlot slot(back_bytes);
+  int32_t* back = static_cast<int32_t*>(slot.p);
+  if (!back) {
     pageable.resize(back_bytes / 4);
     back = pageable.data();
   }
   const auto read_back = [&](size_t bytes) {
-    return hipMemcpyAsync(back, base + L.status, bytes, hipMemcpyDeviceToHost, st) == hipSuccess &&
-           hipStreamSynchronize(st) == hipSuccess;
+    if (slot.p) (void)slot.use<void>();
+    return hipMemcpyAsync(back, base + L.status, bytes, hipMemcpyDeviceToHost, st) == hipSuccess && slot.wait(st);
   };
   if (!read_back(back_bytes)) return fail(PMACE_EDEVICE);
   const int32_t* pos = back + kAlign / 4;
@@ -736,10 +729,11 @@ pmace_status pmace_nrmse(pmace_ctx* c, double* out) {
   if (!c) return PMACE_ESTATE;
   if (!out) return PMACE_EINVAL;
   if (!c->h.xref) return PMACE_ESTATE;
-  double* host = static_cast<double*>(c->slot);
-  if (pmace::launch_nrmse(c->dev, c->ritems, c->h.n_red, c->fitem, 1, 0, 0.f, 0, 0, host, c->stream) != hipSuccess)
+  pmace::HostSlot slot;
+  if (pmace::launch_nrmse(c->dev, c->ritems, c->h.n_red, c->fitem, 1, 0, 0.f, 0, 0, slot.use<double>(), c->stream) !=
+      hipSuccess)
     return record(c, PMACE_EDEVICE);
-  return read_figure(c, host, c->h.track + 1, out);
+  return read_figure(c, slot, c->h.track + 1, out);
 }
 
 pmace_status pmace_set_stream(pmace_ctx* c, void* hip_stream) {
@@ -755,19 +749,21 @@ pmace_status pmace_set_stream(pmace_ctx* c, void* hip_stream) {
 pmace_status pmace_data_fit(pmace_ctx* c, double* out) {
   if (!c) return PMACE_ESTATE;
   if (!out) return PMACE_EINVAL;
-  double* host = static_cast<double*>(c->slot);
+  pmace::HostSlot slot;
   if (pmace::launch_fit_member(c->h, c->dev, 0, c->stream) != hipSuccess ||
-      pmace::launch_fit_finish(c->dev, c->fitem, 1, 0, 0.f, 0, 0, host, c->stream) != hipSuccess)
+      pmace::launch_fit_finish(c->dev, c->fitem, 1, 0, 0.f, 0, 0, slot.use<double>(), c->stream) != hipSuccess)
     return record(c, PMACE_EDEVICE);
-  return read_figure(c, host, c->h.track + 6, out);
+  return read_figure(c, slot, c->h.track + 6, out);
 }
 
 pmace_status pmace_sync(pmace_ctx* c) {
   if (!c) return PMACE_ESTATE;
   unsigned word = 0;
-  unsigned* status = c->slot ? static_cast<unsigned*>(c->slot) : &word;
-  if (hipMemcpyAsync(status, c->h.status, 4, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-      hipStreamSynchronize(c->stream) != hipSuccess)
+  pmace::HostSlot slot;
+  const unsigned* status = slot.p ? static_cast<unsigned*>(slot.p) : &word;
+  if (hipMemcpyAsync(slot.p ? slot.use<void>() : &word, c->h.status, 4, hipMemcpyDeviceToHost, c->stream) !=
+          hipSuccess ||
+      !slot.wait(c->stream))
     return record(c, PMACE_EDEVICE);
   if (c->sticky != PMACE_OK) return c->sticky;
   if (*status & pmace::kStatusNonFinite) return record(c, PMACE_EDIVERGED);
@@ -787,7 +783,6 @@ void pmace_destroy(pmace_ctx* c) {
   for (const auto& hb : c->holders) batch_forget(hb.first, hb.second);
   (void)hipStreamSynchronize(c->stream);
   c->graph.release();
-  pmace::give_host_slot(c->slot);
   delete c;
 }
 
@@ -938,7 +933,6 @@ void batch_release(pmace_batch* b) {
     if (b->join[l]) (void)hipEventDestroy(b->join[l]);
   }
   if (b->fork) (void)hipEventDestroy(b->fork);
-  pmace::give_host_slot(b->slot);
   delete b;
 }
 
@@ -966,7 +960,6 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   pmace_batch* b = new (std::nothrow) pmace_batch();
   if (!b) return PMACE_ENOMEM;
   b->n = n;
-  b->slot = pmace::take_host_slot();
   b->stream = ctxs[0]->stream;
   b->ctxs.assign(ctxs, ctxs + n);
   b->rule = *rule;
@@ -1084,13 +1077,12 @@ pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, 
                                   double* data_fit) {
   if (!b) return PMACE_ESTATE;
   const size_t bytes = (size_t)b->n * sizeof(pmace::PollItem);
-  const bool pinned = b->slot && bytes <= pmace::kHostSlot;  // the kernel then writes there itself
-  std::vector<pmace::PollItem> pageable(pinned ? 0 : b->n);
-  const pmace::PollItem* got = pinned ? static_cast<pmace::PollItem*>(b->slot) : pageable.data();
-  if (pmace::launch_poll(b->recs, b->n, pinned ? static_cast<pmace::PollItem*>(b->slot) : b->polled, b->stream) !=
-          hipSuccess ||
-      (!pinned && hipMemcpyAsync(pageable.data(), b->polled, bytes, hipMemcpyDeviceToHost, b->stream) != hipSuccess) ||
-      hipStreamSynchronize(b->stream) != hipSuccess)
+  pmace::HostSlot slot(bytes);  // (the kernel writes there itself)
+  std::vector<pmace::PollItem> pageable(slot.p ? 0 : b->n);
+  const pmace::PollItem* got = slot.p ? static_cast<pmace::PollItem*>(slot.p) : pageable.data();
+  if (pmace::launch_poll(b->recs, b->n, slot.p ? slot.use<pmace::PollItem>() : b->polled, b->stream) != hipSuccess ||
+      (!slot.p && hipMemcpyAsync(pageable.data(), b->polled, bytes, hipMemcpyDeviceToHost, b->stream) != hipSuccess) ||
+      !slot.wait(b->stream))
     return PMACE_EDEVICE;
   bool changed = false;
   for (int i = 0; i < b->n; ++i)

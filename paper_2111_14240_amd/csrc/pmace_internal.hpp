@@ -8,15 +8,41 @@
 namespace pmace {
 
 // Pinned host memory for what a call reads back (device-mapped, usable from any
-// device): slots of kHostSlot bytes kept for reuse, at most kHostSlotsKept of
-// them while unused (2 MiB), handed out under a lock.  A small read-back through
-// pageable memory takes 22 us from the launch before it to the host, through a
-// slot 15, and written there by the kernel itself 11.  take() returns null if
-// the memory cannot be had; callers then read back through pageable memory.
+// device): slots of kHostSlot bytes, held by a call from its first launch that
+// writes there until it has waited, and handed out under a lock.  At most
+// kHostSlots are made (2 MiB; one for each thread that is in such a call), and
+// they stay until the process ends: none is freed next to work that has only
+// just ended.  A small read-back through pageable memory takes 22 us from the
+// launch before it to the host, through a slot 15, and written there by the
+// kernel itself 11.  take() returns null if there is none to be had; callers
+// then read back through pageable memory.
 constexpr size_t kHostSlot = 32768;
-constexpr size_t kHostSlotsKept = 64;
+constexpr size_t kHostSlots = 64;
 void* take_host_slot();
 void give_host_slot(void* slot);  // null: nothing
+
+// A call's slot.  A call that returns before it has waited for what it queued
+// (a failed wait) leaves the slot out for good: something may still write there.
+struct HostSlot {
+  void* p;
+  bool queued = false;
+  explicit HostSlot(size_t bytes = 8) : p(bytes <= kHostSlot ? take_host_slot() : nullptr) {}
+  HostSlot(const HostSlot&) = delete;
+  HostSlot& operator=(const HostSlot&) = delete;
+  ~HostSlot() {
+    if (!queued) give_host_slot(p);
+  }
+  // the address for a launch or copy that writes there
+  template <class T> T* use() {
+    queued = true;
+    return static_cast<T*>(p);
+  }
+  bool wait(hipStream_t st) {
+    if (hipStreamSynchronize(st) != hipSuccess) return false;
+    queued = false;
+    return true;
+  }
+};
 
 // Launch-shape parameters.  The defaults are overridden at build time by the
 // values the tuner picked (tuned.json beside the package, passed as -D flags).

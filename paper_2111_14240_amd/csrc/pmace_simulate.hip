@@ -523,19 +523,21 @@ inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Intensities, optional Poisson draws and the scale, into z_d; `fr` holds the
 // row transforms (Np > 128), `ctl` the maximum and the position flag, read back
-// through `host` (two words).  Waits for all of it where the scale is asked
+// through the slot, if it is one.  Waits for all of it where the scale is asked
 // for, else for the position check only.
 pmace_status run_simulation(int32_t n1, int32_t n2, int32_t np, int32_t num_pos, const void* probe_d,
                             const int32_t* pos_d, const void* x_d, double peak_photons, uint64_t seed,
-                            float* z_d, float2* fr, unsigned* ctl, unsigned* host, double* scale_out,
+                            float* z_d, float2* fr, unsigned* ctl, pmace::HostSlot& slot, double* scale_out,
                             hipStream_t st) {
   const long long total = (long long)num_pos * np * np;
   const float2* dd = reinterpret_cast<const float2*>(probe_d);
   const int2* pp = reinterpret_cast<const int2*>(pos_d);
   const float2* xx = reinterpret_cast<const float2*>(x_d);
+  unsigned words[2];
+  const unsigned* host = slot.p ? static_cast<unsigned*>(slot.p) : words;
   const auto read_ctl = [&] {
-    if (hipMemcpyAsync(host, ctl, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
+    if (hipMemcpyAsync(slot.p ? slot.use<void>() : words, ctl, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        !slot.wait(st))
       return PMACE_EDEVICE;
     return host[1] ? PMACE_EINVAL : PMACE_OK;
   };
@@ -612,12 +614,9 @@ pmace_status pmace_simulate(int32_t n1, int32_t n2, int32_t np, int32_t num_pos,
   char* base = reinterpret_cast<char*>(up256(reinterpret_cast<size_t>(workspace_d)));
   float2* fr = reinterpret_cast<float2*>(base);
   unsigned* ctl = reinterpret_cast<unsigned*>(base + up256((size_t)num_pos * np * np * 8));
-  unsigned words[2];
-  void* slot = pmace::take_host_slot();
-  const pmace_status s = run_simulation(n1, n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl,
-                                        slot ? static_cast<unsigned*>(slot) : words, scale_out, st);
-  pmace::give_host_slot(slot);
-  return s;
+  pmace::HostSlot slot;
+  return run_simulation(n1, n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl, slot, scale_out,
+                        st);
 }
 
 size_t pmace_simulate_static_max_bytes(void) { return pmace::kSimScratchBytes - 256; }
@@ -639,8 +638,8 @@ pmace_status pmace_simulate_static(int32_t n1, int32_t n2, int32_t np, int32_t n
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   unsigned* ctl = reinterpret_cast<unsigned*>(sp);  // [0] maximum bits, [1] position flag
   float2* fr = reinterpret_cast<float2*>(sp + 256);
-  unsigned words[2];   // (no pinned slot: this entry point allocates nothing at all)
-  return run_simulation(n1, n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl, words,
+  pmace::HostSlot none(pmace::kHostSlot + 1);   // (this entry point allocates nothing at all)
+  return run_simulation(n1, n2, np, num_pos, probe_d, pos_d, x_d, peak_photons, seed, z_d, fr, ctl, none,
                         scale_out, st);
 }
 

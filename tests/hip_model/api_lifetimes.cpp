@@ -1,0 +1,183 @@
+// The C ABI's host side on the model of HIP (see hip/hip_runtime.h): what it
+// keeps, hands out and releases over many contexts and batches.  Kernels are
+// stand-ins that leave what the host reads back; an NRMSE of (J mod 5 + 1)/k
+// after k iterations makes members stop at different times.
+#include "../../paper_2111_14240_amd/csrc/pmace_api.hip"
+
+#include <thread>
+
+namespace pmace {
+static double figure(const Recon& r, double k) { return (r.J % 5 + 1) / (k > 0 ? k : 1); }
+static void finish(const Recon* recs, const int* items, int nf, int update_stop, float tol, int min_iter, int max_iter,
+                   double* host, int word) {
+  for (int i = 0; i < nf; ++i) {
+    const Recon& r = recs[items[i]];
+    if (update_stop && *r.done) continue;
+    if (update_stop) r.track[3] += 1;
+    const double e = figure(r, r.track[3]), prev = r.track[word];
+    r.track[update_stop ? word : word == 4 ? 6 : word] = e;
+    if (host) *host = e;
+    if (update_stop && (r.track[3] >= max_iter || (r.track[3] >= min_iter && std::fabs(e - prev) < tol))) *r.done = 1;
+  }
+}
+int max_ppw(int np) { return np <= 64 ? 2 : np <= 128 ? 1 : 0; }
+int default_ppw(int) { return 1; }
+int cr_round(int) { return 16; }
+hipError_t launch_setup_inputs(const Recon& h, const SetupInputs& in, int* fitem, hipStream_t st) {
+  const Recon r = h;
+  const int2* pos = in.pos;
+  model::launch(st, [=] {
+    *r.status = 0;
+    *r.done = *fitem = 0;
+    r.track[3] = 0;
+    std::memcpy(r.pos, pos, r.J * sizeof(int2));
+  });
+  return hipSuccess;
+}
+hipError_t launch_setup_states(const Recon&, const SetupInputs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_setup_tables(const Recon& h, Recon* rec, int2*, const SetupChunk*, int, int, int, int, hipStream_t st) {
+  const Recon r = h;
+  model::launch(st, [=] { *rec = r; });
+  return hipSuccess;
+}
+static hipError_t nothing(hipStream_t st) { return model::launch(st, [] {}), hipSuccess; }
+hipError_t launch_small_iteration(int, const Recon&, int, hipStream_t st) { return nothing(st); }
+hipError_t launch_small_batch(int, const Recon*, const int2*, int, const int2*, int, int, bool, hipStream_t st) {
+  return nothing(st);
+}
+hipError_t launch_large_iteration(const Recon&, const Recon*, const int2*, const int2*, hipStream_t st) {
+  return nothing(st);
+}
+hipError_t launch_get_state(const Recon&, const Recon*, float2*, hipStream_t st) { return nothing(st); }
+hipError_t launch_set_state(const Recon&, const Recon*, const float2*, const int2*, hipStream_t st) { return nothing(st); }
+hipError_t launch_nrmse(const Recon* recs, const int2*, int, const int* fitems, int nf, int update_stop, float tol,
+                        int min_iter, int max_iter, double* host, hipStream_t st) {
+  model::launch(st, [=] { finish(recs, fitems, nf, update_stop, tol, min_iter, max_iter, host, 1); });
+  return hipSuccess;
+}
+hipError_t launch_fit_member(const Recon&, const Recon*, int, hipStream_t st) { return nothing(st); }
+hipError_t launch_fit_batch(int, const Recon*, const int2*, int, hipStream_t st) { return nothing(st); }
+hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int update_stop, float tol, int min_iter,
+                             int max_iter, double* host, hipStream_t st) {
+  model::launch(st, [=] { finish(recs, fitems, nf, update_stop, tol, min_iter, max_iter, host, 4); });
+  return hipSuccess;
+}
+hipError_t launch_tick(const Recon* recs, int n, int max_iter, hipStream_t st) {
+  model::launch(st, [=] {
+    for (int i = 0; i < n; ++i)
+      if (!*recs[i].done && ++recs[i].track[3] >= max_iter) *recs[i].done = 1;
+  });
+  return hipSuccess;
+}
+hipError_t launch_poll(const Recon* recs, int n, PollItem* out, hipStream_t st) {
+  model::launch(st, [=] {
+    for (int i = 0; i < n; ++i) out[i] = {recs[i].track[1], recs[i].track[3], recs[i].track[4], *recs[i].done, 0};
+  });
+  return hipSuccess;
+}
+hipError_t launch_fft2(int, int, const float2*, float2*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_split_iteration(const Recon&, int, hipStream_t st) { return nothing(st); }
+}  // namespace pmace
+
+#define CHECK(x) \
+  if (!(x)) model::fault(std::string("line ") + std::to_string(__LINE__) + ": " #x)
+
+struct Rec {  // a small reconstruction: np, J
+  std::vector<char> ws;
+  pmace_ctx* c = nullptr;
+  int J;
+  Rec(int np, int J, hipStream_t st = nullptr) : J(J) {
+    pmace_params p{};
+    p.n1 = p.n2 = np + 8;
+    p.np = np;
+    p.num_pos = J;
+    p.alpha = 0.5f;
+    p.kappa = 1.25f;
+    p.rho = 0.5f;
+    ws.resize(pmace_footprint(&p));
+    CHECK(!ws.empty());
+    std::vector<int> pos(2 * J);
+    for (int j = 0; j < J; ++j) pos[2 * j] = pos[2 * j + 1] = j % 9;
+    std::vector<float> any(16);
+    CHECK(pmace_init(&p, any.data(), pos.data(), any.data(), nullptr, ws.data(), ws.size(), st, &c) == PMACE_OK);
+    CHECK(pmace_set_reference(c, any.data(), nullptr) == PMACE_OK);  // never read by the stand-ins
+  }
+  ~Rec() { pmace_destroy(c); }
+  void figures() {
+    double e = -1, f = -1;
+    CHECK(pmace_nrmse(c, &e) == PMACE_OK && e == J % 5 + 1);
+    CHECK(pmace_data_fit(c, &f) == PMACE_OK && f == J % 5 + 1);
+    CHECK(pmace_sync(c) == PMACE_OK);
+  }
+};
+
+struct Bat {
+  std::vector<char> ws;
+  pmace_batch* b = nullptr;
+  int n;
+  std::vector<int> done, it;
+  std::vector<double> e;
+  Bat(const std::vector<Rec*>& rs, pmace_stop_rule rule) : n((int)rs.size()), done(n), it(n), e(n) {
+    std::vector<pmace_ctx*> cs;
+    for (auto* r : rs) cs.push_back(r->c);
+    ws.resize(pmace_batch_footprint(cs.data(), n));
+    CHECK(pmace_batch_create(cs.data(), n, &rule, ws.data(), ws.size(), &b) == PMACE_OK);
+  }
+  ~Bat() { pmace_batch_destroy(b); }
+  void step(int k) { CHECK(pmace_batch_step(b, k) == PMACE_OK); }
+  int poll() {
+    CHECK(pmace_batch_poll(b, done.data(), e.data(), it.data()) == PMACE_OK);
+    int k = 0;
+    for (int d : done) k += d != 0;
+    return k;
+  }
+};
+
+static const int kSides[] = {32, 64, 256, 48, 128, 160, 96, 256};
+
+// Read-back memory: more contexts and batches alive than it has slots, used by
+// several threads, and none to be had.
+static void slots() {
+  std::vector<Rec*> rs;
+  for (int i = 0; i < 100; ++i) rs.push_back(new Rec(kSides[i % 8], 1 + i % 7));
+  {
+    Bat a(rs, {1e-3f, 2, 50, PMACE_STOP_NRMSE, 1}), b({rs[3], rs[5]}, {1e-3f, 2, 50, PMACE_STOP_DATA_FIT, 2});
+    for (auto* r : rs) r->figures();
+    CHECK(a.poll() == 0 && b.poll() == 0);
+  }
+  for (auto* r : rs) delete r;
+  std::vector<std::thread> ts;
+  for (int t = 0; t < 6; ++t)
+    ts.emplace_back([t] {
+      hipStream_t st = nullptr;
+      CHECK(hipStreamCreateWithFlags(&st, 0) == hipSuccess);
+      for (int i = 0; i < 30; ++i) {
+        Rec r(kSides[(i + t) % 8], 2 + t, st);
+        r.figures();
+      }
+      CHECK(hipStreamDestroy(st) == hipSuccess);
+    });
+  for (auto& t : ts) t.join();
+  CHECK(model::host_frees == 0);
+  CHECK(model::host_mallocs <= (long)pmace::kHostSlots);
+  const long had = model::host_mallocs;
+  model::host_malloc_fails = true;
+  std::vector<void*> taken;
+  while (void* p = pmace::take_host_slot()) taken.push_back(p);
+  CHECK((long)taken.size() == had);
+  {
+    Rec r(64, 3), q(256, 4);
+    r.figures();
+    Bat b({&r, &q}, {0.f, 2, 3, PMACE_STOP_NRMSE, 1});
+    b.step(5);
+    CHECK(b.poll() == 2 && b.it[0] == 3 && b.it[1] == 3);
+  }
+  for (void* p : taken) pmace::give_host_slot(p);
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "slots") slots();
+  else return 2;
+  std::printf("ok\n");
+}
