@@ -232,10 +232,10 @@ def bench_batch(args):
 
 
 def batch_comparison(args):
-    """All reconstructions advanced together (one graph launch per iteration)
-    versus the plain solver (one at a time, in order), both to the same
-    on-device stop rule; alone and in the batch each member takes the same
-    iterations and ends at the same NRMSE (the path is deterministic)."""
+    """All reconstructions advanced together (merged launches) versus the plain
+    solver (one at a time, in order), both to the same on-device stop rule;
+    alone and in the batch each member takes the same iterations and ends at
+    the same NRMSE (the path is deterministic)."""
     import torch
     from paper_2111_14240_amd import pmace, synth
     t0 = time.perf_counter()

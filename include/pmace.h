@@ -201,11 +201,11 @@ pmace_status pmace_nrmse(pmace_ctx* ctx, double* out);
 pmace_status pmace_data_fit(pmace_ctx* ctx, double* out);
 
 /* Batches: several reconstructions on one device and stream advanced
- * together; from the third pmace_batch_step call on, one HIP graph launch per
- * iteration (a batch rebuilt every few steps, as in a serving loop, launches
- * eagerly instead of paying for capture).  Positions of members with
- * Np <= 128 share merged launches per patch size; Np > 128 members run as
- * parallel branches beside them.  Every iteration counts towards max_iter; after every
+ * together.  Positions of members with Np <= 128 share merged launches per
+ * patch size; Np > 128 members run as chains of their own on streams beside
+ * the batch's, which fork from it and join it within each pmace_batch_step.
+ * Up to eight sets of these streams (three each) are kept for later batches
+ * when a batch is destroyed.  Every iteration counts towards max_iter; after every
  * check_every-th iteration of the batch the stop rule is evaluated on the
  * device, and a member stops (its kernels return at once) when
  *   PMACE_STOP_NRMSE:    its NRMSE against its reference (set before
@@ -241,9 +241,8 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
 pmace_status pmace_batch_step(pmace_batch* batch, int32_t n_iter);
 /* Synchronise and read back per member: stop flag, last NRMSE, iterations
  * counted by the stop rule.  Host arrays of n entries; any may be NULL.
- * Np > 128 members found stopped are left out of the batch's later launches
- * (the graphs are captured again on the next step); a member whose stop flag
- * the host clears (pmace_iterate, pmace_set_reference) is launched again from
+ * Np > 128 members found stopped are left out of the batch's later launches;
+ * a member whose stop flag the host clears (pmace_iterate, pmace_set_reference) is launched again from
  * the next pmace_batch_step on.  Results are the same either way. */
 pmace_status pmace_batch_poll(pmace_batch* batch, int32_t* done, double* nrmse, int32_t* iters);
 /* As pmace_batch_poll, plus the last data-fit cost the stop rule evaluated

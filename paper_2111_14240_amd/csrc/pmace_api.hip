@@ -1,8 +1,8 @@
 // C ABI of libpmace.so (declared in include/pmace.h).
 //
 // Host responsibilities: argument validation, the workspace layout, the order
-// of the set-up (its tables and lists are built on the device), and replaying
-// iterations as HIP graphs (one per reconstruction, one per batch).
+// of the set-up (its tables and lists are built on the device), and launching
+// iterations (one reconstruction's, or a batch's on several streams).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -98,6 +98,17 @@ struct pmace_ctx {
   std::vector<std::pair<pmace_batch*, int>> holders;
 };
 
+// Streams beside a batch's own, with the events that fork and join them: three,
+// as a process has four hardware queues by default and a fourth would share
+// one with the batch's stream (a 4-iteration pass of 16 mixed members with 2
+// lanes 1782 us, 3 1712, 4 1826, 8 1819).
+constexpr int kLanes = 3;
+struct Lanes {
+  int device;
+  hipStream_t s[kLanes];
+  hipEvent_t fork, join[kLanes];
+};
+
 struct pmace_batch {
   int n;
   hipStream_t stream;
@@ -110,17 +121,18 @@ struct pmace_batch {
   int2* gitems[kClasses];      // device: gather items per class
   int ngitems[kClasses];
   int2* ritems;                // device: (member, block) NRMSE items
-  int nritems;
   int* fitems;                 // device: member indices
   pmace::PollItem* polled;     // device: what a poll reads of each member
   pmace_stop_rule rule;
-  hipStream_t lanes[4];
-  hipEvent_t fork, join[4];
-  Graph graph;                 // one iteration
-  Graph graph_check;           // one iteration + stop-rule evaluation
-  bool graph_tried;
+  // Members that run as chains of their own (Np > 128, or the split agent):
+  // indices, and each member's reduction items and entry of fitems; those of
+  // the other members (nsmall of them) come first in both.
+  std::vector<int> chains;
+  std::vector<int2> rspan;     // (first reduction item, count) per member
+  std::vector<int> fpos;       // its entry of fitems, per member
+  int nsmall, nsmall_ritems;
+  Lanes* lanes;                // where the chains run side by side, or null
   long long iters;             // iterations launched by this batch
-  int step_calls;              // pmace_batch_step calls so far
   // Np > 128 members a poll found stopped: their kernel chains are left out
   // of the launches (they would only read the flag and exit), until the host
   // clears the member's flag (pmace_iterate, pmace_set_reference), seen as a
@@ -850,66 +862,100 @@ pmace_status check_members(pmace_ctx* const* ctxs, int32_t n) {
   return PMACE_OK;
 }
 
-pmace_status enqueue_batch_iteration(pmace_batch* b, hipStream_t st, bool lanes, bool check) {
-  // Np > 128 members are independent chains of kernels spread over the lanes;
-  // they fork before the merged launches of the smaller members, so both run
-  // at once (the small ones are latency-bound and leave most CUs free)
-  bool any_large = false;
-  for (int i = 0; i < b->n; ++i) any_large = any_large || (own_chain(b->ctxs[i]) && !b->pruned[i]);
-  const bool forked = lanes && any_large;
-  if (forked) {
-    PM_HIP(hipEventRecord(b->fork, st));
-    for (int l = 0; l < 4; ++l) PM_HIP(hipStreamWaitEvent(b->lanes[l], b->fork, 0));
-  }
+// One iteration of the members that share merged launches, and the stop rule's
+// evaluation (check) or count.
+pmace_status enqueue_small_members(pmace_batch* b, hipStream_t st, bool check) {
+  const pmace_stop_rule& r = b->rule;
   for (int k = 0; k < kClasses; ++k)
     if (b->nitems[k] > 0)
       PM_HIP(pmace::launch_small_batch(kSmallNp[k], b->recs, b->items[k], b->nitems[k], b->gitems[k],
                                        b->ngitems[k], b->ppw[k], b->zeros[k], st));
-  int lane = 0;
-  for (int i = 0; i < b->n; ++i) {
-    pmace_ctx* c = b->ctxs[i];
-    if (!own_chain(c) || b->pruned[i]) continue;
-    hipStream_t ls = st;
-    if (forked) {
-      ls = b->lanes[lane];
-      lane = (lane + 1) % 4;
-    }
-    if (c->h.split)
-      PM_HIP(pmace::launch_split_iteration(c->h, 1, ls));
-    else
-      PM_HIP(pmace::launch_large_iteration(c->h, b->recs + i, c->chunk_tiles.data(), c->chunk_rows.data(), ls));
-  }
-  if (forked)
-    for (int l = 0; l < 4; ++l) {
-      PM_HIP(hipEventRecord(b->join[l], b->lanes[l]));
-      PM_HIP(hipStreamWaitEvent(st, b->join[l], 0));
-    }
-  if (check && b->rule.criterion == PMACE_STOP_NRMSE) {
-    PM_HIP(pmace::launch_nrmse(b->recs, b->ritems, b->nritems, b->fitems, b->n, 1, b->rule.tol,
-                               b->rule.min_iter, b->rule.max_iter, nullptr, st));
+  if (check && r.criterion == PMACE_STOP_NRMSE) {
+    PM_HIP(pmace::launch_nrmse(b->recs, b->ritems, b->nsmall_ritems, b->fitems, b->nsmall, 1, r.tol, r.min_iter,
+                               r.max_iter, nullptr, st));
   } else if (check) {
     for (int k = 0; k < kClasses; ++k)
       PM_HIP(pmace::launch_fit_batch(kSmallNp[k], b->recs, b->items[k], b->nitems[k], st));
-    for (int i = 0; i < b->n; ++i)
-      if (own_chain(b->ctxs[i]) && !b->pruned[i])
-        PM_HIP(pmace::launch_fit_member(b->ctxs[i]->h, b->recs + i, 1, st));
-    PM_HIP(pmace::launch_fit_finish(b->recs, b->fitems, b->n, 1, b->rule.tol, b->rule.min_iter, b->rule.max_iter,
-                                    nullptr, st));
+    PM_HIP(pmace::launch_fit_finish(b->recs, b->fitems, b->nsmall, 1, r.tol, r.min_iter, r.max_iter, nullptr, st));
   } else {
-    PM_HIP(pmace::launch_tick(b->recs, b->n, b->rule.max_iter, st));
+    PM_HIP(pmace::launch_tick(b->recs, b->fitems, b->nsmall, r.max_iter, st));
   }
   return PMACE_OK;
 }
 
-// The launches of the batch changed: the captured graphs are destroyed once
-// the launches of them in flight have finished, and captured again on the next
-// step.
-pmace_status drop_graphs(pmace_batch* b) {
-  if (hipStreamSynchronize(b->stream) != hipSuccess) return PMACE_EDEVICE;
-  b->graph.release();
-  b->graph_check.release();
-  b->graph_tried = false;
+// The same for member i, a chain of its own.
+pmace_status enqueue_chain(pmace_batch* b, int i, hipStream_t st, bool check) {
+  const pmace_ctx* c = b->ctxs[i];
+  const pmace_stop_rule& r = b->rule;
+  const int* fitem = b->fitems + b->fpos[i];
+  if (c->h.split)
+    PM_HIP(pmace::launch_split_iteration(c->h, 1, st));
+  else
+    PM_HIP(pmace::launch_large_iteration(c->h, b->recs + i, c->chunk_tiles.data(), c->chunk_rows.data(), st));
+  if (check && r.criterion == PMACE_STOP_NRMSE) {
+    PM_HIP(pmace::launch_nrmse(b->recs, b->ritems + b->rspan[i].x, b->rspan[i].y, fitem, 1, 1, r.tol, r.min_iter,
+                               r.max_iter, nullptr, st));
+  } else if (check) {
+    PM_HIP(pmace::launch_fit_member(c->h, b->recs + i, 1, st));
+    PM_HIP(pmace::launch_fit_finish(b->recs, fitem, 1, 1, r.tol, r.min_iter, r.max_iter, nullptr, st));
+  } else {
+    PM_HIP(pmace::launch_tick(b->recs, fitem, 1, r.max_iter, st));
+  }
   return PMACE_OK;
+}
+
+// Sets of lanes: a batch holds one while it lives, and what it gives back is
+// kept for the next, so that a server, which rebuilds its batch with every
+// admission, neither makes nor destroys streams each time.
+constexpr size_t kLaneSetsKept = 8;
+std::mutex g_lanes_mu;
+Lanes* g_lanes[kLaneSetsKept];
+size_t g_nlanes = 0;
+
+void destroy_lanes(Lanes* l) {
+  for (int k = 0; k < kLanes; ++k) {
+    if (l->s[k]) (void)hipStreamDestroy(l->s[k]);
+    if (l->join[k]) (void)hipEventDestroy(l->join[k]);
+  }
+  if (l->fork) (void)hipEventDestroy(l->fork);
+  delete l;
+}
+
+Lanes* take_lanes() {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_lanes_mu);
+    for (size_t i = g_nlanes; i-- > 0;)
+      if (g_lanes[i]->device == device) {
+        Lanes* l = g_lanes[i];
+        g_lanes[i] = g_lanes[--g_nlanes];
+        return l;
+      }
+  }
+  Lanes* l = new (std::nothrow) Lanes();
+  if (!l) return nullptr;
+  l->device = device;
+  bool ok = hipEventCreateWithFlags(&l->fork, hipEventDisableTiming) == hipSuccess;
+  for (int k = 0; k < kLanes && ok; ++k)
+    ok = hipStreamCreateWithFlags(&l->s[k], hipStreamNonBlocking) == hipSuccess &&
+         hipEventCreateWithFlags(&l->join[k], hipEventDisableTiming) == hipSuccess;
+  if (ok) return l;
+  destroy_lanes(l);
+  return nullptr;
+}
+
+// (Their work has been joined to a stream that has been waited for.)
+void give_lanes(Lanes* l) {
+  if (!l) return;
+  {
+    std::lock_guard<std::mutex> lk(g_lanes_mu);
+    if (g_nlanes < kLaneSetsKept) {
+      g_lanes[g_nlanes++] = l;
+      return;
+    }
+  }
+  destroy_lanes(l);
 }
 
 hipError_t batch_recs_update(pmace_batch* b, int i, const Recon& h, hipStream_t st) {
@@ -926,13 +972,7 @@ void batch_release(pmace_batch* b) {
       if (hs[k].first == b) hs.erase(hs.begin() + (long)k);
       else ++k;
   }
-  b->graph.release();
-  b->graph_check.release();
-  for (int l = 0; l < 4; ++l) {
-    if (b->lanes[l]) (void)hipStreamDestroy(b->lanes[l]);
-    if (b->join[l]) (void)hipEventDestroy(b->join[l]);
-  }
-  if (b->fork) (void)hipEventDestroy(b->fork);
+  give_lanes(b->lanes);
   delete b;
 }
 
@@ -964,38 +1004,43 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   b->ctxs.assign(ctxs, ctxs + n);
   b->rule = *rule;
   if (b->rule.check_every == 0) b->rule.check_every = 1;
-  b->graph_tried = false;
   b->iters = 0;
-  b->step_calls = 0;
   b->pruned.assign(n, 0);
   b->pruned_at.assign(n, 0);
   char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<size_t>(workspace_d)));
   b->recs = reinterpret_cast<Recon*>(base + L.recs);
   std::vector<Recon> recs(n);
   std::vector<int2> items[kClasses], gitems[kClasses], ritems;
-  std::vector<int> fitems(n);
+  std::vector<int> fitems;
   for (int i = 0; i < n; ++i) {
+    recs[i] = ctxs[i]->h;
+    if (own_chain(ctxs[i])) b->chains.push_back(i);
+    else fitems.push_back(i);
+  }
+  b->nsmall = (int)fitems.size();
+  fitems.insert(fitems.end(), b->chains.begin(), b->chains.end());
+  b->rspan.resize(n);
+  b->fpos.resize(n);
+  for (int f = 0; f < n; ++f) {
+    const int i = fitems[f];
     pmace_ctx* c = ctxs[i];
-    recs[i] = c->h;
-    fitems[i] = i;
+    b->fpos[i] = f;
+    b->rspan[i] = make_int2((int)ritems.size(), c->h.n_red);
     for (int r = 0; r < c->h.n_red; ++r) ritems.push_back(make_int2(i, r));
-    const int k = own_chain(c) ? -1 : class_of(c->prm.np);
-    if (k < 0) continue;
+    if (f >= b->nsmall) continue;
+    b->nsmall_ritems = (int)ritems.size();
+    const int k = class_of(c->prm.np);
     b->zeros[k] = b->zeros[k] || c->h.has_zero;
     if (items[k].empty()) b->ppw[k] = c->h.ppw;   // the class takes its first member's choice
     for (int j = 0; j < c->prm.num_pos; ++j) items[k].push_back(make_int2(i, j));
     for (int t = 0; t < c->ngitems; ++t) gitems[k].push_back(make_int2(i, t));
   }
-  for (int l = 0; l < 4; ++l) {
-    if (hipStreamCreateWithFlags(&b->lanes[l], hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&b->join[l], hipEventDisableTiming) != hipSuccess) {
+  if (b->chains.size() + (b->nsmall > 0) > 1) {   // else there is nothing to run side by side
+    b->lanes = take_lanes();
+    if (!b->lanes) {
       batch_release(b);
       return PMACE_EDEVICE;
     }
-  }
-  if (hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess) {
-    batch_release(b);
-    return PMACE_EDEVICE;
   }
   hipStream_t st = b->stream;
   bool ok = hipMemcpyAsync(b->recs, recs.data(), (size_t)n * sizeof(Recon), hipMemcpyHostToDevice,
@@ -1013,7 +1058,6 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
                                 hipMemcpyHostToDevice, st) == hipSuccess;
   }
   b->ritems = reinterpret_cast<int2*>(base + L.ritems);
-  b->nritems = (int)ritems.size();
   b->fitems = reinterpret_cast<int*>(base + L.fitems);
   b->polled = reinterpret_cast<pmace::PollItem*>(base + L.polled);
   ok = ok && hipMemcpyAsync(b->ritems, ritems.data(), ritems.size() * 8, hipMemcpyHostToDevice, st) ==
@@ -1036,41 +1080,34 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
 pmace_status pmace_batch_step(pmace_batch* b, int32_t n_iter) {
   if (!b) return PMACE_ESTATE;
   if (n_iter < 0) return PMACE_EINVAL;
-  const int every = b->rule.check_every;
   // a pruned member whose stop flag the host has cleared runs again
-  bool changed = false;
-  for (int i = 0; i < b->n; ++i)
-    if (b->pruned[i] && b->ctxs[i]->resets != b->pruned_at[i]) {
-      b->pruned[i] = 0;
-      changed = true;
-    }
-  if (changed && drop_graphs(b) != PMACE_OK) return PMACE_EDEVICE;
-  // A batch whose membership changes often (a serving loop rebuilds it on
-  // every admission and retirement) would spend more host time capturing and
-  // instantiating graphs than it saves, so the first kCaptureAfter calls
-  // launch eagerly and only a batch that lives longer is captured.
-  constexpr int kCaptureAfter = 2;
-  if (!b->graph_tried && graphs_enabled() && b->step_calls >= kCaptureAfter) {
-    b->graph_tried = true;
-    (void)capture(b->graph_check,
-                  [&](hipStream_t cs) { return enqueue_batch_iteration(b, cs, true, true); });
-    if (every > 1)
-      (void)capture(b->graph, [&](hipStream_t cs) { return enqueue_batch_iteration(b, cs, true, false); });
+  std::vector<int> run;
+  for (int i : b->chains) {
+    if (b->pruned[i] && b->ctxs[i]->resets != b->pruned_at[i]) b->pruned[i] = 0;
+    if (!b->pruned[i]) run.push_back(i);
   }
-  for (int k = 0; k < n_iter; ++k) {
-    // the stop rule is evaluated after every `every`-th iteration of the batch
-    const bool check = (b->iters + 1) % every == 0;
-    ++b->iters;
-    const Graph& g = check ? b->graph_check : b->graph;
-    if (g.x) {
-      if (hipGraphLaunch(g.x, b->stream) != hipSuccess) return PMACE_EDEVICE;
-    } else {
-      pmace_status s = enqueue_batch_iteration(b, b->stream, true, check);
-      if (s != PMACE_OK) return s;
-    }
+  // The chains depend on nothing but themselves, so they fork from the batch's
+  // stream once a call and join it at the end, and each evaluates its own stop
+  // rule (16 mixed members, a 4-iteration pass: 1712 us; with a fork and a join
+  // around every iteration, for one evaluation over all members, 1955, and
+  // those captured as a graph 1755).
+  int nl = 0;
+  if (b->lanes && n_iter > 0 && run.size() + (b->nsmall > 0) > 1) nl = (int)std::min(run.size(), (size_t)kLanes);
+  if (nl) PM_HIP(hipEventRecord(b->lanes->fork, b->stream));
+  for (int l = 0; l < nl; ++l) PM_HIP(hipStreamWaitEvent(b->lanes->s[l], b->lanes->fork, 0));
+  pmace_status s = PMACE_OK;
+  for (int k = 0; k < n_iter && s == PMACE_OK; ++k) {
+    // the stop rule is evaluated after every check_every-th iteration of the batch
+    const bool check = ++b->iters % b->rule.check_every == 0;
+    if (b->nsmall > 0) s = enqueue_small_members(b, b->stream, check);
+    for (size_t q = 0; q < run.size() && s == PMACE_OK; ++q)
+      s = enqueue_chain(b, run[q], nl ? b->lanes->s[q % nl] : b->stream, check);
   }
-  ++b->step_calls;
-  return PMACE_OK;
+  for (int l = 0; l < nl; ++l)   // also after a failed launch: what was queued is waited for with the stream
+    if (hipEventRecord(b->lanes->join[l], b->lanes->s[l]) != hipSuccess ||
+        hipStreamWaitEvent(b->stream, b->lanes->join[l], 0) != hipSuccess)
+      s = PMACE_EDEVICE;
+  return s;
 }
 
 pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, int32_t* iters,
@@ -1084,14 +1121,11 @@ pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, 
       (!slot.p && hipMemcpyAsync(pageable.data(), b->polled, bytes, hipMemcpyDeviceToHost, b->stream) != hipSuccess) ||
       !slot.wait(b->stream))
     return PMACE_EDEVICE;
-  bool changed = false;
-  for (int i = 0; i < b->n; ++i)
-    if (got[i].done && own_chain(b->ctxs[i]) && !b->pruned[i]) {
+  for (int i : b->chains)
+    if (got[i].done && !b->pruned[i]) {
       b->pruned[i] = 1;
       b->pruned_at[i] = b->ctxs[i]->resets;
-      changed = true;
     }
-  if (changed && drop_graphs(b) != PMACE_OK) return PMACE_EDEVICE;
   for (int i = 0; i < b->n; ++i) {
     if (done) done[i] = got[i].done;
     if (nrmse) nrmse[i] = got[i].nrmse;

@@ -270,9 +270,9 @@ hipError_t launch_fit_batch(int np, const Recon* recs, const int2* items, int ni
 // without, into track[6] only.  host as for launch_nrmse.
 hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int update_stop, float tol,
                              int min_iter, int max_iter, double* host, hipStream_t st);
-// Count one iteration for each running member (no stop-rule evaluation after
-// it), stopping those that reached max_iter.
-hipError_t launch_tick(const Recon* recs, int n, int max_iter, hipStream_t st);
+// Count one iteration for each running member of fitems (no stop-rule
+// evaluation after it), stopping those that reached max_iter.
+hipError_t launch_tick(const Recon* recs, const int* fitems, int nf, int max_iter, hipStream_t st);
 // A member's stop flag and figures, for all members of a batch into out[n].
 struct PollItem {
   double nrmse, iters, fit;

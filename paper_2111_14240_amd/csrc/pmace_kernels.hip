@@ -1389,10 +1389,10 @@ __global__ void __launch_bounds__(RED_T) fit_finish(const Recon* __restrict__ re
 
 // An iteration without an evaluation of the stop rule (the kernels that finish
 // an evaluation count theirs).
-__global__ void tick_k(const Recon* __restrict__ recs, int n, int max_iter) {
+__global__ void tick_k(const Recon* __restrict__ recs, const int* __restrict__ items, int n, int max_iter) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const Recon& g = recs[i];
+  const Recon& g = recs[items[i]];
   if (!*g.done) count_iteration(g, max_iter);
 }
 
@@ -2322,8 +2322,8 @@ hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int u
   return hipGetLastError();
 }
 
-hipError_t launch_tick(const Recon* recs, int n, int max_iter, hipStream_t st) {
-  hipLaunchKernelGGL(tick_k, dim3(blocks_for(n, 64)), dim3(64), 0, st, recs, n, max_iter);
+hipError_t launch_tick(const Recon* recs, const int* fitems, int nf, int max_iter, hipStream_t st) {
+  hipLaunchKernelGGL(tick_k, dim3(blocks_for(nf, 64)), dim3(64), 0, st, recs, fitems, nf, max_iter);
   return hipGetLastError();
 }
 

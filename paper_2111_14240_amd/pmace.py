@@ -529,8 +529,8 @@ class Reconstruction:
 
 
 class Batch:
-    """Several Reconstructions (same device and stream) advanced together: one
-    graph launch per iteration, NRMSE and the stop rule kept on the device."""
+    """Several Reconstructions (same device and stream) advanced together:
+    merged launches per patch size, NRMSE and the stop rule kept on the device."""
 
     def __init__(self, recons, tol=1e-4, min_iter=2, max_iter=500, workspace=None,
                  criterion=PMACE_STOP_NRMSE, check_every=1):

@@ -3,8 +3,8 @@
 Requests (one ptychography problem each) arrive over time.  The server keeps
 every admitted reconstruction's agent states resident on the GPU, admits new
 requests as soon as their workspace fits in the memory budget and a slot is
-free, advances all active reconstructions together (one batched graph launch
-per iteration, stop rule evaluated on the device), and retires each as soon as
+free, advances all active reconstructions together (merged launches, stop rule
+evaluated on the device), and retires each as soon as
 it has converged, copying its reconstruction back.  The same executor run with
 one request at a time, in arrival order, is the plain solver it is compared
 with.
@@ -239,10 +239,8 @@ class GPUExecutor:
 
     split_work: requests with at least this much work per iteration (patch
     pixels) are stepped in a batch and on a stream of their own, so the churn
-    of small requests (each admission or retirement rebuilds a batch, and a
-    rebuilt batch runs uncaptured for its first steps) leaves the large
-    requests' batch, and its captured graph, alone; the two batches advance
-    concurrently.  None: one batch for everything."""
+    of small requests (each admission or retirement rebuilds a batch) leaves
+    the large requests' batch alone; the two batches advance concurrently.  None: one batch for everything."""
 
     def __init__(self, alpha: float, kappa: float = 1.25, rho: float = 0.5, tol: float = 1e-4,
                  min_iter: int = 2, max_iter: int = 500, device="cuda", stream=None,

@@ -62,10 +62,12 @@ hipError_t launch_fit_finish(const Recon* recs, const int* fitems, int nf, int u
   model::launch(st, [=] { finish(recs, fitems, nf, update_stop, tol, min_iter, max_iter, host, 4); });
   return hipSuccess;
 }
-hipError_t launch_tick(const Recon* recs, int n, int max_iter, hipStream_t st) {
+hipError_t launch_tick(const Recon* recs, const int* items, int n, int max_iter, hipStream_t st) {
   model::launch(st, [=] {
-    for (int i = 0; i < n; ++i)
-      if (!*recs[i].done && ++recs[i].track[3] >= max_iter) *recs[i].done = 1;
+    for (int i = 0; i < n; ++i) {
+      const Recon& r = recs[items[i]];
+      if (!*r.done && ++r.track[3] >= max_iter) *r.done = 1;
+    }
   });
   return hipSuccess;
 }
@@ -126,7 +128,9 @@ struct Bat {
   ~Bat() { pmace_batch_destroy(b); }
   void step(int k) { CHECK(pmace_batch_step(b, k) == PMACE_OK); }
   int poll() {
+    const long before = model::destroys;
     CHECK(pmace_batch_poll(b, done.data(), e.data(), it.data()) == PMACE_OK);
+    CHECK(model::destroys == before);  // nothing is released next to work that has only just ended
     int k = 0;
     for (int d : done) k += d != 0;
     return k;
@@ -175,9 +179,66 @@ static void slots() {
   for (void* p : taken) pmace::give_host_slot(p);
 }
 
+// Batches: members that stop one after the other, are started again, polls
+// between; many batches one after the other, and several at a time.
+static void batches() {
+  for (int criterion : {PMACE_STOP_NRMSE, PMACE_STOP_DATA_FIT})
+    for (int every : {1, 3}) {
+      std::vector<Rec*> rs;
+      for (int i = 0; i < 64; ++i) rs.push_back(new Rec(kSides[i % 8], 1 + i % 7));
+      {
+        Bat b(rs, {0.02f, 2, 40, criterion, every});
+        int last = 0;
+        for (int k = 0; k < 12 && last < 64; ++k) {
+          b.step(4);
+          const int now = b.poll();
+          CHECK(now >= last);
+          last = now;
+        }
+        CHECK(last == 64);
+        for (int i = 0; i < 64; ++i) {
+          // |e_k - e_(k-1)| = c/(k (k - every)) < tol first, k a multiple of every
+          const double c = rs[i]->J % 5 + 1;
+          int k = every;
+          while (!(k >= 2 && k > every && c / (k - every) - c / k < 0.02 - 1e-12)) k += every;
+          CHECK(b.it[i] == k);
+        }
+        CHECK(pmace_set_reference(rs[2]->c, rs[2]->ws.data(), nullptr) == PMACE_OK);  // runs again
+        CHECK(pmace_iterate(rs[7]->c, 1) == PMACE_OK);
+        b.step(1);
+        CHECK(b.poll() <= 63 && !b.done[2] && b.it[2] == 1);
+      }
+      for (auto* r : rs) delete r;
+    }
+  const long made = model::streams_made;
+  for (int i = 0; i < 100; ++i) {
+    Rec a(256, 3), b(64, 2), c(160, 5);
+    Bat x({&a, &b, &c}, {0.f, 2, 9, PMACE_STOP_NRMSE, 1});
+    x.step(10);
+    CHECK(x.poll() == 3);
+  }
+  CHECK(model::streams_made - made <= 8);
+  {
+    std::vector<Rec*> rs;
+    std::vector<Bat*> bs;
+    for (int i = 0; i < 40; ++i) {
+      rs.push_back(new Rec(256, 3));
+      rs.push_back(new Rec(160, 4));
+      bs.push_back(new Bat({rs[2 * i], rs[2 * i + 1]}, {0.f, 2, 5, PMACE_STOP_NRMSE, 1}));
+      bs.back()->step(6);
+    }
+    for (auto* b : bs) CHECK(b->poll() == 2);
+    for (auto* b : bs) delete b;
+    for (auto* r : rs) delete r;
+  }
+  CHECK(model::streams_live <= 64);
+  CHECK(model::execs_live == 0);
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "slots") slots();
+  else if (what == "batches") batches();
   else return 2;
   std::printf("ok\n");
 }
