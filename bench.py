@@ -14,8 +14,10 @@ recurrence), with all inputs resident in HBM.  Prints one JSON line.
 from __future__ import annotations
 
 import argparse
+import faulthandler
 import json
 import os
+import subprocess
 import sys
 import time
 
@@ -460,6 +462,43 @@ def serve_comparison(args):
     return out
 
 
+def bench_systems(args):
+    """The batched and the served comparison, one JSON line each."""
+    b = batch_comparison(args)
+    out = {k: b[k] for k in ("batched", "plain", "speedup", "same_iterations", "same_nrmse", "iterations", "nrmse")}
+    out["workload"] = b["config"]["workload"]
+    print(json.dumps({"batched_vs_plain": out}), flush=True)
+    sargs = argparse.Namespace(**vars(args))
+    sargs.requests = args.serve_requests
+    sargs.rate = args.serve_rate
+    sv = serve_comparison(sargs)
+    keep = ("solves_per_s", "p50", "p99", "mean_latency", "completed", "max_active")
+    print(json.dumps({"served_vs_plain": {
+        "workload": sv["config"]["workload"], "policy": sv["config"]["policy"],
+        "served": {k: sv["served"].get(k) for k in keep},
+        "plain": {k: sv["plain"].get(k) for k in keep}}}), flush=True)
+
+
+def run_systems(limit_s=400):
+    """bench_systems in a child process with this one's arguments: whatever
+    becomes of it, the plain figures are printed, with its exit status in place
+    of a comparison that it did not print."""
+    cmd = [sys.executable, os.path.abspath(__file__), *sys.argv[1:], "--mode", "systems"]
+    out = {}
+    try:
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, text=True, timeout=limit_s)
+        text, status = r.stdout, f"exit status {r.returncode}"
+    except subprocess.TimeoutExpired as e:
+        text = e.stdout.decode() if isinstance(e.stdout, bytes) else e.stdout or ""
+        status = f"no end within {limit_s} s"
+    for line in text.splitlines():
+        if line.startswith("{"):
+            out.update(json.loads(line))
+    for key in ("batched_vs_plain", "served_vs_plain"):
+        out.setdefault(key, {"error": status})
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -490,7 +529,8 @@ def main():
                     help="plain mode with --systems: arrivals per second in the short served run")
     ap.add_argument("--copy-mib", type=int, default=0,
                     help="after the run, copy this many MiB three times (counter calibration)")
-    ap.add_argument("--mode", default="plain", choices=["plain", "batch", "serve", "simulate"])
+    ap.add_argument("--mode", default="plain", choices=["plain", "batch", "serve", "simulate", "systems"],
+                    help="systems: only the two comparisons that plain mode adds, one JSON line each")
     ap.add_argument("--items", type=int, default=64, help="batch mode: reconstructions")
     ap.add_argument("--requests", type=int, default=2000, help="serve mode: requests")
     ap.add_argument("--rate", type=float, default=20.0, help="serve mode: arrivals per second")
@@ -509,6 +549,7 @@ def main():
     ap.add_argument("--fit-tol", type=float, default=1e-3, help="relative data-fit change for --stop data_fit")
     ap.add_argument("--check-every", type=int, default=1, help="iterations between stop-rule evaluations")
     args = ap.parse_args()
+    faulthandler.enable()   # a fatal signal leaves a Python traceback on stderr
     if args.gpus != 1:
         print(json.dumps({"error": "this build runs on one GPU; --gpus must be 1",
                           "n_gpus": args.gpus}))
@@ -520,6 +561,8 @@ def main():
         return bench_serve(args)
     if args.mode == "simulate":
         return bench_simulate(args)
+    if args.mode == "systems":
+        return bench_systems(args)
 
     import torch
     from paper_2111_14240_amd import pmace, synth
@@ -621,20 +664,10 @@ def main():
         # the metric's second half: the mixed-size batch (64 reconstructions)
         # and a short served run, each against the plain one-at-a-time solver
         # on this GPU, to the same on-device stop rule
+        R.close()
         del R
         torch.cuda.empty_cache()
-        b = batch_comparison(args)
-        out["batched_vs_plain"] = {k: b[k] for k in ("batched", "plain", "speedup", "same_iterations",
-                                                     "same_nrmse", "iterations", "nrmse")}
-        out["batched_vs_plain"]["workload"] = b["config"]["workload"]
-        sargs = argparse.Namespace(**vars(args))
-        sargs.requests = args.serve_requests
-        sargs.rate = args.serve_rate
-        sv = serve_comparison(sargs)
-        keep = ("solves_per_s", "p50", "p99", "mean_latency", "completed", "max_active")
-        out["served_vs_plain"] = {"workload": sv["config"]["workload"], "policy": sv["config"]["policy"],
-                                  "served": {k: sv["served"].get(k) for k in keep},
-                                  "plain": {k: sv["plain"].get(k) for k in keep}}
+        out.update(run_systems())
     print(json.dumps(out), flush=True)
 
 

@@ -104,3 +104,26 @@ def test_traffic_table_lookup(tmp_path, monkeypatch):
     assert bench.measured_traffic("c3") == 6.5e9
     assert bench.measured_traffic("c2") is None          # measured on other sources
     assert bench.measured_traffic("c1") is None          # not measured
+
+
+@pytest.mark.parametrize("printed,rc,expect", [
+    ('{"batched_vs_plain": {"speedup": 2}}\n{"served_vs_plain": {"policy": "p"}}\n', 0,
+     {"batched_vs_plain": {"speedup": 2}, "served_vs_plain": {"policy": "p"}}),
+    ('{"batched_vs_plain": {"speedup": 2}}\n', -11,
+     {"batched_vs_plain": {"speedup": 2}, "served_vs_plain": {"error": "exit status -11"}}),
+    ("", 139, {"batched_vs_plain": {"error": "exit status 139"}, "served_vs_plain": {"error": "exit status 139"}}),
+])
+def test_comparisons_that_end_early_leave_their_status(monkeypatch, printed, rc, expect):
+    """The two comparisons run in a child process; what it printed before it
+    ended is kept, and its exit status stands for the rest."""
+    import bench
+    monkeypatch.setattr(sys, "argv", ["bench.py", "--steps", "5"])
+    seen = []
+
+    def run(cmd, **kw):
+        seen.append(cmd)
+        return subprocess.CompletedProcess(cmd, rc, stdout=printed)
+
+    monkeypatch.setattr(bench.subprocess, "run", run)
+    assert bench.run_systems() == expect
+    assert seen[0][2:] == ["--steps", "5", "--mode", "systems"]
