@@ -2,9 +2,9 @@
 
 * a starting object whose unscanned pixels are NaN or Inf: only its covered
   pixels are read, so the run equals, bit for bit, the one with zeros there;
-* a state with a NaN in its first element: of the patch's other pixels, none
-  reads that element (the gather's last group of list entries is filled up,
-  and what fills it must not be read from a patch)."""
+* a state with a NaN in its first element: no other pixel reads that element
+  (the gather's last group of list entries is filled up, and its lanes go over
+  pixels that an entry's patch does not cover)."""
 import numpy as np
 import pytest
 
@@ -74,9 +74,7 @@ def test_first_element_of_a_state_stays_its_own(P, np_, chunk, J):
         w[j, 0, 0] = np.nan
         R.set_state(w)
         got = R.reconstruct().cpu().numpy()
-        r, c = pos[j]
-        own = np.zeros((n1, n2), bool)
-        own[r:r + np_, c:c + np_] = True
-        own[r, c] = False
-        assert np.array_equal(got[own], ref[own]), j
+        others = np.ones((n1, n2), bool)
+        others[tuple(pos[j])] = False
+        assert np.array_equal(got[others], ref[others]), j
     R.close()
