@@ -301,6 +301,61 @@ void xcd_runs(std::vector<int4>& t, size_t first, size_t end) {
   for (size_t b = 0; b < 8 * q; ++b) t[first + b] = row[(b % 8) * q + b / 8];
 }
 
+// Which cells of a grid some of a set of rectangles meets: a difference in
+// both directions for each rectangle, summed up by close(), which returns how
+// many cells are met.
+struct Cover {
+  int nr, nc;
+  std::vector<int> d;
+  Cover(int r, int c) : nr(r), nc(c), d((size_t)(r + 1) * (c + 1), 0) {}
+  int& cell(int r, int c) { return d[(size_t)r * (nc + 1) + c]; }
+  void add(int r0, int r1, int c0, int c1) {  // inclusive
+    ++cell(r0, c0);
+    --cell(r0, c1 + 1);
+    --cell(r1 + 1, c0);
+    ++cell(r1 + 1, c1 + 1);
+  }
+  int close() {
+    int met = 0;
+    for (int r = 0; r < nr; ++r) {
+      int* row = &cell(r, 0);
+      const int* up = r > 0 ? row - (nc + 1) : row;
+      int run = 0;
+      for (int c = 0; c < nc; ++c) {
+        run += row[c];
+        row[c] = run + (r > 0 ? up[c] : 0);
+        met += row[c] > 0;
+      }
+    }
+    return met;
+  }
+  bool at(int r, int c) { return cell(r, c) > 0; }
+};
+// Share of empty gather tiles or row items from which they are left out (the
+// copy of the host's lists and its wait add some 30 us to a set-up).
+constexpr double kEmptyShare = 1.0 / 16.0;
+
+// The places of a chunk's gather tiles without those that list nothing, row by
+// row, ordered over the XCDs as setup_tiles_k orders whole rows.
+std::vector<int> tile_slots(Cover& tiles, bool xcd) {
+  std::vector<int> slots((size_t)tiles.nr * tiles.nc, -1);
+  int first = 0;
+  for (int r = 0; r < tiles.nr; ++r) {
+    int n = 0, k = 0;
+    for (int c = 0; c < tiles.nc; ++c) n += tiles.at(r, c);
+    const int q = n / 8;
+    for (int c = 0; c < tiles.nc; ++c) {
+      if (!tiles.at(r, c)) continue;
+      int slot = xcd && k < 8 * q ? (k % q) * 8 + k / q : k;
+      if (!xcd && n % 8 == 0) slot = (k + r) % n;
+      slots[(size_t)r * tiles.nc + c] = first + slot;
+      ++k;
+    }
+    first += n;
+  }
+  return slots;
+}
+
 Layout layout_of(const pmace_params& p) {
   Layout L;
   const size_t P = (size_t)p.num_pos * p.np * p.np;
@@ -624,9 +679,15 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   if (in.split_allowed && pmace::launch_setup_states(h, in, st) != hipSuccess) return fail(PMACE_EDEVICE);
 
   // The rows that each chunk covers give its gather tiles (GT_R x GT_C object
-  // pixels) and row items; their lists are built on the device.
+  // pixels) and row items; their lists are built on the device.  On a sparse
+  // or unordered scan many list no position: from kEmptyShare of a chunk's on
+  // they are left out here.  (64 positions of 64^2 on 4096^2: an iteration
+  // 152 us with all of them at work, 39 ending at once, 15.6 left out; 200 of
+  // 160^2, unordered on 2048 x 4096 in chunks of 25: 595, 510, 377.)
   const int tiles_c = (n2 + pmace::GT_C - 1) / pmace::GT_C, nseg = cr_segments(p);
-  std::vector<pmace::SetupChunk> chunks(nch);
+  std::vector<std::vector<int>> slots;  // until the copies of them have been waited for
+  std::vector<std::vector<int2>> rows;
+  size_t listed = 0;
   c->chunk_tiles.assign(nch, make_int2(0, 0));
   c->chunk_rows.assign(nch, make_int2(0, 0));
   int tile0 = 0, item0 = 0;
@@ -637,17 +698,51 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
       lo = std::min(lo, pos[2 * j]);
       hi = std::max(hi, pos[2 * j] + np);
     }
-    const int tiles_r = (hi - lo + pmace::GT_R - 1) / pmace::GT_R, nitems = h.rowspec ? (hi - lo) * nseg : 0;
-    chunks[g] = {ja, jb, lo, tiles_r, tile0, nitems, item0};
-    c->chunk_tiles[g] = make_int2(tile0, tiles_r * tiles_c);
+    const int tiles_r = (hi - lo + pmace::GT_R - 1) / pmace::GT_R;
+    int ntiles = tiles_r * tiles_c, nitems = h.rowspec ? (hi - lo) * nseg : 0;
+    pmace::SetupChunk k{ja, jb, lo, tiles_r, tile0, 0, 0, item0, nullptr, nullptr};
+    Cover tiles(tiles_r, tiles_c), segs(h.rowspec ? hi - lo : 0, nseg);
+    for (int j = ja; j < jb; ++j) {
+      const int r = pos[2 * j] - lo, cc = pos[2 * j + 1];
+      tiles.add(r / pmace::GT_R, (r + np - 1) / pmace::GT_R, cc / pmace::GT_C, (cc + np - 1) / pmace::GT_C);
+      if (h.rowspec) segs.add(r, r + np - 1, cc / pmace::CR_W, (cc + np - 1) / pmace::CR_W);
+    }
+    const int kept = tiles.close();
+    if (ntiles - kept >= kEmptyShare * ntiles) {
+      slots.push_back(tile_slots(tiles, np_large(np)));
+      k.slots = slots.back().data();
+      listed += slots.back().size() * sizeof(int);
+      ntiles = kept;
+    }
+    const int kept_items = segs.close();
+    if (nitems > 0 && nitems - kept_items >= kEmptyShare * nitems) {
+      rows.emplace_back();
+      rows.back().reserve(kept_items);
+      for (int sg = 0; sg < nseg; ++sg)
+        for (int r = 0; r < hi - lo; ++r)
+          if (segs.at(r, sg)) rows.back().push_back(make_int2(lo + r, sg * pmace::CR_W));
+      k.rows = rows.back().data();
+      listed += rows.back().size() * sizeof(int2);
+      nitems = kept_items;
+    }
+    k.ntiles = ntiles;
+    k.nitems = nitems;
+    if (pmace::launch_setup_lists(h, k, tiles_c, nseg, pmace::cr_round(np), st) != hipSuccess)
+      return fail(PMACE_EDEVICE);
+    if (listed > ((size_t)64 << 20)) {  // (many chunks of a huge object)
+      if (!slot.wait(st)) return fail(PMACE_EDEVICE);
+      slots.clear();
+      rows.clear();
+      listed = 0;
+    }
+    c->chunk_tiles[g] = make_int2(tile0, ntiles);
     c->chunk_rows[g] = make_int2(item0, nitems);
-    tile0 += tiles_r * tiles_c;
+    tile0 += ntiles;
     item0 += nitems;
   }
   c->ngitems = tile0;
-  if (pmace::launch_setup_tables(h, c->dev, c->ritems, chunks.data(), nch, tiles_c, nseg, pmace::cr_round(np),
-                                 st) != hipSuccess)
-    return fail(PMACE_EDEVICE);
+  if (pmace::launch_setup_images(h, c->dev, c->ritems, st) != hipSuccess) return fail(PMACE_EDEVICE);
+  if (listed > 0 && !slot.wait(st)) return fail(PMACE_EDEVICE);  // the lists above were still being read
   if (in.split_allowed) {  // the inputs were still being read
     if (!read_back(4)) return fail(PMACE_EDEVICE);
     if ((unsigned)back[0] & kBad) return fail(PMACE_EINVAL);

@@ -218,22 +218,25 @@ struct SetupInputs {
   int split_allowed, rowspec_allowed;
 };
 // A chunk of positions [ja, jb): the object rows [lo, lo + tiles_r GT_R) that
-// its patches cover, its first gather tile and its row items.
+// its patches cover, its gather tiles and its row items.
 struct SetupChunk {
-  int ja, jb, lo, tiles_r, tile0, nitems, item0;
+  int ja, jb, lo, tiles_r, tile0, ntiles, nitems, item0;
+  const int* slots;    // host: place of every tile of those rows (-1: lists nothing, left out),
+                       //   row by row; null: every tile is kept
+  const int2* rows;    // host: (object row, first column) of every item kept; null: all of them
 };
 
 // Kernel launchers (stream-ordered; return the hipError_t of the launches).
 // `rec` / `recs` are device addresses of Recon descriptors, `h` a host copy.
 // Set-up, in two groups (a host step between them reads the status word and
-// the positions): everything that reads the caller's arrays, then the
-// consensus lists, the normaliser and the images.  Where the split agent is
-// allowed, the amplitudes and states wait for the layout: launch_setup_states
-// between the two.
+// the positions): everything that reads the caller's arrays, then each chunk's
+// consensus lists and share of the normaliser, and the images.  Where the
+// split agent is allowed, the amplitudes and states wait for the layout:
+// launch_setup_states between the two.
 hipError_t launch_setup_inputs(const Recon& h, const SetupInputs& in, int* fitem, hipStream_t st);
 hipError_t launch_setup_states(const Recon& h, const SetupInputs& in, hipStream_t st);
-hipError_t launch_setup_tables(const Recon& h, Recon* rec, int2* ritems, const SetupChunk* chunks, int nch,
-                               int tiles_c, int nseg, int rn, hipStream_t st);
+hipError_t launch_setup_lists(const Recon& h, const SetupChunk& k, int tiles_c, int nseg, int rn, hipStream_t st);
+hipError_t launch_setup_images(const Recon& h, Recon* rec, int2* ritems, hipStream_t st);
 // Np <= 128, one reconstruction: fused agent over its J positions, then the
 // fused gather + image update over its ntiles tiles.
 hipError_t launch_small_iteration(int np, const Recon& h, int ntiles, hipStream_t st);

@@ -851,6 +851,11 @@ __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int 
   static_assert(NPX % 64 == 0, "a part is whole waves");
   const int pxl = tid % NPX, part = __builtin_amdgcn_readfirstlane(tid / NPX);
   const int4 ti = g.tiles[tile];
+  // no position: nothing to add (fused with the image update, the test cost the
+  // smallest scans more than the few such tiles, which update zeros to zeros)
+  if constexpr (!FUSE) {
+    if (ti.y == 0) return;
+  }
   const int lr = pxl / GT_C, lc = pxl % GT_C, R = ti.z + lr, C = ti.w + lc;
   // the pixel's thread (part 0) loads what it combines the sum with now, so
   // those loads overlap the list and state loads instead of following them
@@ -987,6 +992,7 @@ __global__ void __launch_bounds__(cr_threads<NP>()) consensus_rows(const Recon g
   __shared__ int pcol[RN];
   const int tid = threadIdx.x, rl = tid / A, p = tid % A;
   const int4 it = g.citems[first_item + blockIdx.x];  // (list start, count, object row, first column)
+  if (it.y == 0) return;   // no position: nothing to add, and the images stay what they are
   TwiddleFetch<NP, NT> twf;
   twf.fetch(g.twn, tid);
   // this row group's entry of a round, its patch row (in the order the

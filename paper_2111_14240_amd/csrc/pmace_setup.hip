@@ -280,10 +280,11 @@ __device__ __forceinline__ bool meets(int p, int np, int a, int w) { return p < 
 // stay in place), and the second read of an edge line shared by two tiles
 // hits its L2.  Without it (one launch, Np <= 128), rows of a multiple of 8
 // tiles are rotated by their number, or the short lists of the object's edge
-// columns would all be two XCDs' share.
+// columns would all be two XCDs' share.  `slots`: these places from the host,
+// without the tiles that list nothing (see SetupChunk).
 constexpr int kPanel = 1024;
 __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int jb, int lo, int tiles_c,
-                                                     int tile0, int xcd) {
+                                                     int tile0, int xcd, const int* __restrict__ slots) {
   __shared__ int lj[256], lr[256], lc[256], wsum[4];
   __shared__ int count[kPanel], at[kPanel];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -338,7 +339,9 @@ __global__ void __launch_bounds__(256) setup_tiles_k(const Recon g, int ja, int 
         at[t] = start;
         int slot = xcd && tc < 8 * q ? (tc % q) * 8 + tc / q : tc;
         if (!xcd && tiles_c % 8 == 0) slot = (tc + (int)blockIdx.x) % tiles_c;
-        g.tiles[(size_t)tile0 + (size_t)blockIdx.x * tiles_c + slot] = make_int4(start, n, row, tc * GT_C);
+        slot += (int)blockIdx.x * tiles_c;
+        if (slots) slot = slots[(size_t)blockIdx.x * tiles_c + tc];
+        if (slot >= 0) g.tiles[(size_t)tile0 + slot] = make_int4(start, n, row, tc * GT_C);
       }
       __syncthreads();
     }
@@ -376,9 +379,11 @@ __global__ void __launch_bounds__(256) setup_order_k(const Recon g, int ja, int 
 // segment, by patch row (so that a round of the row consensus shares few
 // weight rows), then each round of rn entries by patch column (so that the
 // entries covering a run of pixels are consecutive in it); ties in ascending
-// order.  The consensus sums each pixel in this order.
+// order.  The consensus sums each pixel in this order.  `rows`: the rows and
+// segments from the host, without those that list nothing (see SetupChunk).
 __global__ void __launch_bounds__(256) setup_row_items_k(const Recon g, int ja, int jb, int lo, int nitems,
-                                                         int nseg, int item0, int rn) {
+                                                         int nseg, int item0, int rn,
+                                                         const int2* __restrict__ rows) {
   const int lane = threadIdx.x & 63;
   const int item = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= nitems) return;
@@ -386,7 +391,15 @@ __global__ void __launch_bounds__(256) setup_row_items_k(const Recon g, int ja, 
   // alternated, and as workgroup b runs on XCD b mod 8 the long first ones all
   // fell to the even XCDs (960 positions of 192^2: consensus 162 -> 101 us)
   const int nrows = nitems / nseg;
-  const int row = lo + item % nrows, col = (item / nrows) * CR_W;
+  int row, col;
+  if (rows) {
+    const int2 rc = rows[item];
+    row = rc.x;
+    col = rc.y;
+  } else {
+    row = lo + item % nrows;
+    col = (item / nrows) * CR_W;
+  }
   __shared__ int4 pend[4][128];  // per wave: entries not yet written, in order
   int4* pw = pend[threadIdx.x >> 6];
   const auto covers = [&](const int4& e, int k) {
@@ -460,6 +473,7 @@ __global__ void __launch_bounds__(GT_THREADS) setup_sums_k(const Recon g, int fi
   const int tid = threadIdx.x, pxl = tid % NPX, np = g.np;
   const int part = __builtin_amdgcn_readfirstlane(tid / NPX);
   const int4 ti = g.tiles[first_tile + blockIdx.x];
+  if (ti.y == 0) return;
   const int lr = pxl / GT_C, lc = pxl % GT_C, R = ti.z + lr, C = ti.w + lc;
   const bool inside = R < g.n1 && C < g.n2;
   const size_t px = inside ? (size_t)R * g.n2 + C : 0;
@@ -570,19 +584,32 @@ hipError_t launch_setup_states(const Recon& h, const SetupInputs& in, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_setup_tables(const Recon& h, Recon* rec, int2* ritems, const SetupChunk* chunks, int nch,
-                               int tiles_c, int nseg, int rn, hipStream_t st) {
-  for (int c = 0; c < nch; ++c) {
-    const SetupChunk& k = chunks[c];
-    hipLaunchKernelGGL(setup_tiles_k, dim3(k.tiles_r, (tiles_c + kPanel - 1) / kPanel), dim3(256), 0, st, h,
-                       k.ja, k.jb, k.lo, tiles_c, k.tile0, h.np > 128 ? 1 : 0);
-    if (h.rowspec) {
-      hipLaunchKernelGGL(setup_order_k, dim3(blocks_for(k.jb - k.ja, 256)), dim3(256), 0, st, h, k.ja, k.jb);
-      hipLaunchKernelGGL(setup_row_items_k, dim3(blocks_for(k.nitems, 4)), dim3(256), 0, st, h, k.ja, k.jb,
-                         k.lo, k.nitems, nseg, k.item0, rn);
-    }
-    hipLaunchKernelGGL(setup_sums_k, dim3(k.tiles_r * tiles_c), dim3(GT_THREADS), 0, st, h, k.tile0);
+hipError_t launch_setup_lists(const Recon& h, const SetupChunk& k, int tiles_c, int nseg, int rn, hipStream_t st) {
+  // the host's lists go where the consensus image will be (4 B a tile and 8 B
+  // an item in 8 B a pixel)
+  const size_t all = (size_t)k.tiles_r * tiles_c;
+  int* slots = k.slots ? reinterpret_cast<int*>(h.xbar) : nullptr;
+  int2* rows = k.rows ? reinterpret_cast<int2*>(h.xbar) + (all + 1) / 2 : nullptr;
+  if (slots) {
+    const hipError_t e = hipMemcpyAsync(slots, k.slots, all * 4, hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) return e;
   }
+  if (rows) {
+    const hipError_t e = hipMemcpyAsync(rows, k.rows, (size_t)k.nitems * 8, hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(setup_tiles_k, dim3(k.tiles_r, (tiles_c + kPanel - 1) / kPanel), dim3(256), 0, st, h, k.ja,
+                     k.jb, k.lo, tiles_c, k.tile0, h.np > 128 ? 1 : 0, slots);
+  if (h.rowspec) {
+    hipLaunchKernelGGL(setup_order_k, dim3(blocks_for(k.jb - k.ja, 256)), dim3(256), 0, st, h, k.ja, k.jb);
+    hipLaunchKernelGGL(setup_row_items_k, dim3(blocks_for(k.nitems, 4)), dim3(256), 0, st, h, k.ja, k.jb, k.lo,
+                       k.nitems, nseg, k.item0, rn, rows);
+  }
+  hipLaunchKernelGGL(setup_sums_k, dim3(k.ntiles), dim3(GT_THREADS), 0, st, h, k.tile0);
+  return hipGetLastError();
+}
+
+hipError_t launch_setup_images(const Recon& h, Recon* rec, int2* ritems, hipStream_t st) {
   if (h.has_zero) {
     const int A = line_threads(h.np);
     hipLaunchKernelGGL(setup_zeros_k, dim3(blocks_for(h.np * A, 256)), dim3(256), 0, st, h, A);

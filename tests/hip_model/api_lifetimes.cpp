@@ -35,7 +35,20 @@ hipError_t launch_setup_inputs(const Recon& h, const SetupInputs& in, int* fitem
   return hipSuccess;
 }
 hipError_t launch_setup_states(const Recon&, const SetupInputs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_setup_tables(const Recon& h, Recon* rec, int2*, const SetupChunk*, int, int, int, int, hipStream_t st) {
+hipError_t launch_setup_lists(const Recon& h, const SetupChunk& k, int tiles_c, int, int, hipStream_t st) {
+  const Recon r = h;
+  const SetupChunk c = k;
+  model::launch(st, [=] {  // as the kernel: every place once
+    for (int t = 0; t < c.tiles_r * tiles_c; ++t) {
+      const int slot = c.slots ? c.slots[t] : t;
+      if (slot >= 0) r.tiles[c.tile0 + slot] = make_int4(0, 1, 0, 0);
+    }
+    for (int i = 0; i < c.nitems; ++i)
+      if (c.rows) r.citems[c.item0 + i] = make_int4(0, 1, c.rows[i].x, c.rows[i].y);
+  });
+  return hipSuccess;
+}
+hipError_t launch_setup_images(const Recon& h, Recon* rec, int2*, hipStream_t st) {
   const Recon r = h;
   model::launch(st, [=] { *rec = r; });
   return hipSuccess;
@@ -235,10 +248,82 @@ static void batches() {
   CHECK(model::execs_live == 0);
 }
 
+// The places of gather tiles without the empty ones, against a count of what
+// each rectangle meets: every kept tile has one place, in its row's range, and
+// a full row's are the kernel's own.
+static void cover() {
+  unsigned seed = 1;
+  const auto rnd = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+  for (int trial = 0; trial < 2000; ++trial) {
+    const int nr = 1 + rnd(6), nc = 1 + rnd(40), rects = rnd(8);
+    Cover c(nr, nc);
+    std::vector<int> ref(nr * nc, 0);
+    for (int k = 0; k < rects; ++k) {
+      const int r0 = rnd(nr), r1 = r0 + rnd(nr - r0), c0 = rnd(nc), c1 = c0 + rnd(nc - c0);
+      const bool all = rnd(6) == 0;  // a rectangle over everything
+      c.add(all ? 0 : r0, all ? nr - 1 : r1, all ? 0 : c0, all ? nc - 1 : c1);
+      for (int r = all ? 0 : r0; r <= (all ? nr - 1 : r1); ++r)
+        for (int q = all ? 0 : c0; q <= (all ? nc - 1 : c1); ++q) ++ref[r * nc + q];
+    }
+    int met = 0;
+    for (int v : ref) met += v > 0;
+    CHECK(c.close() == met);
+    for (bool xcd : {false, true}) {
+      const std::vector<int> slots = tile_slots(c, xcd);
+      std::vector<int> seen(met, 0);
+      int first = 0;
+      for (int r = 0; r < nr; ++r) {
+        int n = 0;
+        for (int q = 0; q < nc; ++q) n += ref[r * nc + q] > 0;
+        for (int q = 0; q < nc; ++q) {
+          const int s = slots[r * nc + q];
+          CHECK(c.at(r, q) == (ref[r * nc + q] > 0) && (s >= 0) == c.at(r, q));
+          if (s < 0) continue;
+          CHECK(s >= first && s < first + n && !seen[s]++);
+          if (n == nc && first == r * nc) {
+            const int e = nc / 8;
+            int own = xcd && q < 8 * e ? (q % e) * 8 + q / e : q;
+            if (!xcd && nc % 8 == 0) own = (q + r) % nc;
+            CHECK(s == r * nc + own);
+          }
+        }
+        first += n;
+      }
+    }
+  }
+  // through pmace_init, whose tables must hold the kept ones: sparse, and in chunks
+  for (int np : {32, 128, 160, 256})
+    for (int chunk : {0, 3}) {
+      pmace_params p{};
+      p.n1 = 700;
+      p.n2 = 2500;
+      p.np = np;
+      p.num_pos = 14;
+      p.alpha = 0.5f;
+      p.kappa = 1.25f;
+      p.rho = 0.5f;
+      p.chunk = chunk;
+      p.flags = np > 128 ? PMACE_ROWSPEC_AGENT : 0;
+      std::vector<char> ws(pmace_footprint(&p));
+      std::vector<int> pos(28);
+      for (int j = 0; j < 14; ++j) {
+        pos[2 * j] = rnd(700 - np + 1);
+        pos[2 * j + 1] = rnd(2500 - np + 1);
+      }
+      std::vector<float> any(16);
+      pmace_ctx* x = nullptr;
+      CHECK(pmace_init(&p, any.data(), pos.data(), any.data(), nullptr, ws.data(), ws.size(), nullptr, &x) == PMACE_OK);
+      CHECK(x->ngitems > 0 && x->ngitems < (int)max_tiles(p));
+      for (int t = 0; t < x->ngitems; ++t) CHECK(x->h.tiles[t].y == 1);
+      pmace_destroy(x);
+    }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "slots") slots();
   else if (what == "batches") batches();
+  else if (what == "cover") cover();
   else return 2;
   std::printf("ok\n");
 }

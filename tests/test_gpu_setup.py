@@ -77,6 +77,23 @@ def test_first_pass_matches_oracle(P, np_, n1, n2, J, chunk, where):
     R.close()
 
 
+SPARSE = [
+    # most gather tiles or row items list nothing, and are left out
+    (32, 600, 1100, 9, 0, "spread"),
+    (64, 1024, 1024, 2, 0, "corners"),
+    (96, 97, 4000, 3, 0, "spread"),         # rows of many tiles, few of them kept
+    (128, 900, 700, 5, 0, "spread"),
+    (160, 800, 2300, 12, 4, "spread"),      # chunks whose rows span the object
+    (192, 700, 2100, 8, 3, "corners"),      # segments without an item
+    (256, 1100, 600, 7, 2, "spread"),
+]
+
+
+@pytest.mark.parametrize("np_,n1,n2,J,chunk,where", SPARSE)
+def test_sparse_scans_match_oracle(P, np_, n1, n2, J, chunk, where):
+    test_first_pass_matches_oracle(P, np_, n1, n2, J, chunk, where)
+
+
 def test_captured_iterations_equal_launched_ones(P):
     """Np <= 64 replays a captured graph once 256 iterations have been asked
     for; the same number of iterations, launched in small calls, gives the
