@@ -457,6 +457,15 @@ pmace_status capture(Graph& g, F body) {
   return s;
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+__global__ void clear_flag_k(int* flag) { *flag = 0; }
+
 // Reset the stop flag and the NRMSE history of a reconstruction.
 __global__ void reset_tracking_k(int* done, double* track) {
   *done = 0;
@@ -756,7 +765,11 @@ pmace_status pmace_iterate(pmace_ctx* c, int32_t n_iter) {
   if (n_iter < 0) return PMACE_EINVAL;
   if (n_iter == 0) return PMACE_OK;
   // a stop flag left by a batch would make its kernels skip this reconstruction
-  if (c->batched && hipMemsetAsync(c->h.done, 0, 4, c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
+  // (a kernel, not a memset: a caller may be capturing this call)
+  if (c->batched) {
+    hipLaunchKernelGGL(clear_flag_k, dim3(1), dim3(1), 0, c->stream, c->h.done);
+    if (hipGetLastError() != hipSuccess) return record(c, PMACE_EDEVICE);
+  }
   ++c->resets;
   // Iterations are launched as they are: the host queues one in 8 to 12 us,
   // the shortest (36 positions of 32^2) runs in 10.  A graph of kGraphIters of
@@ -764,12 +777,12 @@ pmace_status pmace_iterate(pmace_ctx* c, int32_t n_iter) {
   // per iteration; np 96: 24.7 -> 24.5; np 256: nothing, and a graph of one
   // iteration is slower than its launches at every size), but costs 250 us to
   // capture, so it is made for Np <= 64 once kCaptureFrom iterations have been
-  // asked for.
+  // asked for.  Under a caller's capture there are launches only.
   constexpr int kGraphIters = 32;
   constexpr long long kCaptureFrom = 256;
   c->asked += n_iter;
-  if (!c->graph_tried && n_iter >= kGraphIters && c->asked >= kCaptureFrom && c->prm.np <= 64 &&
-      graphs_enabled()) {
+  const bool whole = n_iter >= kGraphIters && c->asked >= kCaptureFrom && c->prm.np <= 64 && !capturing(c->stream);
+  if (whole && !c->graph_tried && graphs_enabled()) {
     c->graph_tried = true;
     (void)capture(c->graph, [&](hipStream_t cs) {
       for (int i = 0; i < kGraphIters; ++i) {
@@ -780,7 +793,7 @@ pmace_status pmace_iterate(pmace_ctx* c, int32_t n_iter) {
     });
   }
   int k = 0;
-  if (c->graph.x)
+  if (whole && c->graph.x)
     for (; k + kGraphIters <= n_iter; k += kGraphIters)
       if (hipGraphLaunch(c->graph.x, c->stream) != hipSuccess) return record(c, PMACE_EDEVICE);
   for (; k < n_iter; ++k) {

@@ -319,11 +319,45 @@ static void cover() {
     }
 }
 
+// pmace_iterate under a caller's capture: launches only, whatever came before
+// (membership of a batch, a captured graph of its own).
+static void captured() {
+  for (int np : {64, 256}) {
+    hipStream_t st = nullptr;
+    CHECK(hipStreamCreateWithFlags(&st, 0) == hipSuccess);
+    {
+      Rec a(np, 3, st), b(160, 2, st);
+      {
+        Bat x({&a, &b}, {0.f, 2, 4, PMACE_STOP_NRMSE, 1});
+        x.step(5);
+        CHECK(x.poll() == 2);
+      }
+      for (int before : {0, 300}) {
+        CHECK(pmace_iterate(a.c, before) == PMACE_OK);
+        CHECK(pmace_sync(a.c) == PMACE_OK);
+        const long mine = model::graph_calls;
+        hipGraph_t g = nullptr;
+        CHECK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess);
+        CHECK(pmace_iterate(a.c, 40) == PMACE_OK);
+        CHECK(hipStreamEndCapture(st, &g) == hipSuccess);
+        CHECK(model::graph_calls == mine + 1);
+        CHECK(model::memsets_captured == 0);
+        CHECK((int)g->nodes.size() >= 40);
+        CHECK(hipGraphDestroy(g) == hipSuccess);
+        CHECK(pmace_sync(a.c) == PMACE_OK);
+      }
+      CHECK(pmace_iterate(a.c, 300) == PMACE_OK);
+    }
+    CHECK(hipStreamDestroy(st) == hipSuccess);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "slots") slots();
   else if (what == "batches") batches();
   else if (what == "cover") cover();
+  else if (what == "captured") captured();
   else return 2;
   std::printf("ok\n");
 }

@@ -107,3 +107,38 @@ def test_captured_iterations_equal_launched_ones(P):
         got.append((R.get_state().cpu().numpy(), R.reconstruct().cpu().numpy()))
         R.close()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("np_,before", [(64, 0), (64, 300), (256, 0)])
+def test_iterations_captured_by_the_caller(P, np_, before):
+    """iterate() recorded into a caller's graph, on a reconstruction that has
+    been in a batch and (before = 300) has a graph of its own: every replay,
+    with other calls between them, equals the same iterations launched."""
+    prob = synth.make_problem(2 * np_, np_, 3, np_ // 3, 1e5, 11)
+    stream = torch.cuda.Stream()
+    got = []
+    for capture in (False, True):
+        with torch.cuda.stream(stream):
+            R = P.Reconstruction(prob.n1, prob.n2, prob.probe, prob.pos, prob.z, 0.5, stream=stream)
+            B = P.Batch([R], tol=0.0, min_iter=0, max_iter=2)
+            B.step(3)
+            assert B.poll()[0].tolist() == [1]
+            B.close()
+            R.iterate(before)
+            R.sync()
+            graph = torch.cuda.CUDAGraph()
+            if capture:
+                print("[gpu-setup] caller's capture", np_, before, flush=True)
+                with torch.cuda.graph(graph, stream=stream):
+                    R.iterate(33)
+            out = []
+            for _ in range(3):
+                graph.replay() if capture else R.iterate(33)
+                R.sync()
+                out.append(R.reconstruct().cpu().numpy())
+                R.iterate(1)
+            out.append(R.get_state().cpu().numpy())
+            R.close()
+        got.append(out)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
