@@ -142,3 +142,19 @@ def test_iterations_captured_by_the_caller(P, np_, before):
         got.append(out)
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("np_", [48, 64])
+def test_captured_iterations_of_other_sides(P, np_):
+    """As test_captured_iterations_equal_launched_ones for the other sides that
+    are captured, against the kernels launched because a call is too short."""
+    prob = synth.make_problem(3 * np_, np_, 4, np_ // 2, 1e5, 5 + np_)
+    got = []
+    for calls in ([130, 131, 40], [31] * 9 + [22]):
+        R = P.Reconstruction(prob.n1, prob.n2, prob.probe, prob.pos, prob.z, 0.5)
+        for n in calls:
+            R.iterate(n)
+        R.sync()
+        got.append((R.get_state().cpu().numpy(), R.reconstruct().cpu().numpy()))
+        R.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
