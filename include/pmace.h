@@ -39,7 +39,7 @@ typedef enum {
   PMACE_OK = 0,
   PMACE_EINVAL = 1,        /* bad argument: size, range, NaN/Inf, negative intensity, position */
   PMACE_EUNSUPPORTED = 2,  /* valid per the paper but not built here (an Np without a transform here) */
-  PMACE_ENOMEM = 3,        /* workspace smaller than pmace_footprint() */
+  PMACE_ENOMEM = 3,        /* workspace smaller than pmace_footprint(), or no host memory */
   PMACE_EDEVICE = 4,       /* a HIP call failed (launch, copy, sync) */
   PMACE_ESTATE = 5,        /* call out of order (e.g. NULL or destroyed context) */
   PMACE_EDIVERGED = 6      /* the consensus image became non-finite */

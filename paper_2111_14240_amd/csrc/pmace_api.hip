@@ -130,6 +130,7 @@ struct pmace_batch {
   std::vector<int> chains;
   std::vector<int2> rspan;     // (first reduction item, count) per member
   std::vector<int> fpos;       // its entry of fitems, per member
+  std::vector<int> run;        // the chains launched by a call (room for all of them)
   int nsmall, nsmall_ritems;
   Lanes* lanes;                // where the chains run side by side, or null
   long long iters;             // iterations launched by this batch
@@ -507,7 +508,7 @@ size_t pmace_footprint(const pmace_params* p) {
 
 pmace_status pmace_init(const pmace_params* params, const void* probe_d, const int32_t* pos_d,
                         const float* intensity_d, const void* x0_d, void* workspace_d,
-                        size_t ws_bytes, void* hip_stream, pmace_ctx** out) {
+                        size_t ws_bytes, void* hip_stream, pmace_ctx** out) try {
   if (!out) return PMACE_EINVAL;
   *out = nullptr;
   pmace_status ps = check_params(params);
@@ -521,7 +522,20 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   const bool sharp = p.method == PMACE_METHOD_SHARP_PLUS;
   const double inv_np2 = 1.0 / ((double)np * np);
 
-  pmace_ctx* c = new (std::nothrow) pmace_ctx();
+  // What copies in flight may still read or write outlives the context, whose
+  // release waits for them.
+  const size_t back_bytes = kAlign + (size_t)J * 8;
+  pmace::HostSlot slot(back_bytes);
+  std::vector<int32_t> pageable;
+  std::vector<int4> qtiles;
+  std::vector<int> qlist;
+  std::vector<std::vector<int>> slots;
+  std::vector<std::vector<int2>> rows;
+  struct Guard {
+    pmace_ctx* c;
+    ~Guard() { pmace_destroy(c); }
+  } guard{new (std::nothrow) pmace_ctx()};
+  pmace_ctx* c = guard.c;
   if (!c) return PMACE_ENOMEM;
   c->prm = p;
   c->stream = st;
@@ -530,11 +544,7 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   c->asked = 0;
   c->batched = false;
   c->resets = 0;
-  if (hipGetDevice(&c->device) != hipSuccess) { delete c; return PMACE_EDEVICE; }
-  auto fail = [&](pmace_status e) {
-    pmace_destroy(c);
-    return e;
-  };
+  if (hipGetDevice(&c->device) != hipSuccess) return PMACE_EDEVICE;
 
   const Layout L = layout_of(p);
   char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<size_t>(workspace_d)));
@@ -623,10 +633,7 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   in.rho = (double)p.rho;
   in.split_allowed = split_allowed(p) ? 1 : 0;
   in.rowspec_allowed = rowspec_allowed(p) ? 1 : 0;
-  if (pmace::launch_setup_inputs(h, in, c->fitem, st) != hipSuccess) return fail(PMACE_EDEVICE);
-  const size_t back_bytes = kAlign + (size_t)J * 8;
-  std::vector<int32_t> pageable;
-  pmace::HostSlot slot(back_bytes);
+  if (pmace::launch_setup_inputs(h, in, c->fitem, st) != hipSuccess) return PMACE_EDEVICE;
   int32_t* back = static_cast<int32_t*>(slot.p);
   if (!back) {
     pageable.resize(back_bytes / 4);
@@ -636,11 +643,11 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
     if (slot.p) (void)slot.use<void>();
     return hipMemcpyAsync(back, base + L.status, bytes, hipMemcpyDeviceToHost, st) == hipSuccess && slot.wait(st);
   };
-  if (!read_back(back_bytes)) return fail(PMACE_EDEVICE);
+  if (!read_back(back_bytes)) return PMACE_EDEVICE;
   const int32_t* pos = back + kAlign / 4;
   constexpr unsigned kBad = pmace::kStatusBadIntensity | pmace::kStatusBadProbe | pmace::kStatusBadPosition;
   unsigned status = (unsigned)back[0];
-  if (status & kBad) return fail(PMACE_EINVAL);
+  if (status & kBad) return PMACE_EINVAL;
   h.has_zero = !sharp && (status & pmace::kStatusProbeZero) ? 1 : 0;
   h.split = in.split_allowed && !h.has_zero ? 1 : 0;
   h.rowspec = in.rowspec_allowed && !h.has_zero ? 1 : 0;
@@ -657,8 +664,6 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   // Split layout: the base tiles of its consensus, each with the positions
   // whose quadrant-0 block meets it in ascending order.
   const int M = np / 2;
-  std::vector<int4> qtiles;
-  std::vector<int> qlist;
   if (h.split) {
     const int qr = split_rows(p) / pmace::QT_R, qc = split_cols(p) / pmace::QT_C;
     std::vector<std::vector<int>> per_tile((size_t)qr * qc);
@@ -677,15 +682,15 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
       }
       xcd_runs(qtiles, row0, qtiles.size());
     }
-    if (qtiles.size() > split_tiles(p) || qlist.size() > split_list(p)) return fail(PMACE_EDEVICE);
+    if (qtiles.size() > split_tiles(p) || qlist.size() > split_list(p)) return PMACE_EDEVICE;
     h.nqt = (int)qtiles.size();
     if (hipMemcpyAsync(h.qtiles, qtiles.data(), qtiles.size() * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
         (!qlist.empty() &&
          hipMemcpyAsync(h.qlist, qlist.data(), qlist.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess))
-      return fail(PMACE_EDEVICE);
+      return PMACE_EDEVICE;
   }
   // (where the split agent is allowed the amplitudes and states had to wait)
-  if (in.split_allowed && pmace::launch_setup_states(h, in, st) != hipSuccess) return fail(PMACE_EDEVICE);
+  if (in.split_allowed && pmace::launch_setup_states(h, in, st) != hipSuccess) return PMACE_EDEVICE;
 
   // The rows that each chunk covers give its gather tiles (GT_R x GT_C object
   // pixels) and row items; their lists are built on the device.  On a sparse
@@ -694,9 +699,7 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
   // 152 us with all of them at work, 39 ending at once, 15.6 left out; 200 of
   // 160^2, unordered on 2048 x 4096 in chunks of 25: 595, 510, 377.)
   const int tiles_c = (n2 + pmace::GT_C - 1) / pmace::GT_C, nseg = cr_segments(p);
-  std::vector<std::vector<int>> slots;  // until the copies of them have been waited for
-  std::vector<std::vector<int2>> rows;
-  size_t listed = 0;
+  size_t listed = 0;   // bytes of slots and rows whose copies have not been waited for
   c->chunk_tiles.assign(nch, make_int2(0, 0));
   c->chunk_rows.assign(nch, make_int2(0, 0));
   int tile0 = 0, item0 = 0;
@@ -737,9 +740,9 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
     k.ntiles = ntiles;
     k.nitems = nitems;
     if (pmace::launch_setup_lists(h, k, tiles_c, nseg, pmace::cr_round(np), st) != hipSuccess)
-      return fail(PMACE_EDEVICE);
+      return PMACE_EDEVICE;
     if (listed > ((size_t)64 << 20)) {  // (many chunks of a huge object)
-      if (!slot.wait(st)) return fail(PMACE_EDEVICE);
+      if (!slot.wait(st)) return PMACE_EDEVICE;
       slots.clear();
       rows.clear();
       listed = 0;
@@ -750,14 +753,17 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
     item0 += nitems;
   }
   c->ngitems = tile0;
-  if (pmace::launch_setup_images(h, c->dev, c->ritems, st) != hipSuccess) return fail(PMACE_EDEVICE);
-  if (listed > 0 && !slot.wait(st)) return fail(PMACE_EDEVICE);  // the lists above were still being read
+  if (pmace::launch_setup_images(h, c->dev, c->ritems, st) != hipSuccess) return PMACE_EDEVICE;
+  if (listed > 0 && !slot.wait(st)) return PMACE_EDEVICE;  // the lists above were still being read
   if (in.split_allowed) {  // the inputs were still being read
-    if (!read_back(4)) return fail(PMACE_EDEVICE);
-    if ((unsigned)back[0] & kBad) return fail(PMACE_EINVAL);
+    if (!read_back(4)) return PMACE_EDEVICE;
+    if ((unsigned)back[0] & kBad) return PMACE_EINVAL;
   }
+  guard.c = nullptr;
   *out = c;
   return PMACE_OK;
+} catch (...) {  // host memory for the lists
+  return PMACE_ENOMEM;
 }
 
 pmace_status pmace_iterate(pmace_ctx* c, int32_t n_iter) {
@@ -1094,7 +1100,7 @@ size_t pmace_batch_footprint(pmace_ctx* const* ctxs, int32_t n) {
 }
 
 pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_stop_rule* rule,
-                                void* workspace_d, size_t ws_bytes, pmace_batch** out) {
+                                void* workspace_d, size_t ws_bytes, pmace_batch** out) try {
   if (!out) return PMACE_EINVAL;
   *out = nullptr;
   pmace_status ps = check_members(ctxs, n);
@@ -1105,7 +1111,14 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
     return PMACE_EINVAL;
   const BatchLayout L = batch_layout(ctxs, n);
   if (ws_bytes < L.total + kAlign) return PMACE_ENOMEM;
-  pmace_batch* b = new (std::nothrow) pmace_batch();
+  std::vector<Recon> recs(n);
+  std::vector<int2> items[kClasses], gitems[kClasses], ritems;
+  std::vector<int> fitems;
+  struct Guard {
+    pmace_batch* b;
+    ~Guard() { pmace_batch_destroy(b); }
+  } guard{new (std::nothrow) pmace_batch()};
+  pmace_batch* b = guard.b;
   if (!b) return PMACE_ENOMEM;
   b->n = n;
   b->stream = ctxs[0]->stream;
@@ -1117,9 +1130,6 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   b->pruned_at.assign(n, 0);
   char* base = reinterpret_cast<char*>(align_up(reinterpret_cast<size_t>(workspace_d)));
   b->recs = reinterpret_cast<Recon*>(base + L.recs);
-  std::vector<Recon> recs(n);
-  std::vector<int2> items[kClasses], gitems[kClasses], ritems;
-  std::vector<int> fitems;
   for (int i = 0; i < n; ++i) {
     recs[i] = ctxs[i]->h;
     if (own_chain(ctxs[i])) b->chains.push_back(i);
@@ -1127,6 +1137,7 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   }
   b->nsmall = (int)fitems.size();
   fitems.insert(fitems.end(), b->chains.begin(), b->chains.end());
+  b->run.reserve(b->chains.size());
   b->rspan.resize(n);
   b->fpos.resize(n);
   for (int f = 0; f < n; ++f) {
@@ -1145,10 +1156,7 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   }
   if (b->chains.size() + (b->nsmall > 0) > 1) {   // else there is nothing to run side by side
     b->lanes = take_lanes();
-    if (!b->lanes) {
-      batch_release(b);
-      return PMACE_EDEVICE;
-    }
+    if (!b->lanes) return PMACE_EDEVICE;
   }
   hipStream_t st = b->stream;
   bool ok = hipMemcpyAsync(b->recs, recs.data(), (size_t)n * sizeof(Recon), hipMemcpyHostToDevice,
@@ -1173,23 +1181,24 @@ pmace_status pmace_batch_create(pmace_ctx* const* ctxs, int32_t n, const pmace_s
   ok = ok && hipMemcpyAsync(b->fitems, fitems.data(), (size_t)n * 4, hipMemcpyHostToDevice, st) ==
                  hipSuccess;
   ok = ok && hipStreamSynchronize(st) == hipSuccess;
-  if (!ok) {
-    batch_release(b);
-    return PMACE_EDEVICE;
-  }
+  if (!ok) return PMACE_EDEVICE;
   for (int i = 0; i < n; ++i) {
     ctxs[i]->holders.emplace_back(b, i);
     ctxs[i]->batched = true;
   }
+  guard.b = nullptr;
   *out = b;
   return PMACE_OK;
+} catch (...) {  // host memory for the tables
+  return PMACE_ENOMEM;
 }
 
 pmace_status pmace_batch_step(pmace_batch* b, int32_t n_iter) {
   if (!b) return PMACE_ESTATE;
   if (n_iter < 0) return PMACE_EINVAL;
   // a pruned member whose stop flag the host has cleared runs again
-  std::vector<int> run;
+  std::vector<int>& run = b->run;
+  run.clear();
   for (int i : b->chains) {
     if (b->pruned[i] && b->ctxs[i]->resets != b->pruned_at[i]) b->pruned[i] = 0;
     if (!b->pruned[i]) run.push_back(i);
@@ -1219,7 +1228,7 @@ pmace_status pmace_batch_step(pmace_batch* b, int32_t n_iter) {
 }
 
 pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, int32_t* iters,
-                                  double* data_fit) {
+                                  double* data_fit) try {
   if (!b) return PMACE_ESTATE;
   const size_t bytes = (size_t)b->n * sizeof(pmace::PollItem);
   pmace::HostSlot slot(bytes);  // (the kernel writes there itself)
@@ -1241,6 +1250,8 @@ pmace_status pmace_batch_poll_fit(pmace_batch* b, int32_t* done, double* nrmse, 
     if (data_fit) data_fit[i] = got[i].fit;
   }
   return PMACE_OK;
+} catch (...) {  // host memory to read back through
+  return PMACE_ENOMEM;
 }
 
 pmace_status pmace_batch_poll(pmace_batch* b, int32_t* done, double* nrmse, int32_t* iters) {

@@ -4,7 +4,26 @@
 // after k iterations makes members stop at different times.
 #include "../../paper_2111_14240_amd/csrc/pmace_api.hip"
 
+#include <atomic>
 #include <thread>
+
+// Memory that runs out: the allocation from which on every one fails.
+static std::atomic<long> g_allocs_left{-1};
+static bool exhausted() {
+  long n = g_allocs_left.load();
+  if (n < 0 || model::inside > 0) return false;
+  if (n > 0) g_allocs_left = n - 1;
+  return n == 0;
+}
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return exhausted() ? nullptr : std::malloc(n ? n : 1); }
+void* operator new(size_t n) {
+  if (exhausted()) throw std::bad_alloc();
+  void* p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 namespace pmace {
 static double figure(const Recon& r, double k) { return (r.J % 5 + 1) / (k > 0 ? k : 1); }
@@ -352,12 +371,76 @@ static void captured() {
   }
 }
 
+// Host memory that runs out at any allocation of a call: ENOMEM, nothing left
+// behind, and the same call succeeds once there is memory.
+static void no_memory() {
+  const std::vector<float> any(64);
+  for (int np : {64, 160}) {
+    pmace_params p{};
+    p.n1 = 500;
+    p.n2 = 1900;
+    p.np = np;
+    p.num_pos = 5000;  // (more than a slot holds)
+    p.alpha = 0.5f;
+    p.kappa = 1.25f;
+    p.rho = 0.5f;
+    p.chunk = np > 128 ? 2000 : 0;
+    p.flags = np > 128 ? PMACE_ROWSPEC_AGENT : 0;
+    std::vector<char> ws(pmace_footprint(&p)), first;
+    std::vector<int> pos(2 * p.num_pos);
+    for (int j = 0; j < p.num_pos; ++j) {
+      pos[2 * j] = j % 200;
+      pos[2 * j + 1] = 7 * j % 300;  // the right of the object lists nothing
+    }
+    pmace_ctx* c[2] = {nullptr, nullptr};
+    for (int k = 0; k < 2; ++k) {
+      pmace_status s = PMACE_ENOMEM;
+      for (long n = 0; s != PMACE_OK; ++n) {
+        CHECK(n < 2000 && s == PMACE_ENOMEM && !c[k]);
+        g_allocs_left = n;
+        s = pmace_init(&p, any.data(), pos.data(), any.data(), nullptr, ws.data(), ws.size(), nullptr, &c[k]);
+        g_allocs_left = -1;
+      }
+      if (k == 0) {  // the first keeps its own
+        first.swap(ws);
+        ws.resize(first.size());
+      }
+    }
+    const pmace_stop_rule rule{0.f, 2, 4, PMACE_STOP_DATA_FIT, 1};
+    std::vector<char> bws(pmace_batch_footprint(c, 2));
+    pmace_batch* b = nullptr;
+    pmace_status s = PMACE_ENOMEM;
+    for (long n = 0; s != PMACE_OK; ++n) {
+      CHECK(n < 2000 && (s == PMACE_ENOMEM || s == PMACE_EDEVICE) && !b && c[0]->holders.empty() && c[1]->holders.empty());
+      g_allocs_left = n;
+      s = pmace_batch_create(c, 2, &rule, bws.data(), bws.size(), &b);
+      g_allocs_left = -1;
+    }
+    CHECK(pmace_batch_step(b, 5) == PMACE_OK);
+    model::host_malloc_fails = true;
+    std::vector<void*> taken;
+    while (void* q = pmace::take_host_slot()) taken.push_back(q);
+    int done[2];
+    g_allocs_left = 0;
+    s = pmace_batch_poll(b, done, nullptr, nullptr);
+    g_allocs_left = -1;
+    CHECK(s == PMACE_ENOMEM);
+    CHECK(pmace_batch_poll(b, done, nullptr, nullptr) == PMACE_OK && done[0] && done[1]);
+    for (void* q : taken) pmace::give_host_slot(q);
+    model::host_malloc_fails = false;
+    pmace_batch_destroy(b);
+    pmace_destroy(c[0]);
+    pmace_destroy(c[1]);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "slots") slots();
   else if (what == "batches") batches();
   else if (what == "cover") cover();
   else if (what == "captured") captured();
+  else if (what == "no_memory") no_memory();
   else return 2;
   std::printf("ok\n");
 }

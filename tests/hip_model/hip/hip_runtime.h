@@ -35,9 +35,16 @@ enum hipStreamCaptureMode { hipStreamCaptureModeThreadLocal };
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
 
 namespace model {
-// every call holds it: the model is one object to all threads
+// every call holds it: the model is one object to all threads (its own
+// allocations are not the tested code's)
 inline std::recursive_mutex mu;
-#define MODEL_LOCK std::lock_guard<std::recursive_mutex> model_lock_(model::mu)
+inline thread_local int inside = 0;
+struct Lock {
+  std::lock_guard<std::recursive_mutex> lk{mu};
+  Lock() { ++inside; }
+  ~Lock() { --inside; }
+};
+#define MODEL_LOCK model::Lock model_lock_
 [[noreturn]] inline void fault(const std::string& what) {
   std::fprintf(stderr, "model: %s\n", what.c_str());
   std::abort();
@@ -73,11 +80,11 @@ inline bool done(const Clock& c) {
   }
   return true;
 }
-inline void launch(Stream* st, std::function<void()> fn) {
+template <class F> void launch(Stream* st, F fn) {
   MODEL_LOCK;
   Stream* s = of(st);
   if (s->cap) {
-    s->cap->g->nodes.push_back(std::move(fn));
+    s->cap->g->nodes.push_back(fn);
     return;
   }
   ++s->after[s->id];

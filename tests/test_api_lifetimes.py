@@ -22,7 +22,7 @@ def model(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["slots", "batches", "cover", "captured"])
+@pytest.mark.parametrize("what", ["slots", "batches", "cover", "captured", "no_memory"])
 def test_lifetimes(model, what):
     out = subprocess.run([model, what], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stderr[-3000:]
