@@ -337,8 +337,7 @@ def bench_simulate(args):
     """The measurement simulator of eq. (1) and eq. (16) on the workload's
     geometry: frames d P_j x, 2-D DFTs, intensities and their maximum, Poisson
     draws.  One step = one pmace_simulate call over every position (it
-    synchronises twice: positions are checked on the host, the photon scale is
-    read back)."""
+    synchronises once, for the photon scale)."""
     import torch
     from paper_2111_14240_amd import pmace, synth
     cfg = dict(synth.CONFIGS[args.config])
@@ -387,7 +386,7 @@ def bench_simulate(args):
         "data": "synthetic",
         "config": {"workload": f"simulate {args.config}: object {n}x{n}, probe {np_}x{np_}, {J} positions, "
                                f"Poisson peak {peak:g}"},
-        "roofline": {"bound": "hbm", "kernel": "pmace_simulate: frames_k, fft2 passes, intensity_k, poisson_k",
+        "roofline": {"bound": "hbm", "kernel": "pmace_simulate: sim_rows_k, sim_cols_k (Np <= 128: sim_small_k), poisson_k",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None, "algorithmic_bytes_per_step": B},
         "wall_s": wall, "photon_scale": scale, "mean_count": zs / z.numel(),

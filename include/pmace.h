@@ -116,9 +116,9 @@ size_t pmace_footprint(const pmace_params* params);
 
 /* Alg. 1 initialisation: v_j = P_j x0 for every j.  Also computes
  * y = sqrt(z) (eq. (2)), the weights |d|^kappa and Lambda^{-1} of eq. (11)
- * (Lambda^{-1} := 0 where Lambda = 0) and D^{-1} (in FP64 on the host from a
- * copy of the probe), and the starting reconstruction x0 restricted to the
- * covered pixels.
+ * (Lambda^{-1} := 0 where Lambda = 0) and D^{-1} (in FP64, rounded once), and
+ * the starting reconstruction x0 restricted to the covered pixels (x0 may hold
+ * anything where no patch covers it).
  *   probe_d     np*np c64, the known probe d (Sec. II)
  *   pos_d       num_pos x 2 int32 (row, col) top-left patch offsets, each in
  *               [0, n1-np] x [0, n2-np]  (P_j, Sec. II)

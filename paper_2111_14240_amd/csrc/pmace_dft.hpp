@@ -267,7 +267,7 @@ template <int N> constexpr int row_cap() { return N / exch_phases<N>() + Geo<N>:
 template <int N> constexpr int col_rows() { return N / exch_phases<N>(); }
 
 // W_N^m = exp(-2 pi i m / N), m = 0..N-1, into LDS from the reconstruction's
-// table (computed in FP64 on the host and rounded once).
+// table (computed in FP64 by the set-up and rounded once).
 template <int N> __device__ __forceinline__ void load_twiddles(float2* tw, const float2* twn, int tid,
                                                               int nthreads) {
   for (int m = tid; m < N; m += nthreads) tw[m] = twn[m];

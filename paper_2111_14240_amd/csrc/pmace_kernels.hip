@@ -793,7 +793,7 @@ __global__ void __launch_bounds__(row_threads<NP>()) agent_rowsinv_batch(const R
 // -------------------------------------------------------------------------
 // Consensus (eq. (11)) without atomics.  Each thread owns one object pixel
 // of a GT_R x GT_C tile and adds the contributions of the patches that cover
-// it, walking the tile's position list (built on the host, ascending j):
+// it, walking the tile's position list (ascending j):
 //   PMACE : |d|^kappa t_j = (|d|^kappa / d) s_j, |d|^kappa t_j where d == 0 (the
 //           sum S of the weighted states),
 //   SHARP+: the overlap numerators conj(d) P_a s_j left in the stage buffer
@@ -2004,9 +2004,10 @@ static void rowspec_rows(const Recon& h, int j0, int cnt, hipStream_t st) {
   constexpr int NB = NP / rb_of<NP>(), RT = row_threads<NP>();
   if constexpr (NP == 256) {
     // about three positions per workgroup, in whole rounds of the 1024
-    // workgroups (16 to a position) that the chip holds; one for fewer than
-    // two rounds of them
-    const int groups = cnt >= 128 ? std::max(64, (cnt / 3 + 32) / 64 * 64) : cnt;
+    // workgroups of 16 rows (NB to a position) that the chip holds; one for
+    // fewer than two rounds of them
+    constexpr int R = 1024 / NB;
+    const int groups = cnt >= 2 * R ? std::max(R, (cnt / 3 + R / 2) / R * R) : cnt;
     hipLaunchKernelGGL((agent_rows_multi<NP, METHOD, NT, CHECK>), dim3(groups * NB), dim3(RT), 0, st, h, j0, cnt,
                        groups);
   } else if constexpr (CHECK) {

@@ -127,9 +127,8 @@ def cmd_build(args):
 
 
 def _time_library(lib, workloads, iters, chunks=(0,), flags=0, ppw=0, method=0):
-    """Run in a fresh process: load `lib`, time `iters` iterations (one graph
-    replay each) per workload, return ms per iteration (method 1: SHARP+,
-    beta 0.8)."""
+    """Run in a fresh process: load `lib`, time `iters` iterations per workload,
+    return ms per iteration (method 1: SHARP+, beta 0.8)."""
     import torch
     from . import pmace
     pmace.load_library(lib)
