@@ -777,13 +777,15 @@ pmace_status pmace_iterate(pmace_ctx* c, int32_t n_iter) {
     if (hipGetLastError() != hipSuccess) return record(c, PMACE_EDEVICE);
   }
   ++c->resets;
-  // Iterations are launched as they are: the host queues one in 8 to 12 us,
-  // the shortest (36 positions of 32^2) runs in 10.  A graph of kGraphIters of
-  // them closes the gaps between the smallest kernels (np 32: 10.9 -> 9.5 us
-  // per iteration; np 96: 24.7 -> 24.5; np 256: nothing, and a graph of one
-  // iteration is slower than its launches at every size), but costs 250 us to
-  // capture, so it is made for Np <= 64 once kCaptureFrom iterations have been
-  // asked for.  Under a caller's capture there are launches only.
+  // Iterations are launched as they are: the host queues one in 5 to 7 us, the
+  // shortest (36 positions of 32^2) runs in 8.  A graph of kGraphIters of them
+  // closes the gaps between the smallest kernels (36 positions of 32^2: 8.0 ->
+  // 7.2 us per iteration; 64 of 48^2: 11.3 -> 10.7; 144 of 64^2: 14.4 -> 13.9;
+  // np 96 and 256: nothing, and a graph of one iteration is slower than its
+  // launches at every size), but costs 100 to 300 us to capture, the first of
+  // a process 3 to 4 ms, so it is made for Np <= 64 once kCaptureFrom
+  // iterations have been asked for.  Under a caller's capture there are
+  // launches only.
   constexpr int kGraphIters = 32;
   constexpr long long kCaptureFrom = 256;
   c->asked += n_iter;
