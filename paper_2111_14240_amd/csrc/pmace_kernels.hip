@@ -877,7 +877,9 @@ __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int 
   // load nothing and add zero times zero: read and multiplied by a zero weight,
   // a NaN in any patch's first element reached pixels that it has no part in,
   // and a pass of 36 positions of 32^2 took 73 us against 70, the 16 mixed
-  // members 1698 against 1659.
+  // members 1698 against 1659.  SHARP+, which has no weight, reads the first
+  // element there and discards it (behind the test 144 positions of 64^2 took
+  // 17.4 us an iteration against 16.9).
   for (int i0 = part; i0 < ti.y; i0 += U * GT_K) {
     float2 u[U], w[U];
 #pragma unroll
@@ -886,11 +888,17 @@ __device__ __forceinline__ void consensus_gather_body(const Recon& g, const int 
       const int2 e = list[i < ti.y ? i : ti.y - 1];  // (j, patch origin relative to the tile's)
       const unsigned rr = (unsigned)(lr - (e.y >> 16)), cc = (unsigned)(lc - (int)(short)e.y);
       const bool in = rr < (unsigned)NP && cc < (unsigned)NP && i < ti.y;
+      const float2* patch = src + (size_t)(e.x - jb) * NP * NP;
       const unsigned o = rr * NP + cc;
-      u[k] = w[k] = make_float2(0.f, 0.f);
-      if (in) {
-        u[k] = src[(size_t)(e.x - jb) * NP * NP + o];
-        if constexpr (METHOD == kPMACE) w[k] = g.gw[o];
+      if constexpr (METHOD == kPMACE) {
+        u[k] = w[k] = make_float2(0.f, 0.f);
+        if (in) {
+          u[k] = patch[o];
+          w[k] = g.gw[o];
+        }
+      } else {
+        u[k] = patch[in ? o : 0u];
+        if (!in) u[k] = make_float2(0.f, 0.f);
       }
     }
 #pragma unroll
