@@ -332,9 +332,14 @@ struct Cover {
   }
   bool at(int r, int c) { return cell(r, c) > 0; }
 };
-// Share of empty gather tiles or row items from which they are left out (the
-// copy of the host's lists and its wait add some 30 us to a set-up).
+// A chunk's empty gather tiles or row items are left out where they are this
+// share of all, and so many that the iterations gain the 10 us and more that
+// the copy of the host's lists and its wait add to the set-up: an empty tile
+// takes an iteration 2 ns (fused with the image update) or 0.5, an empty row
+// item 0.4.
 constexpr double kEmptyShare = 1.0 / 16.0;
+constexpr int kEmptyTiles = 256, kEmptyItems = 1024;
+bool leave_out(int all, int kept, int least) { return all - kept >= std::max(least, (int)(kEmptyShare * all)); }
 
 // The places of a chunk's gather tiles without those that list nothing, row by
 // row, ordered over the XCDs as setup_tiles_k orders whole rows.
@@ -694,10 +699,11 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
 
   // The rows that each chunk covers give its gather tiles (GT_R x GT_C object
   // pixels) and row items; their lists are built on the device.  On a sparse
-  // or unordered scan many list no position: from kEmptyShare of a chunk's on
-  // they are left out here.  (64 positions of 64^2 on 4096^2: an iteration
-  // 152 us with all of them at work, 39 ending at once, 15.6 left out; 200 of
-  // 160^2, unordered on 2048 x 4096 in chunks of 25: 595, 510, 377.)
+  // or unordered scan many list no position: those that the iterations walk
+  // (the row-spectrum agent its items, the split agent neither) are left out
+  // here.  (64 positions of 64^2 on 4096^2: an iteration 152 us with all of
+  // them at work, 39 ending at once, 15.6 left out; 200 of 160^2, unordered on
+  // 2048 x 4096 in chunks of 25, three-pass: 595, 510, 377.)
   const int tiles_c = (n2 + pmace::GT_C - 1) / pmace::GT_C, nseg = cr_segments(p);
   size_t listed = 0;   // bytes of slots and rows whose copies have not been waited for
   c->chunk_tiles.assign(nch, make_int2(0, 0));
@@ -713,29 +719,37 @@ pmace_status pmace_init(const pmace_params* params, const void* probe_d, const i
     const int tiles_r = (hi - lo + pmace::GT_R - 1) / pmace::GT_R;
     int ntiles = tiles_r * tiles_c, nitems = h.rowspec ? (hi - lo) * nseg : 0;
     pmace::SetupChunk k{ja, jb, lo, tiles_r, tile0, 0, 0, item0, nullptr, nullptr};
-    Cover tiles(tiles_r, tiles_c), segs(h.rowspec ? hi - lo : 0, nseg);
-    for (int j = ja; j < jb; ++j) {
-      const int r = pos[2 * j] - lo, cc = pos[2 * j + 1];
-      tiles.add(r / pmace::GT_R, (r + np - 1) / pmace::GT_R, cc / pmace::GT_C, (cc + np - 1) / pmace::GT_C);
-      if (h.rowspec) segs.add(r, r + np - 1, cc / pmace::CR_W, (cc + np - 1) / pmace::CR_W);
+    if (!h.rowspec && !h.split && ntiles > kEmptyTiles) {
+      Cover tiles(tiles_r, tiles_c);
+      for (int j = ja; j < jb; ++j) {
+        const int r = pos[2 * j] - lo, cc = pos[2 * j + 1];
+        tiles.add(r / pmace::GT_R, (r + np - 1) / pmace::GT_R, cc / pmace::GT_C, (cc + np - 1) / pmace::GT_C);
+      }
+      const int kept = tiles.close();
+      if (leave_out(ntiles, kept, kEmptyTiles)) {
+        slots.push_back(tile_slots(tiles, np_large(np)));
+        k.slots = slots.back().data();
+        listed += slots.back().size() * sizeof(int);
+        ntiles = kept;
+      }
     }
-    const int kept = tiles.close();
-    if (ntiles - kept >= kEmptyShare * ntiles) {
-      slots.push_back(tile_slots(tiles, np_large(np)));
-      k.slots = slots.back().data();
-      listed += slots.back().size() * sizeof(int);
-      ntiles = kept;
-    }
-    const int kept_items = segs.close();
-    if (nitems > 0 && nitems - kept_items >= kEmptyShare * nitems) {
-      rows.emplace_back();
-      rows.back().reserve(kept_items);
-      for (int sg = 0; sg < nseg; ++sg)
-        for (int r = 0; r < hi - lo; ++r)
-          if (segs.at(r, sg)) rows.back().push_back(make_int2(lo + r, sg * pmace::CR_W));
-      k.rows = rows.back().data();
-      listed += rows.back().size() * sizeof(int2);
-      nitems = kept_items;
+    if (nitems > kEmptyItems) {
+      Cover segs(hi - lo, nseg);
+      for (int j = ja; j < jb; ++j) {
+        const int r = pos[2 * j] - lo, cc = pos[2 * j + 1];
+        segs.add(r, r + np - 1, cc / pmace::CR_W, (cc + np - 1) / pmace::CR_W);
+      }
+      const int kept = segs.close();
+      if (leave_out(nitems, kept, kEmptyItems)) {
+        rows.emplace_back();
+        rows.back().reserve(kept);
+        for (int sg = 0; sg < nseg; ++sg)
+          for (int r = 0; r < hi - lo; ++r)
+            if (segs.at(r, sg)) rows.back().push_back(make_int2(lo + r, sg * pmace::CR_W));
+        k.rows = rows.back().data();
+        listed += rows.back().size() * sizeof(int2);
+        nitems = kept;
+      }
     }
     k.ntiles = ntiles;
     k.nitems = nitems;

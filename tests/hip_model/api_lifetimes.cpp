@@ -314,7 +314,7 @@ static void cover() {
   for (int np : {32, 128, 160, 256})
     for (int chunk : {0, 3}) {
       pmace_params p{};
-      p.n1 = 700;
+      p.n1 = np > 128 ? 2200 : 700;
       p.n2 = 2500;
       p.np = np;
       p.num_pos = 14;
@@ -326,14 +326,18 @@ static void cover() {
       std::vector<char> ws(pmace_footprint(&p));
       std::vector<int> pos(28);
       for (int j = 0; j < 14; ++j) {
-        pos[2 * j] = rnd(700 - np + 1);
+        pos[2 * j] = rnd(p.n1 - np + 1);
         pos[2 * j + 1] = rnd(2500 - np + 1);
       }
       std::vector<float> any(16);
       pmace_ctx* x = nullptr;
       CHECK(pmace_init(&p, any.data(), pos.data(), any.data(), nullptr, ws.data(), ws.size(), nullptr, &x) == PMACE_OK);
-      CHECK(x->ngitems > 0 && x->ngitems < (int)max_tiles(p));
+      int items = 0;
+      for (const int2& r : x->chunk_rows) items += r.y;
+      if (np <= 128) CHECK(x->ngitems > 0 && x->ngitems < (int)max_tiles(p) - kEmptyTiles && items == 0);
+      if (np > 128 && chunk == 0) CHECK(items > 0 && items < (int)cr_items(p) - kEmptyItems);
       for (int t = 0; t < x->ngitems; ++t) CHECK(x->h.tiles[t].y == 1);
+      for (int t = 0; np > 128 && chunk == 0 && t < items; ++t) CHECK(x->h.citems[t].y == 1);
       pmace_destroy(x);
     }
 }
